@@ -156,6 +156,32 @@ hx_status validate_schedule(const hx_pipeline* p, const hx_schedule& s) {
     return HX_OK;
 }
 
+// Pass 1 of STORE on one image.  Tiles of up to kShortTile rows take the
+// short sweep: such a tile spends its time fetching the long sweep's
+// unrolled code (1080p k5, 8-row tiles: 20.2 us long, 11 us short at 256
+// columns; 701x1283 k3 18.0 and 7.8; 4096x4096 k7 117 and 53).  Taller
+// tiles amortise that code and its longer loop body is the faster one.
+constexpr int kShortTile = 16;
+static hipError_t launch_store(int ks, int c, int ty, const ImgArgs& a, const Taps& t,
+                               float theta, hipStream_t s) {
+    if (ty <= kShortTile) return launch_tile(SM_STORE, ks, c, ty, a, t, StageOut{}, s);
+    return launch_sweep(SM_STORE, ks, c, ty, a, t, theta, s);
+}
+
+// The untuned STORE tile of an H x W image.  Narrow, short tiles while the
+// image has too few rows and columns to give every SIMD a wave; wider and
+// taller ones (fewer halo rows and columns computed) once it does.
+// Measured best pass 1, us, as columns per lane x rows: 256x256 k5 1x8 5.2
+// (2x8 6.3, 4x8 8.4); 701x1283 k3 1x8 6.2 (2x8 6.3); 1080x1920 k5 1x8 10.0,
+// 2x8 10.1 (4x8 10.8); 2048x2048 k5 2x8 14.3 (1x8 15.2, 4x8 15.8);
+// 4096x4096 k7 2x16 39.4 (1x16 43.9, 2x8 46.8, 64-row long tiles 52.9).
+static hx_schedule store_schedule(int64_t H, int64_t W) {
+    const int64_t px = H * W;
+    const int c = px <= (int64_t(3) << 19) ? 1 : 2;
+    const int th = px <= (int64_t(8) << 20) ? 8 : 16;
+    return hx_schedule{64 * c, th, 4, HX_PASS_STORE, HX_REDUCE_TREE};
+}
+
 hx_schedule choose_schedule(const hx_pipeline* p, int64_t H, int64_t W) {
     if (p->forced) return p->forced_sched;
     hx_schedule s;
@@ -163,16 +189,21 @@ hx_schedule choose_schedule(const hx_pipeline* p, int64_t H, int64_t W) {
     if (it != p->tuned.end()) {
         s = it->second;
     } else if (fused_ks(p->prm.ksize)) {
-        // Untuned: 256-column tiles, one wave each, and the tallest tile of
-        // 64, 32, 16 or 8 rows that still gives every SIMD a wave (taller
-        // tiles re-read fewer halo rows; a 1080p image in 64-row tiles
-        // would leave seven SIMDs in eight idle, and its 8-row tiles
-        // finish a call 5 % sooner than 16-row ones).
-        const int64_t simds = 4 * (int64_t)(p->cu_count > 0 ? p->cu_count : 256);
-        const int64_t strips = (W + 239) / 240;
-        int th = 64;
-        while (th > 8 && strips * ((H + th - 1) / th) < simds) th /= 2;
-        s = hx_schedule{256, th, 4, HX_PASS_STORE, HX_REDUCE_TREE};
+        const hx_params& q = p->prm;
+        if (q.fusion_depth || q.tile_w || q.tile_h ||
+            (q.pass_mode && q.pass_mode != HX_PASS_STORE)) {
+            // Some knobs were fixed at creation: 256-column tiles for the
+            // others' long sweep, the tallest of 64, 32, 16 or 8 rows that
+            // still gives every SIMD a wave (taller tiles re-read fewer
+            // halo rows).
+            const int64_t simds = 4 * (int64_t)(p->cu_count > 0 ? p->cu_count : 256);
+            const int64_t strips = (W + 239) / 240;
+            int th = 64;
+            while (th > 8 && strips * ((H + th - 1) / th) < simds) th /= 2;
+            s = hx_schedule{256, th, 4, HX_PASS_STORE, HX_REDUCE_TREE};
+        } else {
+            s = store_schedule(H, W);
+        }
     } else {
         s = hx_schedule{64, 16, 1, HX_PASS_STORE, HX_REDUCE_TREE};
     }
@@ -221,6 +252,7 @@ static ImgArgs base_args(const hx_image* img, uint32_t* slot, float* d_max) {
     a.H = (int32_t)img->height;
     a.W = (int32_t)img->width;
     a.op = round4(img->width);
+    a.ways = 1;
     return a;
 }
 
@@ -253,8 +285,8 @@ hx_status run_image(hx_pipeline* p, const hx_image* img, float* d_max,
     // slot, so when the previous call left this one at zero the form needs
     // no clearing launch; every other form clears both slots first.
     uint32_t* const slots = (uint32_t*)p->slot1.ptr;
-    uint32_t* const slot = slots + p->img_parity;
-    uint32_t* const next = slots + (p->img_parity ^ 1);
+    uint32_t* const slot = slots + p->img_parity * kSlotWords;
+    uint32_t* const next = slots + (p->img_parity ^ 1) * kSlotWords;
     p->img_parity ^= 1;
     p->img_last_slot = slot;
     const bool store_fused = s.fusion_depth == 4 && s.pass_mode == HX_PASS_STORE;
@@ -263,12 +295,13 @@ hx_status run_image(hx_pipeline* p, const hx_image* img, float* d_max,
     ImgArgs a = base_args(img, slot, d_max);
     const float theta = p->prm.thresh_frac;
     const int ks = p->prm.ksize;
-    if (!(store_fused && slot_zero)) HX_TRY(launch_fill_u32(slots, 0u, 2, stream));
+    if (!(store_fused && slot_zero)) HX_TRY(launch_fill_u32(slots, 0u, 2 * kSlotWords, stream));
     if (s.fusion_depth == 4) {
         const int c = s.tile_w / 64;
         if (s.pass_mode == HX_PASS_STORE) {
             a.fout = (float*)p->planeA.ptr;
-            HX_TRY(launch_sweep(SM_STORE, ks, c, s.tile_h, a, p->taps, theta, stream));
+            a.ways = kSlotWays;
+            HX_TRY(launch_store(ks, c, s.tile_h, a, p->taps, theta, stream));
             HX_TRY(launch_threshold_code(a, theta, stream, next));
         } else {
             HX_TRY(launch_sweep(SM_MAXONLY, ks, c, s.tile_h, a, p->taps, theta, stream));
@@ -787,7 +820,7 @@ static hx_status alloc_scratch(hx_pipeline* p) {
     const size_t pe = (size_t)p->plane_elems;
     HX_TRY(hipStreamCreateWithFlags(&p->capture_stream, hipStreamNonBlocking));
     HX_TRY(hipEventCreateWithFlags(&p->img_ev, hipEventDisableTiming));
-    HX_TRY(p->slot1.alloc(256, m));
+    HX_TRY(p->slot1.alloc(2 * kSlotWords * sizeof(uint32_t), m));
     if (f & (HX_FORM_IMAGE | HX_FORM_STAGES | HX_FORM_SRAD))
         HX_TRY(p->planeA.alloc(pe * sizeof(float), m));
     if (f & (HX_FORM_STAGES | HX_FORM_SRAD)) HX_TRY(p->planeL.alloc(pe * sizeof(float), m));
@@ -1007,19 +1040,15 @@ hx_status hx_edge_detect_static(hx_pipeline* p, const hx_image* img, float* d_ma
                     (long long)need, (long long)HX_STATIC_MAX_ELEMS);
     uint8_t* base = static_scratch_ptr(p->device);
     if (!base) return fail(HX_E_HIP, "static scratch of device %d not set up", p->device);
-    // The untuned fused tile: 256 columns, the tallest of 64/32/16 rows that
-    // gives every SIMD a tile.
-    const int64_t simds = 4 * (int64_t)(p->cu_count > 0 ? p->cu_count : 256);
-    const int64_t strips = (img->width + 239) / 240;
-    int th = 64;
-    while (th > 16 && strips * ((img->height + th - 1) / th) < simds) th /= 2;
+    const hx_schedule sc = store_schedule(img->height, img->width);
     DeviceGuard g(p->device);
     uint32_t* slot = reinterpret_cast<uint32_t*>(base);
     ImgArgs a = base_args(img, slot, d_max);
+    a.ways = 256 / (4 * kSlotStep);
     a.fout = reinterpret_cast<float*>(base + 256);
     const float theta = p->prm.thresh_frac;
-    HX_TRY(launch_fill_u32(slot, 0u, 1, stream));
-    HX_TRY(launch_sweep(SM_STORE, p->prm.ksize, 4, th, a, p->taps, theta, stream));
+    HX_TRY(launch_fill_u32(slot, 0u, 64, stream));
+    HX_TRY(launch_store(p->prm.ksize, sc.tile_w / 64, sc.tile_h, a, p->taps, theta, stream));
     HX_TRY(launch_threshold_code(a, theta, stream));
     return HX_OK;
 }

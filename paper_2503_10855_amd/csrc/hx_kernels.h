@@ -20,6 +20,20 @@ enum SweepMode : int {
                      // the list of pixels it set (SpecTile), and the max
 };
 
+// What the short sweep computes and writes beyond SweepMode.
+enum TileMode : int {
+    TM_STAGES = 6,   // SM_STORE plus B, L, G and Z to caller planes
+    TM_BLUR = 7,     // B only, to fout
+};
+
+// Caller planes of TM_STAGES (each nullable), dense: pitch W.
+struct StageOut {
+    float* B;
+    float* L;
+    float* G;
+    uint8_t* Z;
+};
+
 // Where one SM_SPEC tile lists the pixels whose mask bit it set.  One
 // entry per (row, lane) that set a bit, packed in row then lane order:
 // code[] holds G^2 of the lane's C pixels of that row, and row[] packs
@@ -31,6 +45,16 @@ struct SpecTile {
     uint32_t n;
     uint32_t cap;    // entries the tile may write; n may exceed it
 };
+
+// A per-image STORE call's max slot is spread over several words, one per
+// 64 bytes (ImgArgs::ways of them, a power of two): a workgroup folds its
+// maximum into the word of its index, and the threshold kernel takes the
+// max of the words, one per lane.  One word serialises its atomics (about
+// 10 ns each across the XCDs: a 1080p image in 1180 workgroups took 19.8 us
+// with one word and 11.1 us with 64).
+constexpr int kSlotWays = 64;
+constexpr int kSlotStep = 16;    // words from one to the next
+constexpr int kSlotWords = kSlotWays * kSlotStep;
 
 // One image as the kernels see it.  Pitches are in elements of the
 // respective buffer.  fout: pass-1 code (STORE), B (BG) or L (BGL);
@@ -44,7 +68,8 @@ struct ImgArgs {
     float* fout;
     float* g2;
     int64_t op;
-    uint32_t* slot;   // max G^2 bits of this image
+    uint32_t* slot;   // max G^2 bits of this image (STORE, per image: of
+                      // each of `ways` words, kSlotStep apart)
     float* dmax;      // optional: receives M = sqrt(max G^2)
     int32_t H, W;
     // Batched SPECULATE: the image's pass-1 tile t lists its pixels in
@@ -52,7 +77,18 @@ struct ImgArgs {
     uint32_t list_base, list_cap;
     // Batched calls: rows per sweep tile of this image (a multiple of 8).
     int32_t ty;
+    int32_t ways;     // words of the max slot (1 outside the STORE forms)
 };
+
+// The word of the max slot workgroup `block` folds into.
+__device__ __forceinline__ uint32_t* slot_word(const ImgArgs& a, int block) {
+    return a.slot + (block & (a.ways - 1)) * kSlotStep;
+}
+// The image's max G^2 bits from all words of its slot, in every lane.
+__device__ __forceinline__ uint32_t slot_max(const ImgArgs& a) {
+    const int l = lane_id();
+    return __float_as_uint(wave_max(l < a.ways ? __uint_as_float(a.slot[l * kSlotStep]) : 0.0f));
+}
 
 // Geometry of a register-sweep tile (one wave64): C input columns per lane,
 // TY output rows; KS the blur size.
@@ -74,9 +110,13 @@ bool sweep_supported(int ks, int c, int ty);
 hipError_t launch_fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t s);
 hipError_t launch_sweep(int mode, int ks, int c, int ty, const ImgArgs& a,
                         const Taps& t, float theta, hipStream_t s);
+// The short sweep (tile_impl.h): SM_STORE or TM_STAGES for ks 1, 3, 5, 7,
+// TM_BLUR for the larger sizes; c columns per lane, ty rows per tile (even).
+hipError_t launch_tile(int mode, int ks, int c, int ty, const ImgArgs& a, const Taps& t,
+                       const StageOut& so, hipStream_t s);
 // Pass 2 of STORE: code -> mask, and M into dmax.
-// zero_next (nullable): a word the kernel sets to 0 (the slot of the next
-// per-image call, which no wave of this kernel reads).
+// zero_next (nullable): a slot whose words the kernel sets to 0 (the next
+// per-image call's, which no wave of this kernel reads).
 hipError_t launch_threshold_code(const ImgArgs& a, float theta, hipStream_t s,
                                  uint32_t* zero_next = nullptr);
 // Write M into a.dmax from a.slot (one thread).

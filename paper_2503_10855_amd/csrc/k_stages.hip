@@ -238,11 +238,12 @@ __global__ __launch_bounds__(256) void k_threshold_zg(ImgArgs a, StageBufs b,
 // Pass 2 of STORE on one image: code -> mask, 4 pixels per thread.
 __global__ __launch_bounds__(256) void k_threshold_code(ImgArgs a, float theta,
                                                         uint32_t* zero_next) {
-    const uint32_t m2 = *a.slot;
+    const uint32_t m2 = slot_max(a);
     const float thr2 = thr2_from(m2, theta);
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        if (a.dmax) *a.dmax = max_from(m2);
-        if (zero_next) *zero_next = 0u;  // the next per-image call's max slot
+    if (blockIdx.x == 0) {
+        if (threadIdx.x == 0 && a.dmax) *a.dmax = max_from(m2);
+        // The next per-image call's max slot.
+        if (zero_next && (int)threadIdx.x < a.ways) zero_next[threadIdx.x * kSlotStep] = 0u;
     }
     const int wq = (a.W + 3) / 4;
     const bool mvec = ((reinterpret_cast<uintptr_t>(a.mask) % 4) == 0) & ((a.mp % 4) == 0);

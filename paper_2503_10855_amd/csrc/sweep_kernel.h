@@ -22,7 +22,8 @@ __global__ __launch_bounds__(256) void k_sweep(ImgArgs a, Taps tp, float theta, 
     sweep_tile<KS, C, MODE>(a, tp, bx * S::OW, by * ty, ty, thr2, gmax, nullptr, (by & 1) != 0);
     if constexpr (S::DO_MAX) {
         gmax = wave_max(gmax);
-        if (lane_id() == 0) atomic_max_g2(a.slot, gmax);
+        if (lane_id() == 0)
+            atomic_max_g2(MODE == SM_STORE ? slot_word(a, blockIdx.x) : a.slot, gmax);
     }
 }
 
