@@ -29,9 +29,15 @@ PLAIN = ["k_stages.hip", "k_sweep.hip", "k_tile.hip", "k_batch.hip", "hx_api.cpp
          "hx_tune.hip", "hx_serve.cpp", "hx_sched.cpp", "k_srad.hip", "hx_log.cpp"]
 SWEEP_KS = (3, 5, 7)
 SWEEP_MODES = (0, 1, 2, 3, 4)
+BATCH_PARTS = (1, 2, 3, 0)
 
 
 def _units():
+    # The longest compiles first.
+    for part in BATCH_PARTS:
+        for k in SWEEP_KS:
+            yield ("batch_inst.hip", os.path.join(OUT, f"batch_k{k}_p{part}.o"),
+                   [f"-DHX_KS={k}", f"-DHX_PART={part}"])
     for f in PLAIN:
         yield f, os.path.join(OUT, f.rsplit(".", 1)[0] + ".o"), []
     for k in SWEEP_KS:

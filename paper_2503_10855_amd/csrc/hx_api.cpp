@@ -106,7 +106,13 @@ static BatchCaps batch_caps(const hx_params& prm, bool store_plane) {
     c.items1 = 2 * ((P + (int64_t)g.ow() * g.ty - 1) / ((int64_t)g.ow() * g.ty)) + 16 * n + 4096;
     c.items2 = std::max<int64_t>(c.items1, P / 1024 + 2 * n + 1024);
     c.items0 = 5 * c.items1;
-    c.list_entries = P / 16 + 16;
+    // One listing entry (four pixels of a row) per 16 pixels, and for small
+    // pipelines all of them, up to 2^17: in small images edges are dense.
+    c.list_entries = std::max(P / 16 + 16, std::min<int64_t>(P / 4 + 16 * n, 1 << 17));
+    // Max slots and bounds of neighbouring images 64 bytes apart, so that
+    // atomics of different images do not share a cache line (with very many
+    // images they spread by themselves).
+    c.slot_step = n <= 4096 ? kSlotStep : 1;
     c.table_bytes = batch_table_bytes((int)n, c.items1, c.items2, c.items0);
     c.code_elems = store_plane ? plane_capacity(P) : 0;
     return c;
@@ -156,12 +162,7 @@ hx_status validate_schedule(const hx_pipeline* p, const hx_schedule& s) {
     return HX_OK;
 }
 
-// Pass 1 of STORE on one image.  Tiles of up to kShortTile rows take the
-// short sweep: such a tile spends its time fetching the long sweep's
-// unrolled code (1080p k5, 8-row tiles: 20.2 us long, 11 us short at 256
-// columns; 701x1283 k3 18.0 and 7.8; 4096x4096 k7 117 and 53).  Taller
-// tiles amortise that code and its longer loop body is the faster one.
-constexpr int kShortTile = 16;
+// Pass 1 of STORE on one image.
 static hipError_t launch_store(int ks, int c, int ty, const ImgArgs& a, const Taps& t,
                                float theta, hipStream_t s) {
     if (ty <= kShortTile) return launch_tile(SM_STORE, ks, c, ty, a, t, StageOut{}, s);
@@ -378,16 +379,18 @@ static hx_status ctx_init(hx_pipeline* p, BatchContext& c) {
     MemStats& m = p->mem;
     const BatchCaps& k = p->caps;
     const int64_t n = p->prm.max_images;
-    HX_TRY(c.slots.alloc(sizeof(uint32_t) * n, m));
-    // Bounds (8 B each) and the epoch, cleared once here.
-    const int64_t words = 2 * n + 2;
-    HX_TRY(c.spec_state.alloc(sizeof(uint32_t) * words, m));
-    HX_TRY(hipMemset(c.spec_state.ptr, 0, sizeof(uint32_t) * words));
+    // One buffer: bounds (8 B each), the epoch and the redo queue's length,
+    // cleared once here; then the max slots, the list counts, the redo queue.
+    const int64_t words = 2 * n * k.slot_step + 2 * kSlotStep;
+    HX_TRY(c.state.alloc(sizeof(uint32_t) * (words + n * k.slot_step + 2 * k.items1), m));
+    HX_TRY(hipMemset(c.state.ptr, 0, sizeof(uint32_t) * words));
+    c.slots = (uint32_t*)c.state.ptr + words;
+    c.cand_n = c.slots + n * k.slot_step;
+    c.redo = (int32_t*)(c.cand_n + k.items1);
     HX_TRY(c.table.alloc(k.table_bytes, m));
     HX_TRY(c.h_table.alloc(k.table_bytes, m));
     HX_TRY(c.cand_code.alloc((size_t)k.list_entries * batch_sweep_c() * sizeof(float), m));
     HX_TRY(c.cand_row.alloc((size_t)k.list_entries * sizeof(int32_t), m));
-    HX_TRY(c.cand_n.alloc((size_t)k.items1 * sizeof(uint32_t), m));
     if (k.code_elems) HX_TRY(c.code.alloc((size_t)k.code_elems * sizeof(float), m));
     HX_TRY(hipEventCreateWithFlags(&c.ev_done, hipEventDisableTiming));
     for (auto& e : c.ev_t) HX_TRY(hipEventCreate(&e));
@@ -402,12 +405,10 @@ static void ctx_release(BatchContext& c) {
     }
     c.table.release();
     c.h_table.release();
-    c.slots.release();
-    c.spec_state.release();
+    c.state.release();
     c.code.release();
     c.cand_code.release();
     c.cand_row.release();
-    c.cand_n.release();
     if (c.ev_done) (void)hipEventDestroy(c.ev_done);
     for (auto& e : c.ev_t)
         if (e) (void)hipEventDestroy(e);
@@ -424,38 +425,30 @@ hx_status ctx_wait(BatchContext& c) {
 // Enqueue [reset, pass 1, pass 2] (SPECULATE: [pass 0, pass 1, pass 2])
 // for this context on stream s;
 // with `timed`, bracket each launch with the context's timing events
-// (ev_t: 0 reset 1 pass-0 4 pass-1 2 pass-2 3).  Each pass runs one wave
-// per item (batch_wg_waves() waves per workgroup): a grid sized to the
-// batch measured faster than persistent workgroups striding over the
-// items.
-static int phase_grid(const BatchContext& c, int ph) {
-    const int w = batch_wg_waves();
-    return (int)std::max<int64_t>(1, (c.n_items[ph] + w - 1) / w);
-}
-
+// (ev_t: 0 reset 1 pass-0 4 pass-1 2 pass-2 3).  Grids are sized to the
+// batch (measured faster than persistent workgroups striding over items).
 static hipError_t enqueue_phases(hx_pipeline* p, BatchContext& c, int pass, hipStream_t s,
                                  bool timed = false) {
     const int ks = p->prm.ksize;
     hipError_t e = timed ? hipEventRecord(c.ev_t[0], s) : hipSuccess;
     if (e == hipSuccess && pass != HX_PASS_SPECULATE)
-        e = launch_batch_reset(c.table.ptr, (uint32_t*)c.slots.ptr, (int)p->prm.max_images, s);
+        e = launch_batch_reset(c.table.ptr, (int)p->prm.max_images, s);
     if (e == hipSuccess && timed) e = hipEventRecord(c.ev_t[1], s);
     if (e == hipSuccess && pass == HX_PASS_SPECULATE)
-        e = launch_batch_phase(ks, pass, 0, c.table.ptr, p->taps, phase_grid(c, 0), s);
+        e = launch_batch_phase(ks, pass, 0, c.last_ty, c.n_items[0], c.table.ptr, p->taps, s);
     if (e == hipSuccess && timed) e = hipEventRecord(c.ev_t[4], s);
     if (e == hipSuccess)
-        e = launch_batch_phase(ks, pass, 1, c.table.ptr, p->taps, phase_grid(c, 1), s);
+        e = launch_batch_phase(ks, pass, 1, c.last_ty, c.n_items[1], c.table.ptr, p->taps, s);
     if (e == hipSuccess && timed) e = hipEventRecord(c.ev_t[2], s);
     if (e == hipSuccess)
-        e = launch_batch_phase(ks, pass, 2, c.table.ptr, p->taps, phase_grid(c, 2), s);
+        e = launch_batch_phase(ks, pass, 2, c.last_ty, c.n_items[2], c.table.ptr, p->taps, s);
     if (e == hipSuccess && timed) e = hipEventRecord(c.ev_t[3], s);
     return e;
 }
 
 // Capture the launches once per (context, pass mode, item counts).
 static hx_status ctx_graph(hx_pipeline* p, BatchContext& c, int pass) {
-    if (c.exec[pass] && std::memcmp(c.graph_items[pass], c.n_items, sizeof c.n_items) == 0)
-        return HX_OK;
+    if (c.exec[pass] && c.graph_matches(pass)) return HX_OK;
     if (c.exec[pass]) {
         (void)hipGraphExecDestroy(c.exec[pass]);
         (void)hipGraphDestroy(c.graph[pass]);
@@ -481,6 +474,7 @@ static hx_status ctx_graph(hx_pipeline* p, BatchContext& c, int pass) {
     c.graph[pass] = g;
     c.exec[pass] = ex;
     std::memcpy(c.graph_items[pass], c.n_items, sizeof c.n_items);
+    c.graph_ty[pass] = c.last_ty;
     return HX_OK;
 }
 
@@ -532,30 +526,38 @@ static hx_status build_table(hx_pipeline* p, BatchContext& c, const hx_image* im
     hdr.pass_mode = pass;
     hdr.theta = p->prm.thresh_frac;
     hdr.n_items0 = (int32_t)tot.p0;
+    hdr.ty = geo.ty;
     if (spec) {
         hdr.cand_code = (float*)c.cand_code.ptr;
         hdr.cand_row = (int32_t*)c.cand_row.ptr;
-        hdr.cand_n = (uint32_t*)c.cand_n.ptr;
-        hdr.bound = (unsigned long long*)c.spec_state.ptr;
-        hdr.epoch = (uint32_t*)(hdr.bound + p->prm.max_images);
+        hdr.cand_n = c.cand_n;
+        hdr.bound = (unsigned long long*)c.state.ptr;
+        hdr.bound_step = p->caps.slot_step;
+        hdr.epoch = (uint32_t*)(hdr.bound + p->prm.max_images * hdr.bound_step);
+        hdr.redo_n = hdr.epoch + kSlotStep;
+        hdr.redo = c.redo;
     }
     std::memcpy(h, &hdr, sizeof hdr);
     ImgArgs* ia = (ImgArgs*)(h + sizeof(BatchHeader));
-    int64_t code_off = 0, list_off = 0;
+    int64_t code_off = 0, list_off = 0, total_px = 0;
+    for (int i = 0; i < n; ++i) total_px += imgs[i].height * imgs[i].width;
     for (int i = 0; i < n; ++i) {
-        ia[i] = base_args(&imgs[i], (uint32_t*)c.slots.ptr + i, d_max ? d_max + i : nullptr);
+        ia[i] = base_args(&imgs[i], c.slots + (int64_t)i * p->caps.slot_step,
+                          d_max ? d_max + i : nullptr);
         ia[i].ty = geo.ty;
         if (pass == HX_PASS_STORE) ia[i].fout = (float*)c.code.ptr + code_off;
         code_off += w[i].code;
         if (spec) {
-            const uint32_t cap = spec_tile_cap(imgs[i].height, imgs[i].width, w[i].tiles);
+            const uint32_t cap =
+                spec_tile_cap(p->caps.list_entries, total_px, imgs[i].height * imgs[i].width,
+                              w[i].tiles, geo.ty);
             ia[i].list_base = (uint32_t)list_off;
             ia[i].list_cap = cap;
             list_off += (int64_t)cap * w[i].tiles;
         }
     }
     if (list_off > p->caps.list_entries)
-        return fail(HX_E_INVALID, "listing capacity exceeded");  // cannot happen: sum <= P/16
+        return fail(HX_E_INVALID, "listing capacity exceeded");  // cannot happen: shares sum to it
     BatchItem* it = (BatchItem*)(ia + n);
     for (int i = 0; i < n; ++i)
         for (int64_t t = 0; t < w[i].tiles; ++t) *it++ = BatchItem{i, (int32_t)t};
@@ -580,7 +582,7 @@ static hx_status build_table(hx_pipeline* p, BatchContext& c, const hx_image* im
 // context's first slot.  Same bits as the batched passes.
 static hx_status run_oversized(hx_pipeline* p, BatchContext& c, const hx_image& im,
                                float* d_max, hipStream_t stream) {
-    ImgArgs a = base_args(&im, (uint32_t*)c.slots.ptr, d_max);
+    ImgArgs a = base_args(&im, c.slots, d_max);
     const int ks = p->prm.ksize, cw = batch_sweep_c(), ty = batch_sweep_ty();
     HX_TRY(launch_fill_u32(a.slot, 0u, 1, stream));
     HX_TRY(launch_sweep(SM_MAXONLY, ks, cw, ty, a, p->taps, p->prm.thresh_frac, stream));
@@ -615,8 +617,7 @@ static hx_status launch_on(hx_pipeline* p, BatchContext& c, const hx_image* imgs
         HX_TRY(enqueue_phases(p, c, pass, stream));
         how = "direct launches";
     } else {
-        const bool captured = c.exec[pass] != nullptr &&
-                              std::memcmp(c.graph_items[pass], c.n_items, sizeof c.n_items) == 0;
+        const bool captured = c.exec[pass] != nullptr && c.graph_matches(pass);
         hx_status st = ctx_graph(p, c, pass);
         if (st != HX_OK) return st;
         HX_TRY(hipGraphLaunch(c.exec[pass], stream));
@@ -639,6 +640,24 @@ BatchKey batch_key(const hx_image* imgs, int32_t n) {
     return BatchKey{lg(px), lg(n)};
 }
 
+// The untuned SPECULATE tile height: 48 rows (fewer halo rows computed)
+// where that gives the chip more than two waves per SIMD of tiles, shorter
+// ones where it does not; 16 rows run the short sweep.  Whole calls, us, by
+// tile height (16 / 24 / 32 / 48 / 64 rows) and tiles of 48 rows:
+//   192 (16 x 256x256 k5)          32.4  33.1  36.0  42.6  49.3
+//   368 (2 x 1080x1920 k5)         38.2  36.0  38.2  44.1  50.5
+//   829 (64 of 64..1024 k5)        55.4  52.9  58.3  70.4  83.4
+//   1472 (8 x 1080x1920 k5)        66.1  45.5  47.3  48.1  55.7
+//   2038 (64 of 64..2048 k5)       86.3  66.6  62.7  68.0  78.0
+//   8300 (256 of 64..2048 k5)     283.7 195.4 185.2 183.9 189.8
+//   11776 (64 x 1080x1920 k5)     316.4 198.5 198.0 196.4 204.8
+static int spec_default_ty(int ks, const hx_image* imgs, int32_t n) {
+    const SweepGeom g{ks, batch_sweep_c(), 48};
+    int64_t tiles = 0;
+    for (int i = 0; i < n && tiles <= 2560; ++i) tiles += g.tiles(imgs[i].height, imgs[i].width);
+    return tiles <= 256 ? 16 : tiles <= 1280 ? 24 : tiles <= 2560 ? 32 : 48;
+}
+
 hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
                       float* d_max, int pass, int ty, hipStream_t stream, int ctx) {
     const int ks = p->prm.ksize;
@@ -657,8 +676,8 @@ hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
                 pass = it->second.pass;
         }
     }
-    if (!ty) ty = batch_sweep_ty();
     if (!pass) pass = kBatchPass;
+    if (!ty) ty = pass == HX_PASS_SPECULATE ? spec_default_ty(ks, imgs, n) : batch_sweep_ty();
     if (ty < kBatchTyMin || ty > kBatchTyMax || ty % 8 != 0)
         return fail(HX_E_INVALID, "batch tile height %d not a multiple of 8 in %d..%d", ty,
                     kBatchTyMin, kBatchTyMax);

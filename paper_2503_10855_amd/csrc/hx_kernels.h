@@ -103,6 +103,14 @@ struct SweepGeom {
     int64_t tiles(int64_t H, int64_t W) const { return strips(W) * bands(H); }
 };
 
+// Tiles of up to this many rows take the short sweep (tile_impl.h) where
+// there is one: such a tile spends its time fetching the long sweep's
+// unrolled code (STORE pass 1, 8-row tiles of 256 columns, long and short:
+// 1080x1920 k5 20.2 and 10.8 us, 701x1283 k3 18.0 and 7.7, 4096x4096 k7 117
+// and 53).  Taller tiles amortise that code, and its longer loop body is
+// then the faster one.
+constexpr int kShortTile = 16;
+
 // Is (ks, c, ty) one of the compiled sweep shapes?
 bool sweep_supported(int ks, int c, int ty);
 
@@ -168,11 +176,13 @@ struct BatchHeader {
     int32_t pass_mode;  // HX_PASS_STORE / RECOMPUTE / SPECULATE
     float theta;
     int32_t n_items0;   // SPECULATE: sampled-band items of pass 0
-    int32_t pad[2];
+    int32_t ty;         // rows per sweep tile of every image
+    int32_t bound_step; // elements of `bound` from one image's to the next's
     // SPECULATE: the listed pixels of pass-1 item k (a tile of image i)
     // occupy the image's entries for that tile (ImgArgs::list_base and
     // list_cap) of cand_code / cand_row, and cand_n[k] counts them; a tile
-    // that set more pixels than its capacity is redone whole by pass 2.
+    // that set more pixels than its capacity goes to the queue `redo` (its
+    // length: redo_n, emptied by pass 0) and is redone whole by pass 2.
     float* cand_code;
     int32_t* cand_row;
     uint32_t* cand_n;
@@ -183,6 +193,8 @@ struct BatchHeader {
     // needs no clearing (its epoch is lower); pass 2 advances the epoch.
     unsigned long long* bound;
     uint32_t* epoch;
+    uint32_t* redo_n;
+    int32_t* redo;
 };
 
 size_t batch_table_bytes(int n_images, int64_t n_items1, int64_t n_items2,
@@ -199,24 +211,26 @@ __host__ __device__ inline int sample_stride(int64_t H) {
     return (int)(f < q ? f : q);
 }
 int64_t batch_sample_items(int ks, int64_t H, int64_t W);
-// SPECULATE: listed-pixel capacity of each pass-1 tile of an image with
-// `tiles` tiles: one entry per 16 of the image's pixels, spread evenly.
-inline uint32_t spec_tile_cap(int64_t H, int64_t W, int64_t tiles) {
-    return (uint32_t)((H * W) / (16 * tiles));
+// SPECULATE: listed-pixel capacity of each of an image's `tiles` pass-1
+// tiles, of ty rows: the image's share of the `entries` a batch of
+// total_px pixels may list, spread evenly over the tiles (never more than
+// the lanes a tile can list).
+inline uint32_t spec_tile_cap(int64_t entries, int64_t total_px, int64_t px, int64_t tiles,
+                              int ty) {
+    const int64_t share = (int64_t)((__int128)entries * px / total_px) / tiles;
+    const int64_t all = (int64_t)64 * ty;
+    return (uint32_t)(share < all ? share : all);
 }
 int batch_sweep_c();   // columns per lane of the batch sweep
-int batch_wg_waves();  // waves per workgroup of the batch pass kernels
 int batch_sweep_ty();  // rows per batch sweep tile
 // Rows per pass-2 item of the STORE threshold for width W.
 int batch_p2_rows(int64_t W);
-// Zero the first n (read from the table) max slots; grid sized for
-// max_images.  SPECULATE batches do not need it (pass 0 clears them).
-hipError_t launch_batch_reset(const void* d_table, uint32_t* slots,
-                              int max_images, hipStream_t s);
-// One pass (phase 0, 1 or 2) over the table's item list on `grid`
-// workgroups of four waves.  Phase 0 exists for SPECULATE only.
-hipError_t launch_batch_phase(int ks, int pass_mode, int phase,
-                              const void* d_table, const Taps& t, int grid,
-                              hipStream_t s);
+// Zero the table's images' max slots; grid sized for max_images.
+// SPECULATE batches do not need it (pass 0 clears them).
+hipError_t launch_batch_reset(const void* d_table, int max_images, hipStream_t s);
+// One pass (phase 0, 1 or 2) over the table's `items` items of that phase,
+// ty the batch's tile height.  Phase 0 exists for SPECULATE only.
+hipError_t launch_batch_phase(int ks, int pass_mode, int phase, int ty, int64_t items,
+                              const void* d_table, const Taps& t, hipStream_t s);
 
 }  // namespace hx

@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cstring>
 #include <map>
 #include <mutex>
 #include <string>
@@ -72,6 +73,7 @@ struct HostBuf {
 struct BatchCaps {
     int64_t items1 = 0, items2 = 0, items0 = 0;  // work items per pass
     int64_t list_entries = 0;                    // SPECULATE listing
+    int32_t slot_step = 1;   // words between images' max slots (8 B between bounds)
     size_t table_bytes = 0;
     int64_t code_elems = 0;                      // STORE code plane (0: none)
 };
@@ -82,10 +84,12 @@ struct BatchContext {
     bool ready = false;
     DevBuf table;               // device descriptor table
     HostBuf h_table;            // pinned staging copy of the table
-    DevBuf slots;               // max_images max slots
-    DevBuf spec_state;          // SPECULATE: max_images bounds, the epoch
+    DevBuf state;               // the small arrays, SPECULATE's bounds and epoch first
+    uint32_t* slots = nullptr;  // in state: max_images max slots
+    uint32_t* cand_n = nullptr; // SPECULATE: entries each tile listed
+    int32_t* redo = nullptr;    // SPECULATE: tiles whose lists overflowed
     DevBuf code;                // pass-1 store buffer (STORE batches)
-    DevBuf cand_code, cand_row, cand_n;  // SPECULATE: listed pixels
+    DevBuf cand_code, cand_row; // SPECULATE: listed pixels
     hipEvent_t ev_done = nullptr;
     hipEvent_t ev_t[5] = {};    // timing mode
     bool in_flight = false;
@@ -95,6 +99,11 @@ struct BatchContext {
     hipGraphExec_t exec[4] = {};
     hipGraph_t graph[4] = {};
     int64_t graph_items[4][3] = {};  // item counts baked into each graph
+    int graph_ty[4] = {};            // and tile heights
+    bool graph_matches(int pass) const {
+        return std::memcmp(graph_items[pass], n_items, sizeof n_items) == 0 &&
+               graph_ty[pass] == last_ty;
+    }
     int64_t n_items[3] = {0, 0, 0};  // the table's items of pass 0, 1, 2
     // The call whose table the device copy holds: a repeat of the same
     // batch (same descriptors, outputs and pass mode) reuses it as is.

@@ -1,0 +1,107 @@
+"""The short sweep (tiles of up to 16 rows) where it can go wrong: widths
+and heights at the edges of its 64-, 128- and 256-column tiles, images
+smaller than one lane, pitched and unaligned rows, and SPECULATE batches
+whose lists overflow (every tile queued and redone).  Results are decisions
+and one maximum, so every comparison with another schedule is exact; the
+oracle comparison uses the parity rules of the other tests."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import parity
+from paper_2503_10855_amd import synth
+
+pytestmark = pytest.mark.gpu
+THETA = 0.1
+SIGMA = {3: 0.8, 5: 1.0, 7: 1.5}
+
+
+@pytest.fixture(scope="module")
+def hx():
+    from paper_2503_10855_amd import hx as mod
+    return mod
+
+
+def pitched(img, pad, dtype=torch.float32):
+    buf = torch.zeros((img.shape[0], img.shape[1] + pad), dtype=dtype, device="cuda")
+    v = buf[:, :img.shape[1]]
+    if dtype == torch.float32:
+        v.copy_(torch.from_numpy(img))
+    return v, buf
+
+
+# Output widths of the tiles: 64 - 2 HY, 128 - 2 HY.. and 248 / 240 columns;
+# one below, at and one past one and two of them, and past a strip's halo.
+WIDTHS = {3: [1, 2, 3, 57, 58, 59, 116, 120, 121, 248, 249, 253],
+          5: [1, 2, 5, 55, 56, 57, 112, 119, 120, 121, 248, 250],
+          7: [1, 4, 53, 54, 55, 107, 115, 116, 117, 240, 241, 247]}
+HEIGHTS = [1, 2, 7, 8, 9, 16, 17, 31]
+
+
+@pytest.mark.parametrize("ks", [3, 5, 7])
+@pytest.mark.parametrize("tile", [(64, 8), (64, 16), (128, 8), (128, 16), (256, 8), (256, 16)])
+def test_store_tile_edges(hx, ks, tile):
+    with hx.Pipeline(ksize=ks, sigma=SIGMA[ks], theta=THETA, max_pixels=1 << 16) as p:
+        for i, w in enumerate(WIDTHS[ks]):
+            h, pad = HEIGHTS[i % len(HEIGHTS)], (0, 3, 1)[i % 3]
+            img = synth.image(h, w, 301, i)
+            src, _ = pitched(img, pad)
+            mask, mbuf = pitched(img, pad, torch.uint8)
+            dm = torch.zeros(2, device="cuda")
+            print(f"k{ks} tile {tile} {h}x{w} pad {pad}", flush=True)
+            p.set_schedule(*tile, 4, hx.PASS_STORE)
+            p.edge_detect(src, mask, dmax=dm[:1])
+            p.set_schedule(256, 64, 4, hx.PASS_RECOMPUTE)
+            ref = p.edge_detect(src, dmax=dm[1:])
+            assert torch.equal(mask, ref) and dm[0] == dm[1]
+            assert int(mbuf[:, w:].sum()) == 0
+            o = oracle.edge_detect(img, ks, SIGMA[ks], THETA, stages=True)
+            r = parity.compare_mask(mask.cpu().numpy(), o, THETA)
+            assert r["mismatch"] == 0 and parity.exempt_bounded(r), r
+
+
+@pytest.mark.parametrize("ks", [3, 5, 7])
+@pytest.mark.parametrize("ty", [16, 24, 48])
+def test_speculate_with_every_list_overflowing(hx, ks, ty):
+    """The only bright spot lies between the sampled bands, so the bound is
+    the noise's: every tile sets far more pixels than its list holds and is
+    queued; the true threshold then clears almost all of them.  The second
+    image is ordinary and shares the batch."""
+    a = (synth.image(1000, 1030, 302, ks, n_rect=0) * 1.0).astype(np.float32)
+    a[40:60, 500:530] = 9.0
+    b = synth.image(333, 251, 302, 9)
+    srcs = [pitched(a, 2)[0], pitched(b, 0)[0]]
+    npx = a.size + b.size
+    with hx.Pipeline(ksize=ks, sigma=SIGMA[ks], theta=THETA, max_pixels=npx, max_images=2) as p:
+        out = {}
+        for name, sched in (("spec", (256, ty, 4, hx.PASS_SPECULATE)),
+                            ("rec", (256, 64, 4, hx.PASS_RECOMPUTE))):
+            p.set_schedule(*sched)
+            dm = torch.zeros(2, device="cuda")
+            print(f"k{ks} ty {ty} {name}", flush=True)
+            for _ in range(2):   # the second call on the same context
+                masks = p.edge_detect_batched(srcs, dmax=dm)
+                p.sync()
+            out[name] = (masks, dm.clone())
+    for m, r, img in zip(out["spec"][0], out["rec"][0], (a, b)):
+        assert torch.equal(m, r)
+        o = oracle.edge_detect(img, ks, SIGMA[ks], THETA, stages=True)
+        c = parity.compare_mask(m.cpu().numpy(), o, THETA)
+        assert c["mismatch"] == 0 and parity.exempt_bounded(c), c
+    assert torch.equal(out["spec"][1], out["rec"][1])
+
+
+@pytest.mark.parametrize("n,side", [(1, 64), (3, 200), (40, 130), (5, 1100)])
+def test_batch_default_heights_match_per_image(hx, n, side):
+    """Batches whose default tile heights are 16, 24 and 32 rows: the masks
+    and maxima of the per-image form, bit for bit."""
+    imgs = [synth.image(side + 3 * i, side + 7 * i, 303, i) for i in range(n)]
+    srcs = [torch.from_numpy(x).cuda() for x in imgs]
+    with hx.Pipeline(theta=THETA, max_pixels=sum(x.size for x in imgs), max_images=n) as p:
+        dm = torch.zeros(n, device="cuda")
+        got = p.edge_detect_batched(srcs, dmax=dm)
+        one = torch.zeros(n, device="cuda")
+        ref = [p.edge_detect(s, dmax=one[i:i + 1]) for i, s in enumerate(srcs)]
+        p.sync()
+    assert all(torch.equal(m, r) for m, r in zip(got, ref)) and torch.equal(dm, one)
