@@ -185,8 +185,8 @@ void hx_pipeline_destroy(hx_pipeline* p);
 hx_status hx_pipeline_sync(hx_pipeline* p);
 
 /* Timing mode, for benchmarks.  While enabled, batched calls launch their
- * kernels (reset, [pass 0,] pass 1, pass 2) directly instead of through the
- * graph and bracket each with HIP events on the call's stream.
+ * kernels (reset, [pass 0,] pass 1, pass 2) bracketed with HIP events on
+ * the call's stream.
  * hx_pipeline_last_timing waits for the last batched call and returns the
  * durations in milliseconds of its kernels in ms[0..3]: reset, pass 1,
  * pass 2, and pass 0 (SPECULATE only, 0 otherwise; it runs between the
@@ -247,14 +247,15 @@ hx_status hx_edge_detect(hx_pipeline* p, const hx_image* img, float* d_max,
  * of (image, tile) pass-1 items, then one over the pass-2 items.  No
  * workgroup waits on another; the kernel boundary makes each image's max
  * final before its mask is written.  A batch that a batch context already
- * ran (same descriptors, outputs and pass structure) replays its captured
- * HIP graph.  imgs is a HOST array of n descriptors (device pointers
- * inside); it is copied before the call returns.  d_max (device,
+ * ran (same descriptors, outputs and pass structure) reuses its descriptor
+ * table on the device.  imgs is a HOST array of n descriptors (device
+ * pointers inside); it is copied before the call returns.  d_max (device,
  * nullable) receives n floats.  Requires 1 <= n <= max_images and
  * sum H*W <= max_pixels.  Each image's result is bit-identical to
  * hx_edge_detect on it alone.  Batched calls use one of batch_contexts
  * scratch sets each, so calls on different streams overlap; a call whose
- * context is still in use waits (on the host) for it.  A batch with more
+ * context is still in use waits for it (a repeated batch on the device, a
+ * new one on the host, where its descriptor table is rebuilt).  A batch with more
  * tiles than a context's descriptor table holds (only possible with many
  * images a few pixels wide or tall) runs as several launches in turn. */
 hx_status hx_edge_detect_batched(hx_pipeline* p, const hx_image* imgs,
@@ -440,8 +441,8 @@ hx_status hx_serve_destroy(hx_server* s);
  * text, pipeline and server creation (sizes, bytes), each batched call's
  * schedule (images, pixels, pass structure, tile height and its source,
  * context, groups) and the batch autotuner's trials; HX_LOG=2 adds each
- * per-image call's schedule, each batch's launch form (graph replay,
- * capture, direct) and each serving batch.  HX_TRACE=1 brackets API calls
+ * per-image call's schedule, each batch's items and whether its table
+ * was reused, and each serving batch.  HX_TRACE=1 brackets API calls
  * and batch phases in roctx ranges (rocprofv3 --marker-trace). */
 const char* hx_status_str(hx_status s);
 const char* hx_last_error(void);

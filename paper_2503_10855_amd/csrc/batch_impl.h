@@ -17,10 +17,8 @@
 // Pass 2 starts after pass 1 has finished (a kernel boundary), so every max
 // is final when it is read; no workgroup ever waits for another one.  Each
 // wave takes the item of its index (the host sizes each grid to its pass's
-// item count; were a grid smaller, its waves would stride over the rest).
-// The item lists live in the descriptor table, so the kernels read every
-// size from it and a captured graph is replayed as long as the batch's
-// item counts are unchanged.
+// item count).  The item lists live in the descriptor table, from which the
+// kernels read every size; a repeated batch reuses it.
 #pragma once
 
 #include <hip/hip_runtime.h>

@@ -107,8 +107,8 @@ static BatchCaps batch_caps(const hx_params& prm, bool store_plane) {
     c.items2 = std::max<int64_t>(c.items1, P / 1024 + 2 * n + 1024);
     c.items0 = 5 * c.items1;
     // One listing entry (four pixels of a row) per 16 pixels, and for small
-    // pipelines all of them, up to 2^17: in small images edges are dense.
-    c.list_entries = std::max(P / 16 + 16, std::min<int64_t>(P / 4 + 16 * n, 1 << 17));
+    // pipelines all of them, up to 2^16: in small images edges are dense.
+    c.list_entries = std::max(P / 16 + 16, std::min<int64_t>(P / 4 + 16 * n, 1 << 16));
     // Max slots and bounds of neighbouring images 64 bytes apart, so that
     // atomics of different images do not share a cache line (with very many
     // images they spread by themselves).
@@ -399,10 +399,6 @@ static hx_status ctx_init(hx_pipeline* p, BatchContext& c) {
 }
 
 static void ctx_release(BatchContext& c) {
-    for (int i = 0; i < 4; ++i) {
-        if (c.exec[i]) (void)hipGraphExecDestroy(c.exec[i]);
-        if (c.graph[i]) (void)hipGraphDestroy(c.graph[i]);
-    }
     c.table.release();
     c.h_table.release();
     c.state.release();
@@ -444,38 +440,6 @@ static hipError_t enqueue_phases(hx_pipeline* p, BatchContext& c, int pass, hipS
         e = launch_batch_phase(ks, pass, 2, c.last_ty, c.n_items[2], c.table.ptr, p->taps, s);
     if (e == hipSuccess && timed) e = hipEventRecord(c.ev_t[3], s);
     return e;
-}
-
-// Capture the launches once per (context, pass mode, item counts).
-static hx_status ctx_graph(hx_pipeline* p, BatchContext& c, int pass) {
-    if (c.exec[pass] && c.graph_matches(pass)) return HX_OK;
-    if (c.exec[pass]) {
-        (void)hipGraphExecDestroy(c.exec[pass]);
-        (void)hipGraphDestroy(c.graph[pass]);
-        c.exec[pass] = nullptr;
-        c.graph[pass] = nullptr;
-    }
-    hipStream_t cs = p->capture_stream;
-    HX_TRY(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
-    hipError_t e1 = enqueue_phases(p, c, pass, cs);
-    hipGraph_t g = nullptr;
-    hipError_t e2 = hipStreamEndCapture(cs, &g);
-    if (e1 != hipSuccess) {
-        if (g) (void)hipGraphDestroy(g);
-        return hip_fail(e1, "capturing the batched launch");
-    }
-    if (e2 != hipSuccess) return hip_fail(e2, "hipStreamEndCapture");
-    hipGraphExec_t ex = nullptr;
-    hipError_t e3 = hipGraphInstantiate(&ex, g, nullptr, nullptr, 0);
-    if (e3 != hipSuccess) {
-        (void)hipGraphDestroy(g);
-        return hip_fail(e3, "hipGraphInstantiate");
-    }
-    c.graph[pass] = g;
-    c.exec[pass] = ex;
-    std::memcpy(c.graph_items[pass], c.n_items, sizeof c.n_items);
-    c.graph_ty[pass] = c.last_ty;
-    return HX_OK;
 }
 
 // Work items of one image in each pass, and its STORE code elements.
@@ -591,41 +555,32 @@ static hx_status run_oversized(hx_pipeline* p, BatchContext& c, const hx_image& 
     return HX_OK;
 }
 
-// Launch a batch that fits one context on context c.
+// Is `stream` being captured into a graph (or may it not be asked)?
+static bool is_capturing(hipStream_t stream) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone;
+}
+
+// Launch a batch that fits one context on context c, whose table holds it
+// already if `same`.
 static hx_status launch_on(hx_pipeline* p, BatchContext& c, const hx_image* imgs, int32_t n,
-                           float* d_max, int pass, const SweepGeom& geo, bool allow_graph,
+                           float* d_max, int pass, const SweepGeom& geo, bool same,
                            hipStream_t stream) {
-    const bool same = c.ready && c.last_pass == pass && c.last_ty == geo.ty &&
-                      c.last_dmax == d_max && c.last_imgs.size() == (size_t)n &&
-                      std::memcmp(c.last_imgs.data(), imgs, sizeof(hx_image) * n) == 0;
     if (!same) {
         TraceRange tr("hx.batch.table");
         hx_status st = build_table(p, c, imgs, n, d_max, pass, geo, stream);
         if (st != HX_OK) return st;
     }
     TraceRange tr("hx.batch.enqueue");
-    // A batch seen again on this context replays a captured graph; a new
-    // composition launches its kernels directly (capturing every new batch
-    // would cost more than it saves, e.g. when serving).
-    static const bool no_graph = std::getenv("HX_NO_GRAPH") != nullptr;
-    const char* how;
-    if (p->timing) {
-        HX_TRY(enqueue_phases(p, c, pass, stream, true));
-        p->last_timed_ctx = (int)(&c - p->ctx);
-        how = "timed launches";
-    } else if (no_graph || !same || !allow_graph) {
-        HX_TRY(enqueue_phases(p, c, pass, stream));
-        how = "direct launches";
-    } else {
-        const bool captured = c.exec[pass] != nullptr && c.graph_matches(pass);
-        hx_status st = ctx_graph(p, c, pass);
-        if (st != HX_OK) return st;
-        HX_TRY(hipGraphLaunch(c.exec[pass], stream));
-        how = captured ? "graph replay" : "graph capture + launch";
-    }
-    logf(2, "batch context %d: %d images, items %lld / %lld / %lld (pass 1 / 2 / 0), %s",
+    // The three kernels are launched one by one, also for a repeated batch:
+    // replaying them as a captured graph cost 6 to 8 us more per call (16
+    // thumbnails 28.5 against 21.2 us, 2 x 1080p 36.1 against 28.9).
+    HX_TRY(enqueue_phases(p, c, pass, stream, p->timing));
+    if (p->timing) p->last_timed_ctx = (int)(&c - p->ctx);
+    logf(2, "batch context %d: %d images, items %lld / %lld / %lld (pass 1 / 2 / 0), %s%s",
          (int)(&c - p->ctx), n, (long long)c.n_items[1], (long long)c.n_items[2],
-         (long long)c.n_items[0], how);
+         (long long)c.n_items[0], same ? "table reused" : "table built",
+         p->timing ? ", timed" : "");
     return HX_OK;
 }
 
@@ -677,26 +632,19 @@ hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
         }
     }
     if (!pass) pass = kBatchPass;
-    if (!ty) ty = pass == HX_PASS_SPECULATE ? spec_default_ty(ks, imgs, n) : batch_sweep_ty();
-    if (ty < kBatchTyMin || ty > kBatchTyMax || ty % 8 != 0)
-        return fail(HX_E_INVALID, "batch tile height %d not a multiple of 8 in %d..%d", ty,
-                    kBatchTyMin, kBatchTyMax);
-    const SweepGeom geo{ks, batch_sweep_c(), ty};
     if (pass < HX_PASS_STORE || pass > HX_PASS_SPECULATE)
         return fail(HX_E_INVALID, "pass_mode %d unknown", pass);
-    if (!has_form(p, HX_FORM_BATCH))
-        return fail(HX_E_UNSUPPORTED, "the pipeline was created without HX_FORM_BATCH scratch");
-    if (pass == HX_PASS_STORE && !has_form(p, HX_FORM_BATCH_STORE))
-        return fail(HX_E_UNSUPPORTED,
-                    "batched STORE needs a pipeline created with HX_FORM_BATCH_STORE");
-    std::lock_guard<std::mutex> lk(p->batch_mu);
-    // Which context: one that already holds this batch (its table and
-    // graph are reused as they are) and is idle; else the oldest of those
-    // holding it; else the oldest context.  Consecutive calls that
-    // alternate between a few output sets thus settle on contexts of their
-    // own, whatever the order of the first calls was.
+    std::unique_lock<std::mutex> lk(p->batch_mu);
+    // Which context: one that already holds this batch (its table is reused
+    // as it is) and is idle; else the oldest of those holding it; else the
+    // oldest context.  Consecutive calls that alternate between a few output
+    // sets thus settle on contexts of their own, whatever the order of the
+    // first calls was.  (want_ty 0: the default height, which depends on the
+    // images alone.)
+    const int want_ty = ty;
     auto holds = [&](const BatchContext& c) {
-        return c.ready && c.last_pass == pass && c.last_ty == ty && c.last_dmax == d_max &&
+        return c.ready && c.last_pass == pass && c.last_dmax == d_max &&
+               (want_ty ? c.last_ty == want_ty : c.default_ty) &&
                c.last_imgs.size() == (size_t)n &&
                std::memcmp(c.last_imgs.data(), imgs, sizeof(hx_image) * n) == 0;
     };
@@ -713,15 +661,34 @@ hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
         if (oldest < 0 || c.last_use < p->ctx[oldest].last_use) oldest = i;
     }
     if (pick < 0) pick = oldest_match >= 0 ? oldest_match : oldest;
-    if (ctx >= 0) pick = ctx % p->n_ctx;
+    if (ctx >= 0) pick = p->n_ctx > 0 ? ctx % p->n_ctx : -1;
+    const bool same = pick >= 0 && holds(p->ctx[pick]);
+    if (same) ty = p->ctx[pick].last_ty;
+    if (!ty) ty = pass == HX_PASS_SPECULATE ? spec_default_ty(ks, imgs, n) : batch_sweep_ty();
+    if (ty < kBatchTyMin || ty > kBatchTyMax || ty % 8 != 0)
+        return fail(HX_E_INVALID, "batch tile height %d not a multiple of 8 in %d..%d", ty,
+                    kBatchTyMin, kBatchTyMax);
+    const SweepGeom geo{ks, batch_sweep_c(), ty};
+    if (!has_form(p, HX_FORM_BATCH))
+        return fail(HX_E_UNSUPPORTED, "the pipeline was created without HX_FORM_BATCH scratch");
+    if (pass == HX_PASS_STORE && !has_form(p, HX_FORM_BATCH_STORE))
+        return fail(HX_E_UNSUPPORTED,
+                    "batched STORE needs a pipeline created with HX_FORM_BATCH_STORE");
     BatchContext& c = p->ctx[pick];
     c.last_use = ++p->use_clock;
-    hx_status st = ctx_wait(c);
-    if (st != HX_OK) return st;
+    hx_status st = HX_OK;
+    if (same && c.in_flight && !p->timing && !is_capturing(stream)) {
+        // Nothing on the host changes: the stream waits for the context's
+        // previous call (no wait at all if that is this stream's own).
+        HX_TRY(hipStreamWaitEvent(stream, c.ev_done, 0));
+    } else {
+        st = ctx_wait(c);
+        if (st != HX_OK) return st;
+    }
 
     // The common case: the whole batch fits the context.
     ImgWork tot;
-    for (int i = 0; i < n; ++i) {
+    for (int i = 0; i < n && !same; ++i) {
         const ImgWork w = img_work(imgs[i], pass, geo);
         tot.tiles += w.tiles;
         tot.p2 += w.p2;
@@ -737,8 +704,9 @@ hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
              fits(p->caps, tot, pass) ? "" : ", split into groups");
     }
     if (fits(p->caps, tot, pass)) {
-        st = launch_on(p, c, imgs, n, d_max, pass, geo, true, stream);
+        st = launch_on(p, c, imgs, n, d_max, pass, geo, same, stream);
         if (st != HX_OK) return st;
+        c.default_ty = want_ty == 0;
     } else {
         // Consecutive groups that fit, one after another on this context
         // (each waits for the previous one's table copy before the staging
@@ -837,7 +805,6 @@ static hx_status alloc_scratch(hx_pipeline* p) {
     const int f = p->prm.forms;
     p->plane_elems = plane_capacity(p->prm.max_pixels);
     const size_t pe = (size_t)p->plane_elems;
-    HX_TRY(hipStreamCreateWithFlags(&p->capture_stream, hipStreamNonBlocking));
     HX_TRY(hipEventCreateWithFlags(&p->img_ev, hipEventDisableTiming));
     HX_TRY(p->slot1.alloc(2 * kSlotWords * sizeof(uint32_t), m));
     if (f & (HX_FORM_IMAGE | HX_FORM_STAGES | HX_FORM_SRAD))
@@ -960,7 +927,6 @@ void hx_pipeline_destroy(hx_pipeline* p) {
     p->bufPart.release();
     p->srad_part.release();
     if (p->img_ev) (void)hipEventDestroy(p->img_ev);
-    if (p->capture_stream) (void)hipStreamDestroy(p->capture_stream);
     delete p;
 }
 

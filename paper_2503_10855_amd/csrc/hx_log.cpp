@@ -3,9 +3,9 @@
 //   HX_LOG=1   one line per API call outcome that matters to an operator:
 //              pipeline creation (forms, contexts, bytes), each batched
 //              call (images, pixels, pass structure, tile height and where
-//              it came from, groups, graph capture or replay), the batch
-//              autotuner's trials and choice, server creation, and every
-//              failing call with its hx_last_error() text;
+//              it came from, groups), the batch autotuner's trials and
+//              choice, server creation, and every failing call with its
+//              hx_last_error() text;
 //   HX_LOG=2   also each per-image call's schedule and each serving batch.
 //   HX_TRACE=1 brackets the API calls and the phases of a batched call in
 //              roctx ranges, which rocprofv3 --marker-trace records beside

@@ -94,16 +94,6 @@ struct BatchContext {
     hipEvent_t ev_t[5] = {};    // timing mode
     bool in_flight = false;
     uint64_t last_use = 0;      // the pipeline's call counter at the last use
-    // Captured [reset, (pass 0,) pass 1, pass 2] per pass mode, with the
-    // table address and grid sizes baked into the kernel nodes.
-    hipGraphExec_t exec[4] = {};
-    hipGraph_t graph[4] = {};
-    int64_t graph_items[4][3] = {};  // item counts baked into each graph
-    int graph_ty[4] = {};            // and tile heights
-    bool graph_matches(int pass) const {
-        return std::memcmp(graph_items[pass], n_items, sizeof n_items) == 0 &&
-               graph_ty[pass] == last_ty;
-    }
     int64_t n_items[3] = {0, 0, 0};  // the table's items of pass 0, 1, 2
     // The call whose table the device copy holds: a repeat of the same
     // batch (same descriptors, outputs and pass mode) reuses it as is.
@@ -111,6 +101,7 @@ struct BatchContext {
     float* last_dmax = nullptr;
     int last_pass = -1;
     int last_ty = 0;
+    bool default_ty = false;   // last_ty was the default for these images
 };
 
 // A batch's class for the batch autotuner: floor(log2) of its total
@@ -179,7 +170,6 @@ struct hx_pipeline {
     uint64_t use_clock = 0;
     std::mutex batch_mu;  // guards context choice (the server calls from
                           // its own thread)
-    hipStream_t capture_stream = nullptr;
     bool timing = false;
     int last_timed_ctx = -1;
 };

@@ -10,7 +10,7 @@
 //   admit    a scheduler thread moves queued requests, oldest first, into
 //            the device arena while their buffers fit the HBM budget;
 //   launch   every admitted request not yet launched joins the next batch
-//            (one batched graph launch of the pipeline) on the least busy of
+//            (one batched call of the pipeline) on the least busy of
 //            S compute streams, bracketed by its host-to-device and
 //            device-to-host copies, so batches overlap on the device;
 //   retire   a host callback at the end of the batch stamps completion;

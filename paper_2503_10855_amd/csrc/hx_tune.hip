@@ -291,8 +291,7 @@ hx_status hx_autotune_batch(hx_pipeline* p, const hx_image* imgs, int32_t n,
         }
     }
     for (const BatchChoice& c : cands) {
-        // Untimed: three calls per stream (each context builds its table,
-        // captures its graph and replays it).
+        // Untimed: three calls per stream (each context builds its table).
         for (int r = 0; r < 3 * S && st == HX_OK; ++r)
             st = run_batched(p, imgs, n, nullptr, c.pass, c.ty, st_[r % S], r % S);
         for (int i = 0; i < S && st == HX_OK; ++i)
