@@ -73,6 +73,11 @@ struct TableView {
     const BatchItem* items1;
     const BatchItem* items2;
     const BatchItem* items0;
+    // Item k of a list; a batch of one image has no lists.
+    __device__ __forceinline__ BatchItem item(const BatchItem* items, int64_t k) const {
+        if (hdr.n_images == 1) return BatchItem{0, (int32_t)k};
+        return items[k];
+    }
 };
 
 __device__ __forceinline__ TableView view(const uint8_t* __restrict__ table) {
@@ -97,6 +102,12 @@ __device__ __forceinline__ int global_wave() {
 // columns per lane); on 16 images of 64..256, 5.2 and 4.5 us.
 constexpr int kP0C = 2;
 
+// Word w of the bounds of image a.
+__device__ __forceinline__ unsigned long long* bound_word(const BatchHeader& h, const ImgArgs& a,
+                                                          int w) {
+    return h.bound + ((int64_t)a.way0 + w) * h.slot_step;
+}
+
 // SPECULATE pass 0: G^2 on the sampled bands, folded into the images'
 // bounds under the current epoch.  Any pixel's G^2 is at most the image's
 // max, so each then holds a lower bound of it.  The first item of each
@@ -112,32 +123,39 @@ void k_batch_p0(const uint8_t* __restrict__ table, Taps tp) {
     const uint64_t ep = (uint64_t)*as_global(tv.hdr.epoch) << 32;
     const int k = xcd_remap(blockIdx.x, gridDim.x);   // one item per workgroup
     if (k >= tv.hdr.n_items0) return;
-    const BatchItem it = tv.items0[k];
+    const BatchItem it = tv.item(tv.items0, k);
     const ImgArgs a = tv.imgs[it.image];
     const int nstrips = (a.W + S::OW - 1) / S::OW;
     const int x0 = (it.local % nstrips) * S::OW;
     const int y0 = (it.local / nstrips) * sample_stride(a.H);
     lds_float* lds = (lds_float*)rows;
     tile_load<kP0C>(a, x0 - S::HL, y0 - S::HY, min(kSampleRows, a.H - y0) + 2 * S::HY, lds);
-    if (it.local == 0 && lane_id() == 0) *as_global(a.slot) = 0u;
+    if (it.local == 0 && lane_id() < a.ways)
+        as_global(a.slot)[(int64_t)lane_id() * a.slot_step] = 0u;
     if (k == 0 && lane_id() == 0) *as_global(tv.hdr.redo_n) = 0u;
     tile_loads_done();
     float gmax = 0.0f;
     tile_sweep<KS, kP0C, SM_MAXONLY>(a, tp, x0, y0, kSampleRows, 0.0f, gmax, lds);
     gmax = wave_max(gmax);
     if (lane_id() == 0)
-        atomicMax(tv.hdr.bound + (int64_t)it.image * tv.hdr.bound_step,
+        atomicMax(bound_word(tv.hdr, a, k & (a.ways - 1)),
                   (unsigned long long)(ep | __float_as_uint(gmax)));
 }
 
-// SPECULATE pass 1's threshold on G^2 of image i: pass 0 finished before
+// SPECULATE pass 1's threshold on G^2 of an image: pass 0 finished before
 // this kernel began, and nothing writes the bounds meanwhile.  (Reading the
 // image's slot, which the other tiles keep raising, measured much slower:
 // each read waits behind this wave's own atomic on the same address.)
-__device__ __forceinline__ float bound_thr2(const BatchHeader& h, int i) {
-    const uint64_t bv = as_global(h.bound)[(int64_t)i * h.bound_step];
-    const uint32_t lb2 = (uint32_t)(bv >> 32) == *as_global(h.epoch) ? (uint32_t)bv : 0u;
-    return thr2_from(lb2, h.theta) * kSpecSafety;
+__device__ __forceinline__ float bound_thr2(const BatchHeader& h, const ImgArgs& a) {
+    uint32_t lb2 = 0u;
+    if (lane_id() < a.ways) {
+        const uint64_t bv = *as_global(bound_word(h, a, lane_id()));
+        if ((uint32_t)(bv >> 32) == *as_global(h.epoch)) lb2 = (uint32_t)bv;
+    }
+    uint32_t top = __builtin_amdgcn_readfirstlane(lb2);
+    for (int w = 1; w < a.ways; ++w)
+        top = max(top, (uint32_t)__builtin_amdgcn_readlane((int)lb2, w));
+    return thr2_from(top, h.theta) * kSpecSafety;
 }
 __device__ __forceinline__ SpecTile list_of(const BatchHeader& h, const ImgArgs& a, int local) {
     const int64_t base = (int64_t)a.list_base + (int64_t)local * a.list_cap;
@@ -162,14 +180,14 @@ __device__ __forceinline__ void batch_p1_body(const uint8_t* __restrict__ table,
     const TableView tv = view(table);
     const int nw = gridDim.x * kWG;
     for (int k = global_wave(); k < tv.hdr.n_items1; k += nw) {
-        const BatchItem it = tv.items1[k];
+        const BatchItem it = tv.item(tv.items1, k);
         const ImgArgs a = tv.imgs[it.image];
         const int nstrips = (a.W + S::OW - 1) / S::OW;
         float gmax = 0.0f;
         float thr2 = 0.0f;
         SpecTile sp{nullptr, nullptr, 0u, 0u};
         if constexpr (PASS == HX_PASS_SPECULATE) {
-            thr2 = bound_thr2(tv.hdr, it.image);
+            thr2 = bound_thr2(tv.hdr, a);
             sp = list_of(tv.hdr, a, it.local);
         }
         // Odd bands sweep upwards (their halo rows are then read while the
@@ -179,7 +197,7 @@ __device__ __forceinline__ void batch_p1_body(const uint8_t* __restrict__ table,
                                 gmax, &sp, (band & 1) != 0);
         if constexpr (PASS == HX_PASS_SPECULATE) finish_list(tv.hdr, a, k, sp.n);
         gmax = wave_max(gmax);
-        if (lane_id() == 0) atomic_max_g2(a.slot, gmax);
+        if (lane_id() == 0) atomic_max_g2(slot_word(a, k), gmax);
     }
 }
 
@@ -210,20 +228,20 @@ void k_batch_p1t(const uint8_t* __restrict__ table, Taps tp) {
     const TableView tv = view(table);
     const int k = xcd_remap(blockIdx.x, gridDim.x);
     if (k >= tv.hdr.n_items1) return;
-    const BatchItem it = tv.items1[k];
+    const BatchItem it = tv.item(tv.items1, k);
     const ImgArgs a = tv.imgs[it.image];
     const int nstrips = (a.W + S::OW - 1) / S::OW;
     const int x0 = (it.local % nstrips) * S::OW, y0 = (it.local / nstrips) * a.ty;
     lds_float* lds = (lds_float*)rows;
     tile_load<kBC>(a, x0 - S::HL, y0 - S::HY, min(a.ty, a.H - y0) + 2 * S::HY, lds);
-    const float thr2 = bound_thr2(tv.hdr, it.image);
+    const float thr2 = bound_thr2(tv.hdr, a);
     SpecTile sp = list_of(tv.hdr, a, it.local);
     tile_loads_done();
     float gmax = 0.0f;
     tile_sweep<KS, kBC, SM_SPEC>(a, tp, x0, y0, a.ty, thr2, gmax, lds, &sp);
     finish_list(tv.hdr, a, k, sp.n);
     gmax = wave_max(gmax);
-    if (lane_id() == 0) atomic_max_g2(a.slot, gmax);
+    if (lane_id() == 0) atomic_max_g2(slot_word(a, k), gmax);
 }
 
 // Pass 2 of STORE and RECOMPUTE.  RECOMPUTE's mask-only sweep keeps the
@@ -236,9 +254,9 @@ void k_batch_p2(const uint8_t* __restrict__ table, Taps tp) {
     const int nw = gridDim.x * kWG;
     const int lane = lane_id();
     for (int k = global_wave(); k < tv.hdr.n_items2; k += nw) {
-        const BatchItem it = tv.items2[k];
+        const BatchItem it = tv.item(tv.items2, k);
         const ImgArgs a = tv.imgs[it.image];
-        const uint32_t m2 = *as_global(a.slot);
+        const uint32_t m2 = slot_max(a);
         const float thr2 = thr2_from(m2, tv.hdr.theta);
         if (it.local == 0 && lane == 0 && a.dmax) *as_global(a.dmax) = max_from(m2);
         if constexpr (PASS == HX_PASS_STORE) {
@@ -295,24 +313,37 @@ void k_batch_p2s(const uint8_t* __restrict__ table, Taps tp) {
     const TableView tv = view(table);
     const int tid = threadIdx.x;
     const int n = tv.hdr.n_items2, G = gridDim.x;
-    if (tid < kP2Tiles) {
-        const int64_t k = blockIdx.x + (int64_t)tid * G;
+    // 16 threads per tile read its state (and the words of its image's max).
+    static_assert(kP2Tiles * 16 == 256, "16 threads per tile");
+    {
+        const int j = tid >> 4, l = tid & 15;
+        const int64_t k = blockIdx.x + (int64_t)j * G;
         uint32_t cnt = 0;
         if (k < n) {
-            const BatchItem it = tv.items2[k];
+            const BatchItem it = tv.item(tv.items2, k);
             const ImgArgs& a = tv.imgs[it.image];
             cnt = as_global(tv.hdr.cand_n)[k];
-            const uint32_t m2 = *as_global(a.slot);
+            uint32_t m2 = 0;
+            for (int w = l; w < a.ways; w += 16)
+                m2 = max(m2, as_global(a.slot)[(int64_t)w * a.slot_step]);
+#pragma unroll
+            for (int o = 8; o > 0; o >>= 1) m2 = max(m2, (uint32_t)__shfl_xor((int)m2, o, 16));
             const int nstrips = (a.W + S::OW - 1) / S::OW;
             const int x0 = (it.local % nstrips) * S::OW, y0 = (it.local / nstrips) * a.ty;
             const SpecTile sp = list_of(tv.hdr, a, it.local);
             if (cnt > sp.cap) cnt = 0;   // incomplete: queued
-            if (it.local == 0 && a.dmax) *as_global(a.dmax) = max_from(m2);
-            st[tid] = Tile{sp.code, sp.row, a.mask + (int64_t)y0 * a.mp + (x0 - S::HL), a.mp,
-                           thr2_from(m2, tv.hdr.theta), a.W - (x0 - S::HL),
-                           ((reinterpret_cast<uintptr_t>(a.mask) | (uint64_t)a.mp) & 3u) == 0};
+            if (l == 0) {
+                if (it.local == 0 && a.dmax) *as_global(a.dmax) = max_from(m2);
+                st[j] = Tile{sp.code, sp.row, a.mask + (int64_t)y0 * a.mp + (x0 - S::HL), a.mp,
+                             thr2_from(m2, tv.hdr.theta), a.W - (x0 - S::HL),
+                             ((reinterpret_cast<uintptr_t>(a.mask) | (uint64_t)a.mp) & 3u) == 0};
+            }
         }
-        uint32_t sum = cnt;
+        if (l == 0) first[j + 1] = cnt;
+    }
+    __syncthreads();
+    if (tid < kP2Tiles) {
+        uint32_t sum = first[tid + 1];
 #pragma unroll
         for (int o = 1; o < kP2Tiles; o <<= 1) {
             const uint32_t up = __shfl_up(sum, o, kP2Tiles);
@@ -387,7 +418,7 @@ void k_batch_p2s(const uint8_t* __restrict__ table, Taps tp) {
     for (int64_t c = (int64_t)blockIdx.x * 4 + wave; c < (int64_t)nq * per; c += 4 * (int64_t)G) {
         const int k = __builtin_amdgcn_readfirstlane(as_global(tv.hdr.redo)[c / per]);
         const int r = (int)(c % per);
-        const BatchItem it = tv.items2[k];
+        const BatchItem it = tv.item(tv.items2, k);
         const ImgArgs a = tv.imgs[it.image];
         const int nstrips = (a.W + S::OW - 1) / S::OW;
         const int x0 = (it.local % nstrips) * S::OW + (r % kAcross) * RS::OW;
@@ -395,7 +426,7 @@ void k_batch_p2s(const uint8_t* __restrict__ table, Taps tp) {
         if (x0 >= a.W || y0 >= a.H) continue;
         tile_load<kRedoC>(a, x0 - RS::HL, y0 - RS::HY, min(kRedoRows, a.H - y0) + 2 * RS::HY,
                           lds);
-        const float thr2 = thr2_from(*as_global(a.slot), tv.hdr.theta);
+        const float thr2 = thr2_from(slot_max(a), tv.hdr.theta);
         tile_loads_done();
         float unused = 0.0f;
         tile_sweep<KS, kRedoC, SM_MASK>(a, tp, x0, y0, kRedoRows, thr2, unused, lds);

@@ -109,9 +109,11 @@ static BatchCaps batch_caps(const hx_params& prm, bool store_plane) {
     // One listing entry (four pixels of a row) per 16 pixels, and for small
     // pipelines all of them, up to 2^16: in small images edges are dense.
     c.list_entries = std::max(P / 16 + 16, std::min<int64_t>(P / 4 + 16 * n, 1 << 16));
-    // Max slots and bounds of neighbouring images 64 bytes apart, so that
-    // atomics of different images do not share a cache line (with very many
-    // images they spread by themselves).
+    // Words of max slots and bounds: one per image and one per 128 tiles of
+    // large ones (slot_ways), 64 bytes apart so that atomics of different
+    // words do not share a cache line (with very many images they spread by
+    // themselves).
+    c.ways = n + c.items1 / 128;
     c.slot_step = n <= 4096 ? kSlotStep : 1;
     c.table_bytes = batch_table_bytes((int)n, c.items1, c.items2, c.items0);
     c.code_elems = store_plane ? plane_capacity(P) : 0;
@@ -183,6 +185,30 @@ static hx_schedule store_schedule(int64_t H, int64_t W) {
     return hx_schedule{64 * c, th, 4, HX_PASS_STORE, HX_REDUCE_TREE};
 }
 
+// The untuned SPECULATE tile height for a batch that would have `tiles`
+// tiles of 48 rows: 48 rows (fewer halo rows computed) where that gives the
+// chip more than a round of its 3072 wave slots, shorter ones where it does
+// not; 16 rows run the short sweep.  Whole calls, us, at 16 / 24 / 32 / 48 /
+// 64 rows (the upper rows before the launches and slots got cheaper):
+//   192 (16 x 256x256 k5)          30.7  31.8  34.9  41.3  48.0
+//   368 (2 x 1080x1920 k5)         30.8  28.5  31.9  38.3  44.3
+//   829 (64 of 64..1024 k5)        50.4  47.7  53.3  66.1  78.5
+//   1462 (4096x4096 k5)                  36.2  41.8  40.4  50.8
+//   1472 (8 x 1080x1920 k5)        62.4  39.8  41.2  42.3  49.9
+//   2038 (64 of 64..2048 k5)       82.1  62.1  57.8  64.1  74.0
+//   3150 (6000x6000 k5)                  68.4  63.7  71.3  65.6
+//   5985 (8192x8192 k5)                 104.3 101.0  96.7 100.5
+//   11776 (64 x 1080x1920 k5)                 183.2 178.5 186.8
+static int spec_ty(int64_t tiles) {
+    return tiles <= 256 ? 16 : tiles <= 1700 ? 24 : tiles <= 4096 ? 32 : 48;
+}
+static int spec_default_ty(int ks, const hx_image* imgs, int32_t n) {
+    const SweepGeom g{ks, batch_sweep_c(), 48};
+    int64_t tiles = 0;
+    for (int i = 0; i < n && tiles <= 4096; ++i) tiles += g.tiles(imgs[i].height, imgs[i].width);
+    return spec_ty(tiles);
+}
+
 hx_schedule choose_schedule(const hx_pipeline* p, int64_t H, int64_t W) {
     if (p->forced) return p->forced_sched;
     hx_schedule s;
@@ -204,6 +230,18 @@ hx_schedule choose_schedule(const hx_pipeline* p, int64_t H, int64_t W) {
             s = hx_schedule{256, th, 4, HX_PASS_STORE, HX_REDUCE_TREE};
         } else {
             s = store_schedule(H, W);
+            // Large images: SPECULATE, where the pipeline holds its scratch
+            // (5 bytes of traffic per pixel and a list against STORE's 13).
+            // Whole calls, us, STORE / SPECULATE: 3000x3001 k5 36.6 / 36.2,
+            // 4096x4096 k5 55.6 / 36.2, k7 60.1 / 44.8, 8192x8192 k7 187 /
+            // 101; new buffers cost SPECULATE a descriptor (about 5 us).
+            constexpr int64_t kSpecPixels = int64_t(12) << 20;
+            constexpr int kBoth = HX_FORM_IMAGE | HX_FORM_BATCH;
+            if (!q.pass_mode && H * W >= kSpecPixels && (q.forms & kBoth) == kBoth) {
+                s.tile_w = 64 * batch_sweep_c();
+                s.tile_h = spec_ty(SweepGeom{q.ksize, batch_sweep_c(), 48}.tiles(H, W));
+                s.pass_mode = HX_PASS_SPECULATE;
+            }
         }
     } else {
         s = hx_schedule{64, 16, 1, HX_PASS_STORE, HX_REDUCE_TREE};
@@ -254,6 +292,7 @@ static ImgArgs base_args(const hx_image* img, uint32_t* slot, float* d_max) {
     a.W = (int32_t)img->width;
     a.op = round4(img->width);
     a.ways = 1;
+    a.slot_step = kSlotStep;
     return a;
 }
 
@@ -265,6 +304,12 @@ static ImgArgs base_args(const hx_image* img, uint32_t* slot, float* d_max) {
 
 // Does the pipeline hold scratch for `form`?
 static bool has_form(const hx_pipeline* p, int form) { return (p->prm.forms & form) != 0; }
+
+// Is `stream` being captured into a graph (or may it not be asked)?
+static bool is_capturing(hipStream_t stream) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone;
+}
 
 hx_status run_image(hx_pipeline* p, const hx_image* img, float* d_max,
                     const hx_schedule& s, hipStream_t stream) {
@@ -381,11 +426,11 @@ static hx_status ctx_init(hx_pipeline* p, BatchContext& c) {
     const int64_t n = p->prm.max_images;
     // One buffer: bounds (8 B each), the epoch and the redo queue's length,
     // cleared once here; then the max slots, the list counts, the redo queue.
-    const int64_t words = 2 * n * k.slot_step + 2 * kSlotStep;
-    HX_TRY(c.state.alloc(sizeof(uint32_t) * (words + n * k.slot_step + 2 * k.items1), m));
+    const int64_t words = 2 * k.ways * k.slot_step + 2 * kSlotStep;
+    HX_TRY(c.state.alloc(sizeof(uint32_t) * (words + k.ways * k.slot_step + 2 * k.items1), m));
     HX_TRY(hipMemset(c.state.ptr, 0, sizeof(uint32_t) * words));
     c.slots = (uint32_t*)c.state.ptr + words;
-    c.cand_n = c.slots + n * k.slot_step;
+    c.cand_n = c.slots + k.ways * k.slot_step;
     c.redo = (int32_t*)(c.cand_n + k.items1);
     HX_TRY(c.table.alloc(k.table_bytes, m));
     HX_TRY(c.h_table.alloc(k.table_bytes, m));
@@ -460,6 +505,16 @@ static bool fits(const BatchCaps& k, const ImgWork& t, int pass) {
            (pass != HX_PASS_STORE || t.code <= k.code_elems);
 }
 
+// Words of the max slot of an image of `tiles` tiles: the largest power of
+// two of at most one per 128 tiles and one per lane.  (One 8192x8192 k7
+// image, 6000 tiles of 48 rows: 148 us a call with one word, 102 with
+// several; in batches, images of a few hundred tiles gain nothing.)
+static int32_t slot_ways(int64_t tiles) {
+    int32_t w = 1;
+    while (w < kSlotWays && 2 * w <= tiles / 128) w *= 2;
+    return w;
+}
+
 // Build the descriptor table of a batch in the context's pinned staging
 // buffer and copy it to the device on `stream`.  The caller has checked
 // that the batch fits the context's capacities.
@@ -479,7 +534,9 @@ static hx_status build_table(hx_pipeline* p, BatchContext& c, const hx_image* im
     }
     if (!fits(p->caps, tot, pass))
         return fail(HX_E_INVALID, "batch exceeds the context's capacities");
-    const size_t bytes = batch_table_bytes(n, tot.tiles, tot.p2, tot.p0);
+    // A batch of one image has no item lists (item k is tile k).
+    const size_t bytes = n == 1 ? batch_table_bytes(1, 0, 0, 0)
+                                : batch_table_bytes(n, tot.tiles, tot.p2, tot.p0);
 
     // Fill the pinned table: header, images, pass-1, pass-2, pass-0 items.
     uint8_t* h = (uint8_t*)c.h_table.ptr;
@@ -491,23 +548,28 @@ static hx_status build_table(hx_pipeline* p, BatchContext& c, const hx_image* im
     hdr.theta = p->prm.thresh_frac;
     hdr.n_items0 = (int32_t)tot.p0;
     hdr.ty = geo.ty;
+    hdr.slot_step = p->caps.slot_step;
     if (spec) {
         hdr.cand_code = (float*)c.cand_code.ptr;
         hdr.cand_row = (int32_t*)c.cand_row.ptr;
         hdr.cand_n = c.cand_n;
         hdr.bound = (unsigned long long*)c.state.ptr;
-        hdr.bound_step = p->caps.slot_step;
-        hdr.epoch = (uint32_t*)(hdr.bound + p->prm.max_images * hdr.bound_step);
+        hdr.epoch = (uint32_t*)(hdr.bound + p->caps.ways * hdr.slot_step);
         hdr.redo_n = hdr.epoch + kSlotStep;
         hdr.redo = c.redo;
     }
     std::memcpy(h, &hdr, sizeof hdr);
     ImgArgs* ia = (ImgArgs*)(h + sizeof(BatchHeader));
     int64_t code_off = 0, list_off = 0, total_px = 0;
+    uint32_t way0 = 0;
     for (int i = 0; i < n; ++i) total_px += imgs[i].height * imgs[i].width;
     for (int i = 0; i < n; ++i) {
-        ia[i] = base_args(&imgs[i], c.slots + (int64_t)i * p->caps.slot_step,
+        ia[i] = base_args(&imgs[i], c.slots + (int64_t)way0 * p->caps.slot_step,
                           d_max ? d_max + i : nullptr);
+        ia[i].slot_step = p->caps.slot_step;
+        ia[i].ways = slot_ways(w[i].tiles);
+        ia[i].way0 = way0;
+        way0 += (uint32_t)ia[i].ways;
         ia[i].ty = geo.ty;
         if (pass == HX_PASS_STORE) ia[i].fout = (float*)c.code.ptr + code_off;
         code_off += w[i].code;
@@ -523,11 +585,12 @@ static hx_status build_table(hx_pipeline* p, BatchContext& c, const hx_image* im
     if (list_off > p->caps.list_entries)
         return fail(HX_E_INVALID, "listing capacity exceeded");  // cannot happen: shares sum to it
     BatchItem* it = (BatchItem*)(ia + n);
-    for (int i = 0; i < n; ++i)
+    const int32_t lists = n > 1 ? n : 0;
+    for (int i = 0; i < lists; ++i)
         for (int64_t t = 0; t < w[i].tiles; ++t) *it++ = BatchItem{i, (int32_t)t};
-    for (int i = 0; i < n; ++i)
+    for (int i = 0; i < lists; ++i)
         for (int64_t t = 0; t < w[i].p2; ++t) *it++ = BatchItem{i, (int32_t)t};
-    for (int i = 0; i < n; ++i)
+    for (int i = 0; i < lists; ++i)
         for (int64_t t = 0; t < w[i].p0; ++t) *it++ = BatchItem{i, (int32_t)t};
 
     HX_TRY(hipMemcpyAsync(c.table.ptr, h, bytes, hipMemcpyHostToDevice, stream));
@@ -553,12 +616,6 @@ static hx_status run_oversized(hx_pipeline* p, BatchContext& c, const hx_image& 
     HX_TRY(launch_sweep(SM_MASK, ks, cw, ty, a, p->taps, p->prm.thresh_frac, stream));
     if (d_max) HX_TRY(launch_write_max(a, stream));
     return HX_OK;
-}
-
-// Is `stream` being captured into a graph (or may it not be asked)?
-static bool is_capturing(hipStream_t stream) {
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    return hipStreamIsCapturing(stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone;
 }
 
 // Launch a batch that fits one context on context c, whose table holds it
@@ -593,24 +650,6 @@ BatchKey batch_key(const hx_image* imgs, int32_t n) {
         return b;
     };
     return BatchKey{lg(px), lg(n)};
-}
-
-// The untuned SPECULATE tile height: 48 rows (fewer halo rows computed)
-// where that gives the chip more than two waves per SIMD of tiles, shorter
-// ones where it does not; 16 rows run the short sweep.  Whole calls, us, by
-// tile height (16 / 24 / 32 / 48 / 64 rows) and tiles of 48 rows:
-//   192 (16 x 256x256 k5)          32.4  33.1  36.0  42.6  49.3
-//   368 (2 x 1080x1920 k5)         38.2  36.0  38.2  44.1  50.5
-//   829 (64 of 64..1024 k5)        55.4  52.9  58.3  70.4  83.4
-//   1472 (8 x 1080x1920 k5)        66.1  45.5  47.3  48.1  55.7
-//   2038 (64 of 64..2048 k5)       86.3  66.6  62.7  68.0  78.0
-//   8300 (256 of 64..2048 k5)     283.7 195.4 185.2 183.9 189.8
-//   11776 (64 x 1080x1920 k5)     316.4 198.5 198.0 196.4 204.8
-static int spec_default_ty(int ks, const hx_image* imgs, int32_t n) {
-    const SweepGeom g{ks, batch_sweep_c(), 48};
-    int64_t tiles = 0;
-    for (int i = 0; i < n && tiles <= 2560; ++i) tiles += g.tiles(imgs[i].height, imgs[i].width);
-    return tiles <= 256 ? 16 : tiles <= 1280 ? 24 : tiles <= 2560 ? 32 : 48;
 }
 
 hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
@@ -1000,9 +1039,15 @@ hx_status hx_edge_detect(hx_pipeline* p, const hx_image* img, float* d_max,
     if (!p) return fail(HX_E_INVALID, "pipeline is NULL");
     hx_status st = validate_image(p, img);
     if (st != HX_OK) return st;
-    const hx_schedule s = choose_schedule(p, img->height, img->width);
+    hx_schedule s = choose_schedule(p, img->height, img->width);
     st = validate_schedule(p, s);
     if (st != HX_OK) return st;
+    // SPECULATE chosen by size alone rebuilds a table that the host keeps;
+    // a call recorded into a graph takes STORE, which needs none.
+    if (s.fusion_depth == 4 && s.pass_mode == HX_PASS_SPECULATE && !p->forced &&
+        !p->prm.pass_mode && !p->tuned.count(shape_class(img->height, img->width)) &&
+        is_capturing(stream))
+        s = store_schedule(img->height, img->width);
     TraceRange trace("hx.edge_detect");
     logf(2, "per-image call %lldx%lld: %s", (long long)img->height, (long long)img->width,
          schedule_text(s).c_str());

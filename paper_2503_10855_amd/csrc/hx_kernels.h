@@ -46,13 +46,13 @@ struct SpecTile {
     uint32_t cap;    // entries the tile may write; n may exceed it
 };
 
-// A per-image STORE call's max slot is spread over several words, one per
-// 64 bytes (ImgArgs::ways of them, a power of two): a workgroup folds its
-// maximum into the word of its index, and the threshold kernel takes the
-// max of the words, one per lane.  One word serialises its atomics (about
-// 10 ns each across the XCDs: a 1080p image in 1180 workgroups took 19.8 us
-// with one word and 11.1 us with 64).
-constexpr int kSlotWays = 64;
+// An image's max slot is spread over several words, one per 64 bytes
+// (ImgArgs::ways of them, a power of two): a workgroup folds its maximum
+// into the word of its index, and readers take the max of the words, one
+// per lane.  One word serialises its atomics (about 10 ns each across the
+// XCDs: STORE's pass 1 of a 1080p image in 1180 workgroups took 19.8 us with
+// one word and 11.1 us with 64).
+constexpr int kSlotWays = 64;    // at most: one per lane
 constexpr int kSlotStep = 16;    // words from one to the next
 constexpr int kSlotWords = kSlotWays * kSlotStep;
 
@@ -68,8 +68,8 @@ struct ImgArgs {
     float* fout;
     float* g2;
     int64_t op;
-    uint32_t* slot;   // max G^2 bits of this image (STORE, per image: of
-                      // each of `ways` words, kSlotStep apart)
+    uint32_t* slot;   // max G^2 bits of this image: `ways` words, slot_step
+                      // apart
     float* dmax;      // optional: receives M = sqrt(max G^2)
     int32_t H, W;
     // Batched SPECULATE: the image's pass-1 tile t lists its pixels in
@@ -77,17 +77,19 @@ struct ImgArgs {
     uint32_t list_base, list_cap;
     // Batched calls: rows per sweep tile of this image (a multiple of 8).
     int32_t ty;
-    int32_t ways;     // words of the max slot (1 outside the STORE forms)
+    int32_t ways, slot_step;
+    uint32_t way0;    // batched: the index of its first word among all images'
 };
 
 // The word of the max slot workgroup `block` folds into.
 __device__ __forceinline__ uint32_t* slot_word(const ImgArgs& a, int block) {
-    return a.slot + (block & (a.ways - 1)) * kSlotStep;
+    return a.slot + (int64_t)(block & (a.ways - 1)) * a.slot_step;
 }
 // The image's max G^2 bits from all words of its slot, in every lane.
 __device__ __forceinline__ uint32_t slot_max(const ImgArgs& a) {
     const int l = lane_id();
-    return __float_as_uint(wave_max(l < a.ways ? __uint_as_float(a.slot[l * kSlotStep]) : 0.0f));
+    return __float_as_uint(
+        wave_max(l < a.ways ? __uint_as_float(as_global(a.slot)[(int64_t)l * a.slot_step]) : 0.0f));
 }
 
 // Geometry of a register-sweep tile (one wave64): C input columns per lane,
@@ -177,7 +179,7 @@ struct BatchHeader {
     float theta;
     int32_t n_items0;   // SPECULATE: sampled-band items of pass 0
     int32_t ty;         // rows per sweep tile of every image
-    int32_t bound_step; // elements of `bound` from one image's to the next's
+    int32_t slot_step;  // words between max slots, and bounds (8 B) between bounds
     // SPECULATE: the listed pixels of pass-1 item k (a tile of image i)
     // occupy the image's entries for that tile (ImgArgs::list_base and
     // list_cap) of cand_code / cand_row, and cand_n[k] counts them; a tile
@@ -187,7 +189,8 @@ struct BatchHeader {
     int32_t* cand_row;
     uint32_t* cand_n;
     // SPECULATE: per-image lower bounds of max G^2, written by pass 0 and
-    // only read by pass 1 (whose own maxima go to the images' slots).  A
+    // only read by pass 1 (whose own maxima go to the images' slots), in as
+    // many words per image as its max slot has (from ImgArgs::way0).  A
     // bound is (epoch << 32) | bits of G^2: pass 0 folds values of the
     // current epoch with a 64-bit max, so a bound left by an earlier batch
     // needs no clearing (its epoch is lower); pass 2 advances the epoch.

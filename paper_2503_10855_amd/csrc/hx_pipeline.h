@@ -73,7 +73,8 @@ struct HostBuf {
 struct BatchCaps {
     int64_t items1 = 0, items2 = 0, items0 = 0;  // work items per pass
     int64_t list_entries = 0;                    // SPECULATE listing
-    int32_t slot_step = 1;   // words between images' max slots (8 B between bounds)
+    int64_t ways = 0;        // words of max slots, and of bounds
+    int32_t slot_step = 1;   // words between max slots (8 B between bounds)
     size_t table_bytes = 0;
     int64_t code_elems = 0;                      // STORE code plane (0: none)
 };

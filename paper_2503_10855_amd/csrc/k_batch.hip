@@ -26,7 +26,7 @@ static __global__ void k_batch_reset(const uint8_t* __restrict__ table) {
     const ImgArgs* imgs = reinterpret_cast<const ImgArgs*>(table + sizeof(BatchHeader));
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < h.n_images;
          i += gridDim.x * blockDim.x)
-        *imgs[i].slot = 0;
+        for (int w = 0; w < imgs[i].ways; ++w) imgs[i].slot[(int64_t)w * h.slot_step] = 0;
 }
 
 hipError_t launch_batch_reset(const void* d_table, int max_images, hipStream_t s) {

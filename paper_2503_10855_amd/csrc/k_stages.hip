@@ -243,7 +243,7 @@ __global__ __launch_bounds__(256) void k_threshold_code(ImgArgs a, float theta,
     if (blockIdx.x == 0) {
         if (threadIdx.x == 0 && a.dmax) *a.dmax = max_from(m2);
         // The next per-image call's max slot.
-        if (zero_next && (int)threadIdx.x < a.ways) zero_next[threadIdx.x * kSlotStep] = 0u;
+        if (zero_next && (int)threadIdx.x < a.ways) zero_next[threadIdx.x * a.slot_step] = 0u;
     }
     const int wq = (a.W + 3) / 4;
     const bool mvec = ((reinterpret_cast<uintptr_t>(a.mask) % 4) == 0) & ((a.mp % 4) == 0);

@@ -105,3 +105,31 @@ def test_batch_default_heights_match_per_image(hx, n, side):
         ref = [p.edge_detect(s, dmax=one[i:i + 1]) for i, s in enumerate(srcs)]
         p.sync()
     assert all(torch.equal(m, r) for m, r in zip(got, ref)) and torch.equal(dm, one)
+
+
+@pytest.mark.parametrize("ks,shape", [(3, (3200, 4001)), (7, (12600, 1000))])
+def test_large_image_default_matches_store(hx, ks, shape):
+    """Above the size where an untuned per-image call changes from STORE to
+    SPECULATE: the same masks and maximum, eagerly, and inside a captured
+    graph (where it stays with STORE)."""
+    img = synth.image(*shape, 304, ks, n_rect=16)
+    src = torch.from_numpy(img).cuda()
+    with hx.Pipeline(ksize=ks, sigma=SIGMA[ks], theta=THETA, max_pixels=img.size,
+                     max_images=1) as p:
+        assert p.schedule(*shape)[3] == hx.PASS_SPECULATE
+        assert p.schedule(500, 500)[3] == hx.PASS_STORE
+        dm = torch.zeros(3, device="cuda")
+        print(f"k{ks} {shape}", flush=True)
+        m = p.edge_detect(src, dmax=dm[:1])
+        p.set_schedule(128, 16, 4, hx.PASS_STORE)
+        ref = p.edge_detect(src, dmax=dm[1:2])
+        p.set_schedule()
+        p.sync()
+        got = torch.zeros_like(ref)
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            p.edge_detect(src, got, dmax=dm[2:])
+        g.replay()
+        torch.cuda.synchronize()
+    assert torch.equal(m, ref) and torch.equal(got, ref)
+    assert dm[0] == dm[1] and dm[2] == dm[1]
