@@ -311,6 +311,67 @@ static bool is_capturing(hipStream_t stream) {
     return hipStreamIsCapturing(stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone;
 }
 
+// This call's max slot of the pair, *next left at zero for the next call.
+// The fused STORE form's threshold kernel zeroes the other slot (store), so
+// when the previous call left this one at zero it needs no clearing launch;
+// every other form clears both slots first.
+static hipError_t begin_slots(hx_pipeline* p, bool store, hipStream_t stream, uint32_t** slot,
+                              uint32_t** next) {
+    uint32_t* const slots = (uint32_t*)p->slot1.ptr;
+    *slot = slots + p->img_parity * kSlotWords;
+    *next = slots + (p->img_parity ^ 1) * kSlotWords;
+    p->img_parity ^= 1;
+    p->img_last_slot = *slot;
+    const bool slot_zero = p->img_next_zero;
+    p->img_next_zero = false;  // until this call's launches are all enqueued
+    if (store && slot_zero) return hipSuccess;
+    return launch_fill_u32(slots, 0u, 2 * kSlotWords, stream);
+}
+
+// The STORE form on the short sweep alone, for every blur size and with the
+// stage planes so (nullable) written on the way.  Blur sizes above 7 run
+// their blur as a sweep of its own and the rest on its plane (with the
+// one-tap blur, exactly the identity): 1080x1920 k9 77 us a call in five
+// unfused kernels (blur 26), 24 in these three (blur 7.8).  The stage hook
+// on 1080x1920 k5: 78 us in five kernels and a copy of the planes, 25 here.
+static hx_status run_short(hx_pipeline* p, const hx_image* img, float* d_max,
+                           const StageOut* so, hipStream_t stream) {
+    uint32_t *slot, *next;
+    HX_TRY(begin_slots(p, true, stream, &slot, &next));
+    ImgArgs a = base_args(img, slot, d_max);
+    a.ways = kSlotWays;
+    a.fout = (float*)p->planeA.ptr;
+    int ks = p->prm.ksize;
+    Taps t = p->taps;
+    if (ks > 7) {
+        // One column per lane: the ring of 2R earlier rows is what a tile's
+        // registers go to.  16 rows, 8 while the image has few tiles (700^2
+        // k15 7.0 against 6.8 us, 256^2 k9 4.2 against 4.9).
+        const int th = img->height * img->width <= (int64_t(1) << 18) ? 8 : 16;
+        HX_TRY(launch_tile(TM_BLUR, ks, 1, th, a, t, StageOut{}, stream));
+        a.src = a.fout;
+        a.sp = a.op;
+        a.fout = (float*)p->planeL.ptr;
+        ks = 1;
+        t = Taps{};
+        t.g[0] = 1.0f;
+    }
+    const hx_schedule sc = store_schedule(img->height, img->width);
+    HX_TRY(launch_tile(so ? (int)TM_STAGES : (int)SM_STORE, ks, sc.tile_w / 64, sc.tile_h, a, t,
+                       so ? *so : StageOut{}, stream));
+    HX_TRY(launch_threshold_code(a, p->prm.thresh_frac, stream, next));
+    p->img_next_zero = true;
+    return HX_OK;
+}
+
+// Does the depth-1 schedule s, chosen and not asked for, stand for run_short
+// (a blur size without fused sweeps)?  Its planes' rows are addressed with
+// 32 bits.
+static bool takes_short_form(const hx_pipeline* p, const hx_image* img, const hx_schedule& s) {
+    return !p->forced && !p->prm.fusion_depth && !fused_ks(p->prm.ksize) &&
+           s.reduce_mode == HX_REDUCE_TREE && img->width < (int64_t(1) << 28);
+}
+
 hx_status run_image(hx_pipeline* p, const hx_image* img, float* d_max,
                     const hx_schedule& s, hipStream_t stream) {
     // SPECULATE runs the batch kernels on a batch of one.
@@ -326,22 +387,14 @@ hx_status run_image(hx_pipeline* p, const hx_image* img, float* d_max,
                     "hold %lld (raise max_pixels)",
                     (long long)img->height, (long long)img->width,
                     (long long)plane_need(img->height, img->width), (long long)p->plane_elems);
-    // The max slot: this call's of the pair, the other left at zero for the
-    // next call.  The fused STORE form's threshold kernel zeroes the other
-    // slot, so when the previous call left this one at zero the form needs
-    // no clearing launch; every other form clears both slots first.
-    uint32_t* const slots = (uint32_t*)p->slot1.ptr;
-    uint32_t* const slot = slots + p->img_parity * kSlotWords;
-    uint32_t* const next = slots + (p->img_parity ^ 1) * kSlotWords;
-    p->img_parity ^= 1;
-    p->img_last_slot = slot;
     const bool store_fused = s.fusion_depth == 4 && s.pass_mode == HX_PASS_STORE;
-    const bool slot_zero = p->img_next_zero;
-    p->img_next_zero = false;  // until this call's launches are all enqueued
+    if (s.fusion_depth == 1 && takes_short_form(p, img, s))
+        return run_short(p, img, d_max, nullptr, stream);
+    uint32_t *slot, *next;
+    HX_TRY(begin_slots(p, store_fused, stream, &slot, &next));
     ImgArgs a = base_args(img, slot, d_max);
     const float theta = p->prm.thresh_frac;
     const int ks = p->prm.ksize;
-    if (!(store_fused && slot_zero)) HX_TRY(launch_fill_u32(slots, 0u, 2 * kSlotWords, stream));
     if (s.fusion_depth == 4) {
         const int c = s.tile_w / 64;
         if (s.pass_mode == HX_PASS_STORE) {
@@ -1134,16 +1187,25 @@ hx_status hx_edge_detect_stages(hx_pipeline* p, const hx_image* img, float* d_B,
     hx_status st = validate_image(p, img);
     if (st != HX_OK) return st;
     DeviceGuard g(p->device);
-    // Depth 1 unless a depth-1, -2 or -3 schedule is forced; depths 2 and 3
-    // keep one stage on chip (L, respectively B), which cannot be exported.
+    // The short sweep writes every plane, unless a depth-1, -2 or -3 schedule
+    // is forced; depths 2 and 3 keep one stage on chip (L, respectively B),
+    // which cannot be exported.
     hx_schedule s{64, 16, 1, HX_PASS_STORE, HX_REDUCE_TREE};
     if (p->forced && p->forced_sched.fusion_depth <= 3) s = p->forced_sched;
     if (s.fusion_depth == 2 && d_L)
         return fail(HX_E_UNSUPPORTED, "fusion depth 2 keeps L on chip: pass d_L = NULL");
     if (s.fusion_depth == 3 && d_B)
         return fail(HX_E_UNSUPPORTED, "fusion depth 3 keeps B on chip: pass d_B = NULL");
+    const bool as_asked = p->forced && p->forced_sched.fusion_depth <= 3;
     st = img_order_begin(p, stream);
     if (st != HX_OK) return st;
+    if (!as_asked && has_form(p, HX_FORM_STAGES) && img->width < (int64_t(1) << 28) &&
+        plane_need(img->height, img->width) <= p->plane_elems) {
+        const StageOut so{d_B, d_L, d_G, d_Z};
+        st = run_short(p, img, d_max, &so, stream);
+        hx_status st2 = img_order_end(p, stream);
+        return st != HX_OK ? st : st2;
+    }
     st = run_image(p, img, d_max, s, stream);
     if (st == HX_OK) {
         ImgArgs a = base_args(img, p->img_last_slot, d_max);

@@ -133,3 +133,29 @@ def test_large_image_default_matches_store(hx, ks, shape):
         torch.cuda.synchronize()
     assert torch.equal(m, ref) and torch.equal(got, ref)
     assert dm[0] == dm[1] and dm[2] == dm[1]
+
+
+@pytest.mark.parametrize("ks", [1, 3, 5, 7, 9, 15])
+def test_stage_planes_and_masks_match_depth_one(hx, ks):
+    """The stage hook's planes and mask, and for blur sizes without fused
+    sweeps the per-image call, against one kernel per stage (depth 1,
+    forced): the same bits at tile edges, pitched and odd widths."""
+    sigma = 0.4 * ks
+    shapes = [(1, 1), (2, 7), (9, 56), (17, 57), (8, 121), (33, 250), (40, 63 - ks), (700, 1101)]
+    with hx.Pipeline(ksize=ks, sigma=sigma, theta=THETA, max_pixels=1 << 20) as p:
+        for i, (h, w) in enumerate(shapes):
+            img = synth.image(h, w, 305, i)
+            src, _ = pitched(img, (0, 5, 2)[i % 3])
+            dm = torch.zeros(2, device="cuda")
+            print(f"k{ks} {h}x{w}", flush=True)
+            p.set_schedule()
+            got = p.edge_detect_stages(src)
+            some = p.edge_detect_stages(src, stages=("Z", "G"))
+            m = p.edge_detect(src, dmax=dm[:1])
+            p.set_schedule(64, 16, 1)
+            ref = p.edge_detect_stages(src)
+            r = p.edge_detect(src, dmax=dm[1:])
+            for k in ref:
+                assert torch.equal(got[k], ref[k]), (k, h, w)
+                assert k not in some or torch.equal(some[k], ref[k]), (k, h, w)
+            assert torch.equal(m, r) and dm[0] == dm[1]
