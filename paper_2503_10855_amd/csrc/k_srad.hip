@@ -9,8 +9,8 @@
 //   J'   = J + lambda/4 (c dN + c_S dS + c dW + c_E dE)
 //
 // Every kernel is a register sweep: a wave64 owns a strip of 256 columns
-// (4 per lane, 16-byte loads) and a band of kBH rows, and walks the band
-// top to bottom keeping the last rows in registers; west / east
+// (4 per lane, 16-byte loads) and a band of bh <= 63 rows, and walks the band
+// (odd ones bottom to top) keeping the last rows in registers; west / east
 // neighbours come from the adjacent lane by DPP, and the strip's outer
 // neighbours from one extra load per row.  Loads run kRing rows ahead.
 // Workgroups (4 waves, 4 adjacent strips) are numbered so that each XCD
@@ -37,16 +37,12 @@
 namespace hx {
 namespace {
 
-#ifndef HX_SRAD_BH
-#define HX_SRAD_BH 32
-#endif
 #ifndef HX_SRAD_RING
 #define HX_SRAD_RING 4
 #endif
 constexpr int kSW = 256;          // strip width: 64 lanes x 4 columns
-constexpr int kBH = HX_SRAD_BH;   // band height
+constexpr int kBH = 32;           // band height of images a few columns wide
 constexpr int kRing = HX_SRAD_RING;   // rows the fused sweep loads ahead
-static_assert(kBH >= 1 && kBH <= 63, "kBH + 1 rows of east c must fit one VGPR");
 static_assert(kRing % 4 == 0, "the fused sweep's 4-row window must divide the ring");
 enum { kFused = 0, kCoeff = 1, kUpdate = 2, kSums = 3 };
 
@@ -60,7 +56,7 @@ struct SradArgs {
     const double* prev;  // workgroup partial pairs of the sums of J (fused, coeff)
     double* part;        // this kernel's workgroup partial pairs (fused, update, sums)
     double* q_log;       // nullable: q0^2 of iteration `it`
-    int H, W, nstrips, nitems, nprev, it;
+    int H, W, nstrips, nitems, nprev, it, bh;
     float step;          // lambda / 4
     int vin, vout, vc;   // rows of J / out / c are 16-byte aligned
 };
@@ -274,44 +270,51 @@ __device__ __forceinline__ void sweep_coeff(const SradArgs& a, const Strip& g, f
         });
 }
 
-// J and c rows y0-1 .. y1; at row t >= 2, J' of image row y0 + t - 2.
-template <bool FULL>
+// J and c rows y0-1 .. y1 (UP: from y1 up); at row t >= 2, J' of the row
+// before it.
+template <bool FULL, bool UP>
 __device__ __forceinline__ void sweep_update(const SradArgs& a, const Strip& g, double& s,
                                              double& s2) {
     Row j0{}, j1{}, j2{};
-    float c0[4] = {}, c1[4] = {}, c0e = 0.0f, c1e = 0.0f;
+    float c0[4] = {}, c1[4] = {}, c2[4] = {}, c0e = 0.0f, c1e = 0.0f;
+    auto row = [&](int t) { return UP ? g.y1 - t : g.y0 - 1 + t; };
     auto load = [&](int t) {
-        return Pair{load_row<FULL>(a.J, a.pin, g.y0 - 1 + t, g),
-                    load_row<FULL>(a.c, a.pc, g.y0 - 1 + t, g)};
+        return Pair{load_row<FULL>(a.J, a.pin, row(t), g), load_row<FULL>(a.c, a.pc, row(t), g)};
     };
     auto push = [&](const Pair& in) {
         j2 = j1;
         j1 = j0;
         j0 = with_nb(in.j);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) c1[k] = c0[k];
+        for (int k = 0; k < 4; ++k) {
+            c2[k] = c1[k];
+            c1[k] = c0[k];
+            c0[k] = in.c.v[k];
+        }
         c1e = c0e;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) c0[k] = in.c.v[k];
         c0e = from_east(in.c.ex, in.c.v[0]);
     };
     sweep_rows<2, 6>(
         g.y1 - g.y0 + 2, load, [&](const Pair& in, int) { push(in); },
         [&](const Pair& in, int t) {
             push(in);
+            const Row &n = UP ? j0 : j2, &so = UP ? j2 : j0;
+            const float(&cs)[4] = UP ? c2 : c0;
             float v[4];
 #pragma unroll
             for (int k = 0; k < 4; ++k)
-                v[k] = srad_new(j1.v[k], j2.v[k], j0.v[k], west_of(j1, k), east_of(j1, k),
-                                c1[k], c0[k], k < 3 ? c1[k + 1] : c1e, a.step);
-            store_row<FULL>(a.out, a.pout, g.y0 + t - 2, g, v);
+                v[k] = srad_new(j1.v[k], n.v[k], so.v[k], west_of(j1, k), east_of(j1, k), c1[k],
+                                cs[k], k < 3 ? c1[k + 1] : c1e, a.step);
+            store_row<FULL>(a.out, a.pout, row(t - 1), g, v);
             accumulate<FULL>(v, g, s, s2);
         });
 }
 
-// Fused.  J rows y0-1 .. y1+1; at row t >= 2, c of image row y0 + t - 2
-// (into c1, the previous c1 moving to c2); at t >= 3, J' of row y0 + t - 3.
-template <bool FULL>
+// Fused.  J rows y0-1 .. y1+1 (UP: from y1+1 up).  At row t >= 2, c of the
+// row before it (into c1, the previous c1 moving to c2); at t >= 3, J': going
+// down of the row two before, whose c_S has just been computed; going up of
+// the row before, whose c_S is the previous c.
+template <bool FULL, bool UP>
 __device__ __forceinline__ void sweep_fused(const SradArgs& a, const Strip& g, float q0,
                                             float K, float lo, double& s, double& s2) {
     const int H = g.H, W = g.W;
@@ -327,35 +330,87 @@ __device__ __forceinline__ void sweep_fused(const SradArgs& a, const Strip& g, f
     }
     Row j0{}, j1{}, j2{}, j3{};
     float c1[4] = {}, c2[4] = {}, c1e = 0.0f, c2e = 0.0f;
-    auto load = [&](int t) { return load_row<FULL>(a.J, a.pin, g.y0 - 1 + t, g); };
+    auto row = [&](int t) { return UP ? g.y1 + 1 - t : g.y0 - 1 + t; };
+    auto load = [&](int t) { return load_row<FULL>(a.J, a.pin, row(t), g); };
     auto push = [&](const Raw& in, int t) {
-        j3 = j2;
+        if constexpr (!UP) j3 = j2;
         j2 = j1;
         j1 = j0;
         j0 = with_nb(in);
         if (t >= 2) {
+            const Row &n = UP ? j0 : j2, &so = UP ? j2 : j0;
 #pragma unroll
             for (int k = 0; k < 4; ++k) c2[k] = c1[k];
             c2e = c1e;
 #pragma unroll
             for (int k = 0; k < 4; ++k)
-                c1[k] = srad_c(j1.v[k], j2.v[k], j0.v[k], west_of(j1, k), east_of(j1, k), q0,
-                               K, lo);
+                c1[k] = srad_c(j1.v[k], n.v[k], so.v[k], west_of(j1, k), east_of(j1, k), q0, K,
+                               lo);
             const float cx =
-                __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ce), t - 2));
+                __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ce), row(t - 1) - g.y0));
             c1e = from_east(cx, c1[0]);
         }
     };
     sweep_rows<3, kRing>(g.y1 - g.y0 + 3, load, push, [&](const Raw& in, int t) {
         push(in, t);
+        const Row &m = UP ? j1 : j2, &n = UP ? j0 : j3, &so = UP ? j2 : j1;
+        const float(&c)[4] = UP ? c1 : c2;
+        const float(&cs)[4] = UP ? c2 : c1;
+        const float ce3 = UP ? c1e : c2e;
         float v[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k)
-            v[k] = srad_new(j2.v[k], j3.v[k], j1.v[k], west_of(j2, k), east_of(j2, k), c2[k],
-                            c1[k], k < 3 ? c2[k + 1] : c2e, a.step);
-        store_row<FULL>(a.out, a.pout, g.y0 + t - 3, g, v);
+            v[k] = srad_new(m.v[k], n.v[k], so.v[k], west_of(m, k), east_of(m, k), c[k], cs[k],
+                            k < 3 ? c[k + 1] : ce3, a.step);
+        store_row<FULL>(a.out, a.pout, row(UP ? t - 1 : t - 2), g, v);
         accumulate<FULL>(v, g, s, s2);
     });
+}
+
+// Level 3 of the previous kernel's sums: every workgroup folds all pairs;
+// the iteration's constants from them.
+__device__ __forceinline__ void fold_sums(const SradArgs& a, double (&sh)[2][4], int lane,
+                                          int wave, float& q0, float& K, float& lo) {
+    double s = 0.0, s2 = 0.0;
+    for (int i = threadIdx.x; i < a.nprev; i += 256) {
+        s += a.prev[2 * i];
+        s2 += a.prev[2 * i + 1];
+    }
+    s = wave_sum_d(s);
+    s2 = wave_sum_d(s2);
+    if (lane == 0) {
+        sh[0][wave] = s;
+        sh[1][wave] = s2;
+    }
+    __syncthreads();
+    const double S = ((sh[0][0] + sh[0][1]) + sh[0][2]) + sh[0][3];
+    const double S2 = ((sh[1][0] + sh[1][1]) + sh[1][2]) + sh[1][3];
+    const double npix = (double)a.H * (double)a.W;
+    const double mean = S / npix;
+    const double var = S2 / npix - mean * mean;
+    const double q = var / (mean * mean);
+    if (blockIdx.x == 0 && threadIdx.x == 0 && a.q_log) a.q_log[a.it] = q;
+    q0 = (float)q;
+    const bool flat = !(q0 > 0.0f);
+    K = flat ? 0.0f : (float)(1.0 / (q * (1.0 + q)));
+    lo = flat ? 1.0f : 0.0f;
+    __syncthreads();   // sh is reused
+}
+
+// Level 2: the wave's lanes by shuffles, the workgroup's waves in order.
+__device__ __forceinline__ void write_sums(const SradArgs& a, double (&sh)[2][4], int lane,
+                                           int wave, double s, double s2) {
+    s = wave_sum_d(s);
+    s2 = wave_sum_d(s2);
+    if (lane == 0) {
+        sh[0][wave] = s;
+        sh[1][wave] = s2;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        a.part[2 * blockIdx.x] = ((sh[0][0] + sh[0][1]) + sh[0][2]) + sh[0][3];
+        a.part[2 * blockIdx.x + 1] = ((sh[1][0] + sh[1][1]) + sh[1][2]) + sh[1][3];
+    }
 }
 
 }  // namespace
@@ -369,39 +424,15 @@ __global__ __launch_bounds__(256) void k_srad_sweep(SradArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     float q0 = 0.0f, K = 0.0f, lo = 1.0f;
     if constexpr (MODE == kFused || MODE == kCoeff) {
-        // Level 3 of the previous sums: every workgroup folds all pairs.
-        double s = 0.0, s2 = 0.0;
-        for (int i = threadIdx.x; i < a.nprev; i += 256) {
-            s += a.prev[2 * i];
-            s2 += a.prev[2 * i + 1];
-        }
-        s = wave_sum_d(s);
-        s2 = wave_sum_d(s2);
-        if (lane == 0) {
-            sh[0][wave] = s;
-            sh[1][wave] = s2;
-        }
-        __syncthreads();
-        const double S = ((sh[0][0] + sh[0][1]) + sh[0][2]) + sh[0][3];
-        const double S2 = ((sh[1][0] + sh[1][1]) + sh[1][2]) + sh[1][3];
-        const double npix = (double)a.H * (double)a.W;
-        const double mean = S / npix;
-        const double var = S2 / npix - mean * mean;
-        const double q = var / (mean * mean);
-        if (blockIdx.x == 0 && threadIdx.x == 0 && a.q_log) a.q_log[a.it] = q;
-        q0 = (float)q;
-        const bool flat = !(q0 > 0.0f);
-        K = flat ? 0.0f : (float)(1.0 / (q * (1.0 + q)));
-        lo = flat ? 1.0f : 0.0f;
-        __syncthreads();   // sh is reused below
+        fold_sums(a, sh, lane, wave, q0, K, lo);
     }
     double s = 0.0, s2 = 0.0;
     const int item = xcd_block(blockIdx.x, gridDim.x) * 4 + wave;
     if (item < a.nitems) {
         Strip g;
         g.x0 = (item % a.nstrips) * kSW;
-        g.y0 = (item / a.nstrips) * kBH;
-        g.y1 = g.y0 + kBH < a.H ? g.y0 + kBH : a.H;
+        g.y0 = (item / a.nstrips) * a.bh;
+        g.y1 = g.y0 + a.bh < a.H ? g.y0 + a.bh : a.H;
         g.H = a.H;
         g.W = a.W;
         g.lane = lane;
@@ -412,56 +443,191 @@ __global__ __launch_bounds__(256) void k_srad_sweep(SradArgs a) {
         } else if constexpr (MODE == kCoeff) {
             if (inside && a.vin && a.vout) sweep_coeff<true>(a, g, q0, K, lo);
             else sweep_coeff<false>(a, g, q0, K, lo);
-        } else if constexpr (MODE == kUpdate) {
-            if (inside && a.vin && a.vc && a.vout) sweep_update<true>(a, g, s, s2);
-            else sweep_update<false>(a, g, s, s2);
         } else {
-            if (inside && a.vin && a.vout) sweep_fused<true>(a, g, q0, K, lo, s, s2);
-            else sweep_fused<false>(a, g, q0, K, lo, s, s2);
+            // Odd bands sweep upwards: neighbouring bands then read the rows
+            // they share at the same time, and the second read hits L2.
+            const bool up = ((item / a.nstrips) & 1) != 0;
+            if constexpr (MODE == kUpdate) {
+                const bool full = inside && a.vin && a.vc && a.vout;
+                if (full && !up) sweep_update<true, false>(a, g, s, s2);
+                else if (full) sweep_update<true, true>(a, g, s, s2);
+                else if (!up) sweep_update<false, false>(a, g, s, s2);
+                else sweep_update<false, true>(a, g, s, s2);
+            } else {
+                const bool full = inside && a.vin && a.vout;
+                if (full && !up) sweep_fused<true, false>(a, g, q0, K, lo, s, s2);
+                else if (full) sweep_fused<true, true>(a, g, q0, K, lo, s, s2);
+                else if (!up) sweep_fused<false, false>(a, g, q0, K, lo, s, s2);
+                else sweep_fused<false, true>(a, g, q0, K, lo, s, s2);
+            }
         }
     }
-    if constexpr (MODE != kCoeff) {
-        s = wave_sum_d(s);
-        s2 = wave_sum_d(s2);
-        if (lane == 0) {
-            sh[0][wave] = s;
-            sh[1][wave] = s2;
-        }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            a.part[2 * blockIdx.x] = ((sh[0][0] + sh[0][1]) + sh[0][2]) + sh[0][3];
-            a.part[2 * blockIdx.x + 1] = ((sh[1][0] + sh[1][1]) + sh[1][2]) + sh[1][3];
-        }
-    }
+    if constexpr (MODE != kCoeff) write_sums(a, sh, lane, wave, s, s2);
 }
 
+// ------------------------------------------------------- short tiles --
+// Images that give the sweeps above too few waves run in tiles of 61 columns
+// (one per lane, the outer lanes holding the halo) by BH rows, fully
+// unrolled.  All of a tile's rows are loaded before the previous kernel's
+// sums are folded, so an iteration pays one memory latency, and one variant
+// serves every border and alignment.  Same arithmetic as the sweeps; the
+// order of the sums is the tiles', in both forms.  Per iteration, us, sweeps
+// and tiles: 256x256 13.3 and 4.6, 512x512 14.2 and 5.2 (32 waves of 35
+// serial rows against 576 of 11), 1024x1024 14.7 and 7.2.
+constexpr int kTW = 61;   // c of lane 62 is the last one read, J of lane 63
+
+template <int MODE, int BH>
+__global__ __launch_bounds__(256) void k_srad_tile(SradArgs a) {
+    // J rows from y0 - 1 (sums: from y0); c rows from y0.
+    constexpr int NJ = MODE == kFused ? BH + 3 : MODE == kSums ? BH : BH + 2;
+    constexpr int NC = MODE == kCoeff ? BH : BH + 1;
+    constexpr int J0 = MODE == kSums ? 0 : 1;
+    __shared__ double sh[2][4];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int item = xcd_block(blockIdx.x, gridDim.x) * 4 + wave;
+    const bool live = item < a.nitems;
+    const int x0 = (item % a.nstrips) * kTW, y0 = (item / a.nstrips) * BH;
+    const int x = x0 + lane - 1;
+    const uint32_t xc = (uint32_t)clampi_s(x, 0, a.W - 1);
+    auto load = [&](const float* P, int64_t pitch, int r) {
+        return at<const float>(P + (int64_t)clampi_s(r, 0, a.H - 1) * pitch, xc);
+    };
+    float j[NJ], c[NC];
+    if (live) {
+#pragma unroll
+        for (int r = 0; r < NJ; ++r) j[r] = load(a.J, a.pin, y0 - J0 + r);
+        if constexpr (MODE == kUpdate) {
+#pragma unroll
+            for (int r = 0; r < NC; ++r) c[r] = load(a.c, a.pc, y0 + r);
+        }
+    }
+    float q0 = 0.0f, K = 0.0f, lo = 1.0f;
+    if constexpr (MODE == kFused || MODE == kCoeff) fold_sums(a, sh, lane, wave, q0, K, lo);
+    double s = 0.0, s2 = 0.0;
+    if (live) {
+        if constexpr (MODE == kFused || MODE == kCoeff) {
+#pragma unroll
+            for (int r = 0; r < NC; ++r)
+                c[r] = srad_c(j[r + 1], j[r], j[r + 2], from_west(0.0f, j[r + 1]),
+                              from_east(0.0f, j[r + 1]), q0, K, lo);
+        }
+        const bool mine = lane >= 1 && lane <= kTW && x < a.W;
+#pragma unroll
+        for (int r = 0; r < BH; ++r) {
+            float v;
+            if constexpr (MODE == kCoeff) v = c[r];
+            else if constexpr (MODE == kSums) v = j[r];
+            else
+                v = srad_new(j[r + 1], j[r], j[r + 2], from_west(0.0f, j[r + 1]),
+                             from_east(0.0f, j[r + 1]), c[r], c[r + 1], from_east(0.0f, c[r]),
+                             a.step);
+            if (mine && y0 + r < a.H) {
+                if constexpr (MODE != kSums)
+                    at<float>(a.out + (int64_t)(y0 + r) * a.pout, (uint32_t)x) = v;
+                if constexpr (MODE != kCoeff) {
+                    const double d = (double)v;
+                    s += d;
+                    s2 = __builtin_fma(d, d, s2);
+                }
+            }
+        }
+    }
+    if constexpr (MODE != kCoeff) write_sums(a, sh, lane, wave, s, s2);
+}
+
+namespace {
+
+// How an H x W image is cut into work items, one wave each: tiles of 61
+// columns, or the sweeps' strips of 256, by bh rows.  By H and W alone, so
+// that both forms, every pitch and every call on an image sum in one order.
+struct SradGeo {
+    bool tiles;
+    int bh;
+    int64_t nstrips, nitems, nblocks;
+};
+SradGeo srad_cut(int64_t H, int64_t W, bool tiles, int bh) {
+    const int64_t ow = tiles ? kTW : kSW;
+    SradGeo g{tiles, bh, (W + ow - 1) / ow, 0, 0};
+    g.nitems = g.nstrips * ((H + bh - 1) / bh);
+    g.nblocks = (g.nitems + 3) / 4;
+    return g;
+}
+SradGeo srad_geo(int64_t H, int64_t W) {
+    // A few columns: bands of 32 rows (the partial sums' buffer is sized for
+    // those).
+    if (W < 32) return srad_cut(H, W, false, kBH);
+    const int64_t px = H * W;
+    // Short tiles while the image is small: 2.2 Mpx (1500x1500) 9.7 us an
+    // iteration against the best band's 10.4, 4.2 Mpx (2048x2048) 13.1
+    // against 11.1.
+    if (px <= int64_t(3) << 20)
+        return srad_cut(H, W, true, px <= int64_t(1) << 17 ? 4 : px <= int64_t(3) << 19 ? 8 : 16);
+    // Planes that memory and not the chip bounds: 32 rows.
+    if (px >= int64_t(48) << 20) return srad_cut(H, W, false, 32);
+    // Else the band height that leaves the last round of workgroups fullest.
+    // Cost: rounds of 256 workgroups (one per CU) times the rows each walks
+    // (about 6 more than it writes), more where one or two waves per SIMD
+    // cannot hide each other's latency.  Per iteration, us, at 12 / 16 / 20 /
+    // 24 / 32 / 48 rows, the chosen one first by this cost marked *:
+    //   2048x2048  13.1  11.1* 12.4  13.8  15.7  21.3
+    //   3000x3001  25.5* 30.0  26.0  28.7  35.2  29.7
+    //   4000x4100  29.1  29.9  29.4  28.0* 33.2  34.0
+    //   4096x4096  28.7  26.5  29.9  28.5  27.4* 32.7
+    //   6000x6000  75.2  72.2  71.4  72.2  73.8  69.8*
+    //   8192x8192 141.0 126.5 126.9 124.2 116.4* 124.4 (memory)
+    SradGeo best{};
+    double least = 0.0;
+    for (int bh = 8; bh <= 48; bh += 4) {
+        const SradGeo g = srad_cut(H, W, false, bh);
+        const int64_t rounds = (g.nblocks + 255) / 256;
+        const double cost = (double)(rounds * (bh + 6)) *
+                            (rounds == 1 ? 1.25 : rounds == 2 ? 1.1 : 1.0);
+        if (!best.nitems || cost < least) {
+            best = g;
+            least = cost;
+        }
+    }
+    return best;
+}
+
+template <int MODE>
+void launch_kernel(const SradGeo& g, const SradArgs& a, hipStream_t s) {
+    const dim3 grid((unsigned)g.nblocks), block(256);
+    if (!g.tiles) hipLaunchKernelGGL(k_srad_sweep<MODE>, grid, block, 0, s, a);
+    else if (g.bh == 4) hipLaunchKernelGGL((k_srad_tile<MODE, 4>), grid, block, 0, s, a);
+    else if (g.bh == 8) hipLaunchKernelGGL((k_srad_tile<MODE, 8>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_srad_tile<MODE, 16>), grid, block, 0, s, a);
+}
+
+}  // namespace
+
 int64_t srad_blocks(int64_t H, int64_t W) {
-    const int64_t items = ((W + kSW - 1) / kSW) * ((H + kBH - 1) / kBH);
-    return (items + 3) / 4;
+    return srad_geo(H, W).nblocks;
 }
 
 hipError_t launch_srad(const float* J, float* Jb, int64_t pj, int64_t pb, float* cbuf,
                        int64_t pc, double* partials, double* q_log, int H, int W, int niter,
                        float lambda, bool fused, hipStream_t s) {
-    const int nstrips = (W + kSW - 1) / kSW;
-    const int nitems = nstrips * ((H + kBH - 1) / kBH);
-    const int nblocks = (nitems + 3) / 4;
+    const SradGeo g = srad_geo(H, W);
+    const int64_t nblocks = g.nblocks;
     auto aligned = [](const void* p, int64_t pitch) {
         return ((uintptr_t)p % 16 == 0) && (pitch % 4 == 0);
     };
     SradArgs a{};
     a.H = H;
     a.W = W;
-    a.nstrips = nstrips;
-    a.nitems = nitems;
-    a.nprev = nblocks;
+    a.nstrips = (int)g.nstrips;
+    a.nitems = (int)g.nitems;
+    a.nprev = (int)nblocks;
+    a.bh = g.bh;
     a.step = 0.25f * lambda;
     a.q_log = q_log;
     a.J = J;
     a.pin = pj;
     a.vin = aligned(J, pj);
     a.part = partials;
-    hipLaunchKernelGGL(k_srad_sweep<kSums>, dim3(nblocks), dim3(256), 0, s, a);
+    launch_kernel<kSums>(g, a, s);
     hipError_t e = hipGetLastError();
     const float* cur = J;
     int64_t pcur = pj;
@@ -474,19 +640,19 @@ hipError_t launch_srad(const float* J, float* Jb, int64_t pj, int64_t pb, float*
         a.J = cur;
         a.pin = pcur;
         a.vin = aligned(cur, pcur);
-        a.prev = partials + 2 * (int64_t)nblocks * (it % 2);
-        a.part = partials + 2 * (int64_t)nblocks * ((it + 1) % 2);
+        a.prev = partials + 2 * nblocks * (it % 2);
+        a.part = partials + 2 * nblocks * ((it + 1) % 2);
         if (fused) {
             a.out = nxt;
             a.pout = pnxt;
             a.vout = aligned(nxt, pnxt);
-            hipLaunchKernelGGL(k_srad_sweep<kFused>, dim3(nblocks), dim3(256), 0, s, a);
+            launch_kernel<kFused>(g, a, s);
         } else {
             SradArgs ac = a;
             ac.out = cbuf;
             ac.pout = pc;
             ac.vout = aligned(cbuf, pc);
-            hipLaunchKernelGGL(k_srad_sweep<kCoeff>, dim3(nblocks), dim3(256), 0, s, ac);
+            launch_kernel<kCoeff>(g, ac, s);
             SradArgs au = a;
             au.c = cbuf;
             au.pc = pc;
@@ -494,7 +660,7 @@ hipError_t launch_srad(const float* J, float* Jb, int64_t pj, int64_t pb, float*
             au.out = nxt;
             au.pout = pnxt;
             au.vout = aligned(nxt, pnxt);
-            hipLaunchKernelGGL(k_srad_sweep<kUpdate>, dim3(nblocks), dim3(256), 0, s, au);
+            launch_kernel<kUpdate>(g, au, s);
         }
         e = hipGetLastError();
         cur = nxt;

@@ -7,9 +7,9 @@
 namespace hx {
 
 // ---- SRAD ------------------------------------------------------------
-// Workgroups of one SRAD launch over an H x W image (4 sweep items of 256
-// columns x 32 rows each); the partial-sum buffer holds 4 doubles per
-// workgroup (two halves of one pair each).
+// Workgroups of one SRAD launch over an H x W image (4 waves, one work item
+// each); the partial-sum buffer holds 4 doubles per workgroup (two halves of
+// one pair each).
 int64_t srad_blocks(int64_t H, int64_t W);
 // niter iterations on J (pitch pj): iteration k reads one of J / Jb and
 // writes the other, starting from J (so an odd niter ends in Jb).  cbuf
