@@ -234,12 +234,14 @@ hx_status hx_pipeline_get_schedule(const hx_pipeline* p, int64_t height,
                                    int64_t width, hx_schedule* out);
 
 /* One image, the per-image form: a handful of kernel launches on `stream`.
- * d_max (device, nullable) receives M = max G as one float.  Per-image
- * calls share one set of the pipeline's scratch: a call on a different
- * stream from the previous per-image call (hx_edge_detect,
- * hx_edge_detect_stages, hx_srad) first makes its stream wait for that
- * call's work, so calls on several streams are correct but do not
- * overlap.  (SPECULATE per-image calls use the batch contexts instead.) */
+ * d_max (device, nullable) receives M = max G as one float.  The first
+ * stream that makes a STORE-form call (hx_edge_detect or
+ * hx_edge_detect_stages) has a set of the pipeline's scratch to itself.
+ * All other per-image calls (on other streams, in other forms, hx_srad)
+ * share one set: such a call on a different stream from the previous one
+ * first makes its stream wait for that call's work, so calls on several
+ * streams are correct but need not overlap.  (SPECULATE per-image calls use
+ * the batch contexts instead.) */
 hx_status hx_edge_detect(hx_pipeline* p, const hx_image* img, float* d_max,
                          hipStream_t stream);
 

@@ -315,17 +315,19 @@ static bool is_capturing(hipStream_t stream) {
 // The fused STORE form's threshold kernel zeroes the other slot (store), so
 // when the previous call left this one at zero it needs no clearing launch;
 // every other form clears both slots first.
-static hipError_t begin_slots(hx_pipeline* p, bool store, hipStream_t stream, uint32_t** slot,
-                              uint32_t** next) {
-    uint32_t* const slots = (uint32_t*)p->slot1.ptr;
-    *slot = slots + p->img_parity * kSlotWords;
-    *next = slots + (p->img_parity ^ 1) * kSlotWords;
-    p->img_parity ^= 1;
-    p->img_last_slot = *slot;
-    const bool slot_zero = p->img_next_zero;
-    p->img_next_zero = false;  // until this call's launches are all enqueued
-    if (store && slot_zero) return hipSuccess;
-    return launch_fill_u32(slots, 0u, 2 * kSlotWords, stream);
+static hipError_t begin_slots(hx_pipeline::ImgScratch& sc, bool store, hipStream_t stream,
+                              uint32_t** slot, uint32_t** next, bool* leaves_zero) {
+    *slot = sc.slots + sc.parity * kSlotWords;
+    *next = sc.slots + (sc.parity ^ 1) * kSlotWords;
+    sc.parity ^= 1;
+    const bool slot_zero = sc.next_zero;
+    sc.next_zero = false;  // until this call's launches are all enqueued
+    // A call recorded into a graph runs later, any number of times: it
+    // clears its slots itself and leaves nothing to the next call.
+    const bool recorded = is_capturing(stream);
+    *leaves_zero = !recorded;
+    if (store && slot_zero && !recorded) return hipSuccess;
+    return launch_fill_u32(sc.slots, 0u, 2 * kSlotWords, stream);
 }
 
 // The STORE form on the short sweep alone, for every blur size and with the
@@ -335,12 +337,14 @@ static hipError_t begin_slots(hx_pipeline* p, bool store, hipStream_t stream, ui
 // unfused kernels (blur 26), 24 in these three (blur 7.8).  The stage hook
 // on 1080x1920 k5: 78 us in five kernels and a copy of the planes, 25 here.
 static hx_status run_short(hx_pipeline* p, const hx_image* img, float* d_max,
-                           const StageOut* so, hipStream_t stream) {
+                           const StageOut* so, hx_pipeline::ImgScratch& scr,
+                           hipStream_t stream) {
     uint32_t *slot, *next;
-    HX_TRY(begin_slots(p, true, stream, &slot, &next));
+    bool leaves_zero;
+    HX_TRY(begin_slots(scr, true, stream, &slot, &next, &leaves_zero));
     ImgArgs a = base_args(img, slot, d_max);
     a.ways = kSlotWays;
-    a.fout = (float*)p->planeA.ptr;
+    a.fout = scr.code;
     int ks = p->prm.ksize;
     Taps t = p->taps;
     if (ks > 7) {
@@ -348,10 +352,11 @@ static hx_status run_short(hx_pipeline* p, const hx_image* img, float* d_max,
         // registers go to.  16 rows, 8 while the image has few tiles (700^2
         // k15 7.0 against 6.8 us, 256^2 k9 4.2 against 4.9).
         const int th = img->height * img->width <= (int64_t(1) << 18) ? 8 : 16;
+        a.fout = scr.blur;
         HX_TRY(launch_tile(TM_BLUR, ks, 1, th, a, t, StageOut{}, stream));
-        a.src = a.fout;
+        a.src = scr.blur;
         a.sp = a.op;
-        a.fout = (float*)p->planeL.ptr;
+        a.fout = scr.code;
         ks = 1;
         t = Taps{};
         t.g[0] = 1.0f;
@@ -360,7 +365,7 @@ static hx_status run_short(hx_pipeline* p, const hx_image* img, float* d_max,
     HX_TRY(launch_tile(so ? (int)TM_STAGES : (int)SM_STORE, ks, sc.tile_w / 64, sc.tile_h, a, t,
                        so ? *so : StageOut{}, stream));
     HX_TRY(launch_threshold_code(a, p->prm.thresh_frac, stream, next));
-    p->img_next_zero = true;
+    scr.next_zero = leaves_zero;
     return HX_OK;
 }
 
@@ -372,8 +377,9 @@ static bool takes_short_form(const hx_pipeline* p, const hx_image* img, const hx
            s.reduce_mode == HX_REDUCE_TREE && img->width < (int64_t(1) << 28);
 }
 
-hx_status run_image(hx_pipeline* p, const hx_image* img, float* d_max,
-                    const hx_schedule& s, hipStream_t stream) {
+static hx_status run_image(hx_pipeline* p, const hx_image* img, float* d_max,
+                           const hx_schedule& s, hx_pipeline::ImgScratch& scr,
+                           hipStream_t stream) {
     // SPECULATE runs the batch kernels on a batch of one.
     if (s.fusion_depth == 4 && s.pass_mode == HX_PASS_SPECULATE)
         return run_batched(p, img, 1, d_max, HX_PASS_SPECULATE, s.tile_h, stream);
@@ -389,16 +395,18 @@ hx_status run_image(hx_pipeline* p, const hx_image* img, float* d_max,
                     (long long)plane_need(img->height, img->width), (long long)p->plane_elems);
     const bool store_fused = s.fusion_depth == 4 && s.pass_mode == HX_PASS_STORE;
     if (s.fusion_depth == 1 && takes_short_form(p, img, s))
-        return run_short(p, img, d_max, nullptr, stream);
+        return run_short(p, img, d_max, nullptr, scr, stream);
     uint32_t *slot, *next;
-    HX_TRY(begin_slots(p, store_fused, stream, &slot, &next));
+    bool leaves_zero;
+    HX_TRY(begin_slots(scr, store_fused, stream, &slot, &next, &leaves_zero));
+    p->img_last_slot = slot;
     ImgArgs a = base_args(img, slot, d_max);
     const float theta = p->prm.thresh_frac;
     const int ks = p->prm.ksize;
     if (s.fusion_depth == 4) {
         const int c = s.tile_w / 64;
         if (s.pass_mode == HX_PASS_STORE) {
-            a.fout = (float*)p->planeA.ptr;
+            a.fout = scr.code;
             a.ways = kSlotWays;
             HX_TRY(launch_store(ks, c, s.tile_h, a, p->taps, theta, stream));
             HX_TRY(launch_threshold_code(a, theta, stream, next));
@@ -407,7 +415,7 @@ hx_status run_image(hx_pipeline* p, const hx_image* img, float* d_max,
             HX_TRY(launch_sweep(SM_MASK, ks, c, s.tile_h, a, p->taps, theta, stream));
             if (d_max) HX_TRY(launch_write_max(a, stream));
         }
-        p->img_next_zero = true;
+        scr.next_zero = leaves_zero;
         return HX_OK;
     }
     StageBufs b{};
@@ -430,7 +438,7 @@ hx_status run_image(hx_pipeline* p, const hx_image* img, float* d_max,
             HX_TRY(launch_zero_cross(a, b, b.L, tw1, th1, stream));
         }
         HX_TRY(launch_threshold_zg(a, b, theta, tw1, th1, stream));
-        p->img_next_zero = true;
+        scr.next_zero = leaves_zero;
         return HX_OK;
     }
     // Depth 1: one kernel per stage.
@@ -439,7 +447,7 @@ hx_status run_image(hx_pipeline* p, const hx_image* img, float* d_max,
     HX_TRY(launch_zero_cross(a, b, b.L, s.tile_w, s.tile_h, stream));
     HX_TRY(launch_sobel_max(a, b, s.tile_w, s.tile_h, s.reduce_mode, stream));
     HX_TRY(launch_threshold_zg(a, b, theta, s.tile_w, s.tile_h, stream));
-    p->img_next_zero = true;
+    scr.next_zero = leaves_zero;
     return HX_OK;
 }
 
@@ -458,13 +466,29 @@ static hx_status img_order_end(hx_pipeline* p, hipStream_t stream) {
     return HX_OK;
 }
 
+// Does the stream own the pipeline's private STORE scratch?  The first
+// stream to ask does, for the pipeline's life.  (hipStreamPerThread names
+// another stream in every thread.)
+static bool owns_scratch(hx_pipeline* p, hipStream_t stream) {
+    if (!p->img_own.code || stream == hipStreamPerThread) return false;
+    if (!p->own_taken) {
+        p->own_taken = true;
+        p->own_stream = stream;
+    }
+    return p->own_stream == stream;
+}
+
 hx_status run_image_ordered(hx_pipeline* p, const hx_image* img, float* d_max,
-                            const hx_schedule& s, hipStream_t stream) {
+                            const hx_schedule& s, hipStream_t stream, bool may_own) {
     if (s.fusion_depth == 4 && s.pass_mode == HX_PASS_SPECULATE)
-        return run_image(p, img, d_max, s, stream);
+        return run_image(p, img, d_max, s, p->img_shared, stream);
+    const bool store = s.fusion_depth == 4 ? s.pass_mode == HX_PASS_STORE
+                                           : s.fusion_depth == 1 && takes_short_form(p, img, s);
+    if (may_own && store && owns_scratch(p, stream))
+        return run_image(p, img, d_max, s, p->img_own, stream);
     hx_status st = img_order_begin(p, stream);
     if (st != HX_OK) return st;
-    st = run_image(p, img, d_max, s, stream);
+    st = run_image(p, img, d_max, s, p->img_shared, stream);
     hx_status st2 = img_order_end(p, stream);
     return st != HX_OK ? st : st2;
 }
@@ -898,10 +922,23 @@ static hx_status alloc_scratch(hx_pipeline* p) {
     p->plane_elems = plane_capacity(p->prm.max_pixels);
     const size_t pe = (size_t)p->plane_elems;
     HX_TRY(hipEventCreateWithFlags(&p->img_ev, hipEventDisableTiming));
-    HX_TRY(p->slot1.alloc(2 * kSlotWords * sizeof(uint32_t), m));
+    HX_TRY(p->slot1.alloc(4 * kSlotWords * sizeof(uint32_t), m));
     if (f & (HX_FORM_IMAGE | HX_FORM_STAGES | HX_FORM_SRAD))
         HX_TRY(p->planeA.alloc(pe * sizeof(float), m));
     if (f & (HX_FORM_STAGES | HX_FORM_SRAD)) HX_TRY(p->planeL.alloc(pe * sizeof(float), m));
+    // The private STORE scratch: of the per-image form, and for blur sizes
+    // without fused sweeps of the stage kernels' form.
+    const bool wide = p->prm.ksize > 7;
+    if (fused_ks(p->prm.ksize) ? (f & (HX_FORM_IMAGE | HX_FORM_STAGES)) : (f & HX_FORM_STAGES)) {
+        HX_TRY(p->planeOwn.alloc(pe * sizeof(float), m));
+        if (wide) HX_TRY(p->planeOwnB.alloc(pe * sizeof(float), m));
+    }
+    p->img_shared.slots = (uint32_t*)p->slot1.ptr;
+    p->img_shared.code = (float*)(wide ? p->planeL.ptr : p->planeA.ptr);
+    p->img_shared.blur = (float*)p->planeA.ptr;
+    p->img_own.slots = p->img_shared.slots + 2 * kSlotWords;
+    p->img_own.code = (float*)p->planeOwn.ptr;
+    p->img_own.blur = (float*)p->planeOwnB.ptr;
     if (f & HX_FORM_STAGES) {
         HX_TRY(p->planeG2.alloc(pe * sizeof(float), m));
         HX_TRY(p->planeZ.alloc(pe, m));
@@ -1014,6 +1051,8 @@ void hx_pipeline_destroy(hx_pipeline* p) {
     p->slot1.release();
     p->planeA.release();
     p->planeL.release();
+    p->planeOwn.release();
+    p->planeOwnB.release();
     p->planeG2.release();
     p->planeZ.release();
     p->bufPart.release();
@@ -1197,16 +1236,20 @@ hx_status hx_edge_detect_stages(hx_pipeline* p, const hx_image* img, float* d_B,
     if (s.fusion_depth == 3 && d_B)
         return fail(HX_E_UNSUPPORTED, "fusion depth 3 keeps B on chip: pass d_B = NULL");
     const bool as_asked = p->forced && p->forced_sched.fusion_depth <= 3;
+    const bool sweep = !as_asked && has_form(p, HX_FORM_STAGES) &&
+                       img->width < (int64_t(1) << 28) &&
+                       plane_need(img->height, img->width) <= p->plane_elems;
+    const StageOut so{d_B, d_L, d_G, d_Z};
+    if (sweep && owns_scratch(p, stream))
+        return run_short(p, img, d_max, &so, p->img_own, stream);
     st = img_order_begin(p, stream);
     if (st != HX_OK) return st;
-    if (!as_asked && has_form(p, HX_FORM_STAGES) && img->width < (int64_t(1) << 28) &&
-        plane_need(img->height, img->width) <= p->plane_elems) {
-        const StageOut so{d_B, d_L, d_G, d_Z};
-        st = run_short(p, img, d_max, &so, stream);
+    if (sweep) {
+        st = run_short(p, img, d_max, &so, p->img_shared, stream);
         hx_status st2 = img_order_end(p, stream);
         return st != HX_OK ? st : st2;
     }
-    st = run_image(p, img, d_max, s, stream);
+    st = run_image(p, img, d_max, s, p->img_shared, stream);
     if (st == HX_OK) {
         ImgArgs a = base_args(img, p->img_last_slot, d_max);
         StageBufs b{};

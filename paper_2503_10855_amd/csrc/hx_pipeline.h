@@ -151,17 +151,32 @@ struct hx_pipeline {
     hx::DevBuf planeL;   // L / SRAD's c plane
     hx::DevBuf planeG2, planeZ, bufPart;
     hx::DevBuf srad_part;
-    // Ordering of per-image calls: each records img_ev on its stream; a
-    // call on another stream waits for it first.
+    // Ordering of per-image calls on the shared scratch: each records img_ev
+    // on its stream; a call on another stream waits for it first.
     hipEvent_t img_ev = nullptr;
     hipStream_t img_stream = nullptr;
     bool img_used = false;
-    // The per-image max slots: slot1 holds two; each call uses one and
-    // leaves the other at zero for the next call (img_next_zero says the
-    // previous call did).  img_last_slot: the slot of the last call.
-    int img_parity = 0;
-    bool img_next_zero = false;
-    uint32_t* img_last_slot = nullptr;
+    // Scratch of the STORE forms: two max slots (each call uses one and
+    // leaves the other at zero for the next call; next_zero says the
+    // previous call did) and the code plane, and for blur sizes above 7 the
+    // plane of B.
+    struct ImgScratch {
+        uint32_t* slots = nullptr;
+        int parity = 0;
+        bool next_zero = false;
+        float* code = nullptr;
+        float* blur = nullptr;
+    };
+    ImgScratch img_shared;
+    uint32_t* img_last_slot = nullptr;   // of the last call on img_shared
+    // A set of its own for STORE-form calls on one stream, the first that
+    // makes one: no other stream's call ever uses it, so its calls are
+    // ordered by their stream alone and record no event (one costs about 3
+    // of the 17 us of a 1080p call).
+    ImgScratch img_own;
+    hx::DevBuf planeOwn, planeOwnB;
+    hipStream_t own_stream = nullptr;
+    bool own_taken = false;
 
     // Batched launches.
     static constexpr int kMaxContexts = 8;
@@ -184,12 +199,10 @@ hx_status validate_schedule(const hx_pipeline* p, const hx_schedule& s);
 hx_status validate_image(const hx_pipeline* p, const hx_image* img);
 
 // The per-image form with an explicit schedule (used by hx_edge_detect
-// and the autotuner).
-hx_status run_image(hx_pipeline* p, const hx_image* img, float* d_max,
-                    const hx_schedule& s, hipStream_t stream);
-// run_image ordered after the previous per-image call (see img_ev).
+// and the autotuner): on the private scratch if the stream owns it (may_own:
+// or takes it), else on the shared one after the previous call there.
 hx_status run_image_ordered(hx_pipeline* p, const hx_image* img, float* d_max,
-                            const hx_schedule& s, hipStream_t stream);
+                            const hx_schedule& s, hipStream_t stream, bool may_own = true);
 // Pass structure of batched calls unless one is fixed: SPECULATE reads
 // the input about 1.1 times (once, plus the sampled bands) and measured
 // fastest on the 64 x 1920x1080 batch (0.30 ms per step against 0.36 ms

@@ -159,12 +159,12 @@ hx_status hx_autotune(hx_pipeline* p, int64_t height, int64_t width, const char*
     for (const hx_schedule& c : candidates(p->prm.ksize)) {
         if (validate_schedule(p, c) != HX_OK) continue;
         // One warm-up call (allocates scratch), then the fastest of three.
-        st = run_image_ordered(p, &im, nullptr, c, s);
+        st = run_image_ordered(p, &im, nullptr, c, s, false);
         if (st != HX_OK) break;
         float ms_min = 1e30f;
         for (int r = 0; r < 3 && st == HX_OK; ++r) {
             e = hipEventRecord(e0, s);
-            if (e == hipSuccess) st = run_image_ordered(p, &im, nullptr, c, s);
+            if (e == hipSuccess) st = run_image_ordered(p, &im, nullptr, c, s, false);
             if (e == hipSuccess && st == HX_OK) e = hipEventRecord(e1, s);
             if (e == hipSuccess && st == HX_OK) e = hipEventSynchronize(e1);
             float ms = 0.0f;

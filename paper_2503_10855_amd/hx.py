@@ -137,23 +137,30 @@ def raw():
     return _lib
 
 
+# The current stream's handle without building a Stream object around it
+# (1.5 us of a small image's 15 us call).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream):
     if stream is None:
+        if _raw_stream is not None:
+            return _raw_stream(torch.cuda.current_device())
         stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    return stream.cuda_stream
 
 
 def image_desc(src: torch.Tensor, mask: torch.Tensor) -> Image:
-    if src.dtype != torch.float32 or src.dim() != 2 or src.stride(1) != 1:
+    ss, ms, shape = src.stride(), mask.stride(), src.shape
+    if src.dtype != torch.float32 or len(ss) != 2 or ss[1] != 1:
         raise TypeError("src must be a 2-D float32 tensor with unit column stride")
-    if mask.dtype != torch.uint8 or mask.dim() != 2 or mask.stride(1) != 1:
+    if mask.dtype != torch.uint8 or len(ms) != 2 or ms[1] != 1:
         raise TypeError("mask must be a 2-D uint8 tensor with unit column stride")
-    if tuple(mask.shape) != tuple(src.shape):
+    if mask.shape != shape:
         raise ValueError("mask and src shapes differ")
     if not (src.is_cuda and mask.is_cuda):
         raise ValueError("src and mask must be device tensors")
-    H, W = src.shape
-    return Image(src.data_ptr(), H, W, src.stride(0), mask.data_ptr(), mask.stride(0))
+    return Image(src.data_ptr(), shape[0], shape[1], ss[0], mask.data_ptr(), ms[0])
 
 
 def compile_schedule(text):

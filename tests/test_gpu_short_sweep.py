@@ -159,3 +159,45 @@ def test_stage_planes_and_masks_match_depth_one(hx, ks):
                 assert torch.equal(got[k], ref[k]), (k, h, w)
                 assert k not in some or torch.equal(some[k], ref[k]), (k, h, w)
             assert torch.equal(m, r) and dm[0] == dm[1]
+
+
+def test_two_streams_and_replays_keep_their_maxima(hx):
+    """Calls alternating between two streams with nothing between them (one
+    owns the private scratch), and a captured call replayed between eager
+    ones on images with smaller and larger maxima: every maximum and mask is
+    the image's own."""
+    imgs = [synth.image(300, 500, 306, i) * np.float32(s) for i, s in
+            enumerate((1.0, 0.25, 3.0, 0.5, 2.0, 0.1))]
+    srcs = [torch.from_numpy(x).cuda() for x in imgs]
+    n = len(srcs)
+    with hx.Pipeline(theta=THETA, max_pixels=1 << 18, max_images=n) as p:
+        p.set_schedule(256, 64, 4, hx.PASS_RECOMPUTE)
+        want_m = torch.zeros(n, device="cuda")
+        want = [p.edge_detect(s, dmax=want_m[i:i + 1]) for i, s in enumerate(srcs)]
+        p.set_schedule()
+        p.sync()
+        streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+        for rep in range(3):
+            got_m = torch.zeros(n, device="cuda")
+            got = [torch.full_like(w, 7) for w in want]
+            torch.cuda.synchronize()
+            print(f"two streams, repeat {rep}", flush=True)
+            for i in range(n):
+                p.edge_detect(srcs[i], got[i], dmax=got_m[i:i + 1], stream=streams[i % 2])
+            torch.cuda.synchronize()
+            assert torch.equal(got_m, want_m)
+            assert all(torch.equal(a, b) for a, b in zip(got, want))
+        x, mask, m = srcs[0].clone(), torch.zeros_like(want[0]), torch.zeros(1, device="cuda")
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            p.edge_detect(x, mask, dmax=m)
+        em = torch.zeros(1, device="cuda")
+        for i in (2, 1, 3, 5, 4, 0):
+            x.copy_(srcs[i])
+            print(f"replay on image {i}", flush=True)
+            g.replay()
+            torch.cuda.synchronize()
+            assert m[0] == want_m[i] and torch.equal(mask, want[i])
+            e = p.edge_detect(srcs[(i + 1) % n], dmax=em, stream=streams[i % 2])
+            torch.cuda.synchronize()
+            assert em[0] == want_m[(i + 1) % n] and torch.equal(e, want[(i + 1) % n])
