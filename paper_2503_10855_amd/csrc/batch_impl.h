@@ -278,6 +278,58 @@ void k_batch_p2(const uint8_t* __restrict__ table, Taps tp) {
     }
 }
 
+// The form of small batches (kPassShort): the maxima of all tiles, then the
+// masks against them, in two launches of the short sweep on 8-row tiles.  A
+// small batch is bound by its launches and by what one wave takes for its
+// tile, so a third launch, and pass 1's wider tiles with their lists, cost
+// more than the second blur.  Whole calls, us, this form and SPECULATE: 16
+// images of 64..256 k3 14.5 and 24.4, 4 x 512x512 k5 17.1 and 28.0,
+// 1080x1920 k5 18.6 and 25.4, 2 of them 25.0 and 28.8, 3 of them 30.8 and
+// 32.0, 4 of them 39.8 and 33.8.  Each tile's arguments come from the launch
+// where they can, which saves a chain of loads through the table's header.
+template <int KS, int C>
+__global__ __launch_bounds__(64) void k_batch_short_max(ShortArgs s, Taps tp) {
+    using S = TileShape<KS, C, SM_MAXONLY>;
+    constexpr int OW = TileShape<KS, C, SM_MASK>::OW;
+    static_assert(S::OW >= OW, "the mask's tiles cover the image");
+    __shared__ __align__(16) float rows[S::lds_floats(kShortBatchRows)];
+    const int k = xcd_remap(blockIdx.x, gridDim.x);
+    const BatchItem it = s.items ? s.items[k] : BatchItem{0, k};
+    const ImgArgs a = s.imgs[it.image];
+    const int nstrips = (a.W + OW - 1) / OW;
+    const int x0 = (it.local % nstrips) * OW, y0 = (it.local / nstrips) * kShortBatchRows;
+    lds_float* lds = (lds_float*)rows;
+    tile_load<C>(a, x0 - S::HL, y0 - S::HY, min(kShortBatchRows, a.H - y0) + 2 * S::HY, lds);
+    tile_loads_done();
+    float gmax = 0.0f;
+    tile_sweep<KS, C, SM_MAXONLY>(a, tp, x0, y0, kShortBatchRows, 0.0f, gmax, lds);
+    gmax = wave_max(gmax);
+    if (lane_id() == 0) atomic_max_g2(slot_word(a, k) + s.set, gmax);
+}
+
+template <int KS, int C>
+__global__ __launch_bounds__(64) void k_batch_short_mask(ShortArgs s, Taps tp) {
+    using S = TileShape<KS, C, SM_MASK>;
+    __shared__ __align__(16) float rows[S::lds_floats(kShortBatchRows)];
+    const int k = xcd_remap(blockIdx.x, gridDim.x);
+    const BatchItem it = s.items ? s.items[k] : BatchItem{0, k};
+    ImgArgs a = s.imgs[it.image];
+    const int nstrips = (a.W + S::OW - 1) / S::OW;
+    const int x0 = (it.local % nstrips) * S::OW, y0 = (it.local / nstrips) * kShortBatchRows;
+    lds_float* lds = (lds_float*)rows;
+    tile_load<C>(a, x0 - S::HL, y0 - S::HY, min(kShortBatchRows, a.H - y0) + 2 * S::HY, lds);
+    a.slot += s.set;
+    const uint32_t m2 = slot_max(a);
+    if (it.local == 0 && lane_id() == 0 && a.dmax) *as_global(a.dmax) = max_from(m2);
+    // The next call's words.
+    for (int w = blockIdx.x * 64 + lane_id(); w < s.nzero; w += gridDim.x * 64)
+        as_global(s.other)[(int64_t)w * a.slot_step] = 0u;
+    tile_loads_done();
+    float unused = 0.0f;
+    tile_sweep<KS, C, SM_MASK>(a, tp, x0, y0, kShortBatchRows, thr2_from(m2, s.theta), unused,
+                               lds);
+}
+
 // Tiles whose lists one workgroup of SPECULATE's pass 2 takes, at most, and
 // the columns per lane of the pieces it redoes queued tiles in (8 rows
 // each; four waves' rows are 32 KB of LDS at k = 5, five workgroups per CU).

@@ -14,10 +14,16 @@
 namespace hx {
 
 // The kernel of (pass structure, phase); short_tile: SPECULATE's pass 1 on
-// tiles of up to kShortTile rows.  nullptr: not in this part.
+// tiles of up to kShortTile rows, kPassShort's one-column tiles.  nullptr:
+// not in this part.
 const void* HX_CAT(batch_kernel_k, HX_KS, _p, HX_PART)(int pass, int phase, bool short_tile) {
     (void)pass, (void)phase, (void)short_tile;
 #if HX_PART == 0
+    if (pass == kPassShort)
+        return phase == 1 ? (short_tile ? (const void*)k_batch_short_max<HX_KS, 1>
+                                        : (const void*)k_batch_short_max<HX_KS, 2>)
+                          : (short_tile ? (const void*)k_batch_short_mask<HX_KS, 1>
+                                        : (const void*)k_batch_short_mask<HX_KS, 2>);
     if (pass == HX_PASS_SPECULATE) {
         if (phase == 0) return (const void*)k_batch_p0<HX_KS>;
         if (phase == 1 && short_tile) return (const void*)k_batch_p1t<HX_KS>;

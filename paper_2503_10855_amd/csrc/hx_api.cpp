@@ -501,13 +501,14 @@ static hx_status ctx_init(hx_pipeline* p, BatchContext& c) {
     MemStats& m = p->mem;
     const BatchCaps& k = p->caps;
     const int64_t n = p->prm.max_images;
-    // One buffer: bounds (8 B each), the epoch and the redo queue's length,
-    // cleared once here; then the max slots, the list counts, the redo queue.
+    // One buffer: bounds (8 B each), the epoch, the redo queue's length and
+    // the max slots, cleared once here; the list counts, the redo queue.
     const int64_t words = 2 * k.ways * k.slot_step + 2 * kSlotStep;
-    HX_TRY(c.state.alloc(sizeof(uint32_t) * (words + k.ways * k.slot_step + 2 * k.items1), m));
-    HX_TRY(hipMemset(c.state.ptr, 0, sizeof(uint32_t) * words));
+    const int64_t slots = 2 * k.ways * k.slot_step;   // two sets
+    HX_TRY(c.state.alloc(sizeof(uint32_t) * (words + slots + 2 * k.items1), m));
+    HX_TRY(hipMemset(c.state.ptr, 0, sizeof(uint32_t) * (words + slots)));
     c.slots = (uint32_t*)c.state.ptr + words;
-    c.cand_n = c.slots + k.ways * k.slot_step;
+    c.cand_n = c.slots + slots;
     c.redo = (int32_t*)(c.cand_n + k.items1);
     HX_TRY(c.table.alloc(k.table_bytes, m));
     HX_TRY(c.h_table.alloc(k.table_bytes, m));
@@ -572,7 +573,7 @@ static ImgWork img_work(const hx_image& im, int pass, const SweepGeom& geo) {
     ImgWork w;
     w.tiles = geo.tiles(im.height, im.width);
     const int64_t rb = batch_p2_rows(im.width);
-    w.p2 = pass == HX_PASS_STORE ? (im.height + rb - 1) / rb : w.tiles;
+    w.p2 = pass == HX_PASS_STORE ? (im.height + rb - 1) / rb : pass == kPassShort ? 0 : w.tiles;
     w.p0 = pass == HX_PASS_SPECULATE ? batch_sample_items(geo.ks, im.height, im.width) : 0;
     w.code = pass == HX_PASS_STORE ? plane_need(im.height, im.width) : 0;
     return w;
@@ -659,6 +660,7 @@ static hx_status build_table(hx_pipeline* p, BatchContext& c, const hx_image* im
             list_off += (int64_t)cap * w[i].tiles;
         }
     }
+    c.n_ways = way0;
     if (list_off > p->caps.list_entries)
         return fail(HX_E_INVALID, "listing capacity exceeded");  // cannot happen: shares sum to it
     BatchItem* it = (BatchItem*)(ia + n);
@@ -678,6 +680,7 @@ static hx_status build_table(hx_pipeline* p, BatchContext& c, const hx_image* im
     c.last_dmax = d_max;
     c.last_pass = pass;
     c.last_ty = geo.ty;
+    c.last_c = geo.c;
     return HX_OK;
 }
 
@@ -687,11 +690,36 @@ static hx_status build_table(hx_pipeline* p, BatchContext& c, const hx_image* im
 static hx_status run_oversized(hx_pipeline* p, BatchContext& c, const hx_image& im,
                                float* d_max, hipStream_t stream) {
     ImgArgs a = base_args(&im, c.slots, d_max);
+    c.dirty[0] = std::max(c.dirty[0], 1);
     const int ks = p->prm.ksize, cw = batch_sweep_c(), ty = batch_sweep_ty();
     HX_TRY(launch_fill_u32(a.slot, 0u, 1, stream));
     HX_TRY(launch_sweep(SM_MAXONLY, ks, cw, ty, a, p->taps, p->prm.thresh_frac, stream));
     HX_TRY(launch_sweep(SM_MASK, ks, cw, ty, a, p->taps, p->prm.thresh_frac, stream));
     if (d_max) HX_TRY(launch_write_max(a, stream));
+    return HX_OK;
+}
+
+// The two launches of a small batch.  They use whichever set of the
+// context's max slots is known to be zero and leave the other one zero.
+static hx_status enqueue_short(hx_pipeline* p, BatchContext& c, hipStream_t stream) {
+    int set = c.dirty[0] == 0 ? 0 : 1;
+    const int64_t words = p->caps.ways * p->caps.slot_step;   // of one set
+    if (c.dirty[set] != 0) {
+        HX_TRY(launch_fill_u32(c.slots + set * words, 0u, words, stream));
+        c.dirty[set] = 0;
+    }
+    const int n_images = (int)c.last_imgs.size();
+    ShortArgs s{};
+    s.imgs = (const ImgArgs*)((const uint8_t*)c.table.ptr + sizeof(BatchHeader));
+    s.items = n_images > 1 ? (const BatchItem*)(s.imgs + n_images) : nullptr;
+    s.n = (int32_t)c.n_items[1];
+    s.set = set * words;
+    s.other = c.slots + (1 - set) * words;
+    s.nzero = c.dirty[1 - set];
+    s.theta = p->prm.thresh_frac;
+    c.dirty[set] = c.n_ways;
+    HX_TRY(launch_batch_short(p->prm.ksize, c.last_c, s, p->taps, stream));
+    c.dirty[1 - set] = 0;
     return HX_OK;
 }
 
@@ -706,6 +734,8 @@ static hx_status launch_on(hx_pipeline* p, BatchContext& c, const hx_image* imgs
         if (st != HX_OK) return st;
     }
     TraceRange tr("hx.batch.enqueue");
+    if (pass == kPassShort) return enqueue_short(p, c, stream);
+    c.dirty[0] = std::max(c.dirty[0], c.n_ways);
     // The three kernels are launched one by one, also for a repeated batch:
     // replaying them as a captured graph cost 6 to 8 us more per call (16
     // thumbnails 28.5 against 21.2 us, 2 x 1080p 36.1 against 28.9).
@@ -729,6 +759,13 @@ BatchKey batch_key(const hx_image* imgs, int32_t n) {
     return BatchKey{lg(px), lg(n)};
 }
 
+// Batches of up to this many pixels run in two launches on short tiles
+// (k_batch_short_max has the figures), of one column per lane up to
+// kNarrowPixels: 16 images of 64..256 14.5 us a call with one, 15.2 with two;
+// 1 Mpx 17.1 and 17.5, 2.9 Mpx 33.8 and 19.3.
+constexpr int64_t kShortBatchPixels = int64_t(6) << 20;
+constexpr int64_t kNarrowPixels = int64_t(1) << 19;
+
 hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
                       float* d_max, int pass, int ty, hipStream_t stream, int ctx) {
     const int ks = p->prm.ksize;
@@ -747,8 +784,15 @@ hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
                 pass = it->second.pass;
         }
     }
+    // Nothing asked for or tuned: by the batch's size.
+    const bool by_size = !pass && !ty && ctx < 0;
+    int64_t px = 0;
+    for (int i = 0; i < n && by_size && px <= kShortBatchPixels; ++i)
+        px += imgs[i].height * imgs[i].width;
+    if (by_size && px <= kShortBatchPixels && !p->timing && !is_capturing(stream))
+        pass = kPassShort;
     if (!pass) pass = kBatchPass;
-    if (pass < HX_PASS_STORE || pass > HX_PASS_SPECULATE)
+    if (pass < HX_PASS_STORE || pass > kPassShort)
         return fail(HX_E_INVALID, "pass_mode %d unknown", pass);
     std::unique_lock<std::mutex> lk(p->batch_mu);
     // Which context: one that already holds this batch (its table is reused
@@ -780,11 +824,15 @@ hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
     if (ctx >= 0) pick = p->n_ctx > 0 ? ctx % p->n_ctx : -1;
     const bool same = pick >= 0 && holds(p->ctx[pick]);
     if (same) ty = p->ctx[pick].last_ty;
-    if (!ty) ty = pass == HX_PASS_SPECULATE ? spec_default_ty(ks, imgs, n) : batch_sweep_ty();
-    if (ty < kBatchTyMin || ty > kBatchTyMax || ty % 8 != 0)
-        return fail(HX_E_INVALID, "batch tile height %d not a multiple of 8 in %d..%d", ty,
-                    kBatchTyMin, kBatchTyMax);
-    const SweepGeom geo{ks, batch_sweep_c(), ty};
+    SweepGeom geo{ks, px <= kNarrowPixels ? 1 : 2, kShortBatchRows};
+    if (pass != kPassShort) {
+        if (!ty)
+            ty = pass == HX_PASS_SPECULATE ? spec_default_ty(ks, imgs, n) : batch_sweep_ty();
+        if (ty < kBatchTyMin || ty > kBatchTyMax || ty % 8 != 0)
+            return fail(HX_E_INVALID, "batch tile height %d not a multiple of 8 in %d..%d", ty,
+                        kBatchTyMin, kBatchTyMax);
+        geo = SweepGeom{ks, batch_sweep_c(), ty};
+    }
     if (!has_form(p, HX_FORM_BATCH))
         return fail(HX_E_UNSUPPORTED, "the pipeline was created without HX_FORM_BATCH scratch");
     if (pass == HX_PASS_STORE && !has_form(p, HX_FORM_BATCH_STORE))
@@ -811,12 +859,25 @@ hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
         tot.p0 += w.p0;
         tot.code += w.code;
     }
-    static const char* const kPassName[] = {"auto", "STORE", "RECOMPUTE", "SPECULATE"};
+    if (pass == kPassShort && !fits(p->caps, tot, pass)) {
+        // Images so thin that their tiles exceed the table: in groups.
+        pass = kBatchPass;
+        ty = spec_default_ty(ks, imgs, n);
+        geo = SweepGeom{ks, batch_sweep_c(), ty};
+        tot = ImgWork{};
+        for (int i = 0; i < n; ++i) {
+            const ImgWork w = img_work(imgs[i], pass, geo);
+            tot.tiles += w.tiles;
+            tot.p2 += w.p2;
+            tot.p0 += w.p0;
+        }
+    }
+    static const char* const kPassName[] = {"auto", "STORE", "RECOMPUTE", "SPECULATE", "short"};
     if (log_level() >= 1) {
         int64_t px = 0;
         for (int i = 0; i < n; ++i) px += imgs[i].height * imgs[i].width;
         logf(1, "batched call: %d images, %lld px, %s, %d-row tiles (%s), context %d%s", n,
-             (long long)px, kPassName[pass], ty, ty_from, pick,
+             (long long)px, kPassName[pass], geo.ty, ty_from, pick,
              fits(p->caps, tot, pass) ? "" : ", split into groups");
     }
     if (fits(p->caps, tot, pass)) {

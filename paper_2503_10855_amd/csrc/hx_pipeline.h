@@ -95,13 +95,17 @@ struct BatchContext {
     hipEvent_t ev_t[5] = {};    // timing mode
     bool in_flight = false;
     uint64_t last_use = 0;      // the pipeline's call counter at the last use
+    // Leading words of each set of max slots that a call may have left
+    // non-zero, and those the table's images use.
+    int32_t dirty[2] = {0, 0};
+    int32_t n_ways = 0;
     int64_t n_items[3] = {0, 0, 0};  // the table's items of pass 0, 1, 2
     // The call whose table the device copy holds: a repeat of the same
     // batch (same descriptors, outputs and pass mode) reuses it as is.
     std::vector<hx_image> last_imgs;
     float* last_dmax = nullptr;
     int last_pass = -1;
-    int last_ty = 0;
+    int last_ty = 0, last_c = 0;
     bool default_ty = false;   // last_ty was the default for these images
 };
 

@@ -55,6 +55,19 @@ static const void* batch_kernel_ptr(int ks, int pass, int phase, bool short_tile
     return k;
 }
 
+hipError_t launch_batch_short(int ks, int c, const ShortArgs& s, const Taps& t, hipStream_t stream) {
+    ShortArgs sc = s;
+    Taps tc = t;
+    void* args[] = {(void*)&sc, (void*)&tc};
+    for (int phase = 1; phase <= 2; ++phase) {
+        const void* k = batch_kernel_ptr(ks, kPassShort, phase, c == 1);
+        if (!k || s.n < 1 || (c != 1 && c != 2)) return hipErrorInvalidValue;
+        hipError_t e = hipLaunchKernel(k, dim3((unsigned)s.n), dim3(64), args, 0, stream);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 hipError_t launch_batch_phase(int ks, int pass_mode, int phase, int ty, int64_t items,
                               const void* d_table, const Taps& t, hipStream_t s) {
     const bool spec = pass_mode == HX_PASS_SPECULATE;

@@ -201,3 +201,30 @@ def test_two_streams_and_replays_keep_their_maxima(hx):
             e = p.edge_detect(srcs[(i + 1) % n], dmax=em, stream=streams[i % 2])
             torch.cuda.synchronize()
             assert em[0] == want_m[(i + 1) % n] and torch.equal(e, want[(i + 1) % n])
+
+
+@pytest.mark.parametrize("ks", [3, 5, 7])
+def test_small_batches_in_turn_on_one_context(hx, ks):
+    """Small batches of different sizes and contrasts one after another on
+    one context, mixed with SPECULATE and STORE calls: the two sets of max
+    slots are handed from call to call, and no call sees another's maximum."""
+    rng = np.random.default_rng(307 + ks)
+    with hx.Pipeline(ksize=ks, sigma=SIGMA[ks], theta=THETA, max_pixels=1 << 21, max_images=40,
+                     batch_contexts=1) as p:
+        for step, n in enumerate((3, 40, 1, 17, 2, 40, 5)):
+            srcs = []
+            for i in range(n):
+                h, w = (int(v) for v in rng.integers(1, 130 if n > 5 else 400, 2))
+                srcs.append(torch.from_numpy(synth.image(h, w, 307, 50 * step + i) * np.float32(
+                    10.0 ** rng.uniform(-3, 3))).cuda())
+            dm = torch.zeros(n, device="cuda")
+            print(f"k{ks} step {step}: {n} images", flush=True)
+            got = p.edge_detect_batched(srcs, dmax=dm)
+            rm = torch.zeros(n, device="cuda")
+            p.set_schedule(256, 64, 4, (hx.PASS_SPECULATE, hx.PASS_STORE)[step % 2])
+            ref = p.edge_detect_batched(srcs, dmax=rm)
+            p.set_schedule()
+            got2 = p.edge_detect_batched(srcs, got, dmax=dm)
+            p.sync()
+            assert torch.equal(dm, rm)
+            assert all(torch.equal(a, b) for a, b in zip(got2, ref))
