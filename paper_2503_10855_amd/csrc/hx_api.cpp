@@ -547,7 +547,7 @@ hx_status ctx_wait(BatchContext& c) {
 // (ev_t: 0 reset 1 pass-0 4 pass-1 2 pass-2 3).  Grids are sized to the
 // batch (measured faster than persistent workgroups striding over items).
 static hipError_t enqueue_phases(hx_pipeline* p, BatchContext& c, int pass, hipStream_t s,
-                                 bool timed = false) {
+                                 bool timed, hipEvent_t done) {
     const int ks = p->prm.ksize;
     hipError_t e = timed ? hipEventRecord(c.ev_t[0], s) : hipSuccess;
     if (e == hipSuccess && pass != HX_PASS_SPECULATE)
@@ -560,7 +560,8 @@ static hipError_t enqueue_phases(hx_pipeline* p, BatchContext& c, int pass, hipS
         e = launch_batch_phase(ks, pass, 1, c.last_ty, c.n_items[1], c.table.ptr, p->taps, s);
     if (e == hipSuccess && timed) e = hipEventRecord(c.ev_t[2], s);
     if (e == hipSuccess)
-        e = launch_batch_phase(ks, pass, 2, c.last_ty, c.n_items[2], c.table.ptr, p->taps, s);
+        e = launch_batch_phase(ks, pass, 2, c.last_ty, c.n_items[2], c.table.ptr, p->taps, s,
+                               done);
     if (e == hipSuccess && timed) e = hipEventRecord(c.ev_t[3], s);
     return e;
 }
@@ -701,7 +702,8 @@ static hx_status run_oversized(hx_pipeline* p, BatchContext& c, const hx_image& 
 
 // The two launches of a small batch.  They use whichever set of the
 // context's max slots is known to be zero and leave the other one zero.
-static hx_status enqueue_short(hx_pipeline* p, BatchContext& c, hipStream_t stream) {
+static hx_status enqueue_short(hx_pipeline* p, BatchContext& c, hipStream_t stream,
+                               hipEvent_t done) {
     int set = c.dirty[0] == 0 ? 0 : 1;
     const int64_t words = p->caps.ways * p->caps.slot_step;   // of one set
     if (c.dirty[set] != 0) {
@@ -718,7 +720,7 @@ static hx_status enqueue_short(hx_pipeline* p, BatchContext& c, hipStream_t stre
     s.nzero = c.dirty[1 - set];
     s.theta = p->prm.thresh_frac;
     c.dirty[set] = c.n_ways;
-    HX_TRY(launch_batch_short(p->prm.ksize, c.last_c, s, p->taps, stream));
+    HX_TRY(launch_batch_short(p->prm.ksize, c.last_c, s, p->taps, stream, done));
     c.dirty[1 - set] = 0;
     return HX_OK;
 }
@@ -734,12 +736,16 @@ static hx_status launch_on(hx_pipeline* p, BatchContext& c, const hx_image* imgs
         if (st != HX_OK) return st;
     }
     TraceRange tr("hx.batch.enqueue");
-    if (pass == kPassShort) return enqueue_short(p, c, stream);
+    // The last kernel completes the context's event itself, except in a
+    // recorded call, where run_batched records it.
+    const hipEvent_t done = is_capturing(stream) ? nullptr : c.ev_done;
+    c.done_set = done != nullptr;
+    if (pass == kPassShort) return enqueue_short(p, c, stream, done);
     c.dirty[0] = std::max(c.dirty[0], c.n_ways);
     // The three kernels are launched one by one, also for a repeated batch:
     // replaying them as a captured graph cost 6 to 8 us more per call (16
     // thumbnails 28.5 against 21.2 us, 2 x 1080p 36.1 against 28.9).
-    HX_TRY(enqueue_phases(p, c, pass, stream, p->timing));
+    HX_TRY(enqueue_phases(p, c, pass, stream, p->timing, done));
     if (p->timing) p->last_timed_ctx = (int)(&c - p->ctx);
     logf(2, "batch context %d: %d images, items %lld / %lld / %lld (pass 1 / 2 / 0), %s%s",
          (int)(&c - p->ctx), n, (long long)c.n_items[1], (long long)c.n_items[2],
@@ -840,6 +846,7 @@ hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
                     "batched STORE needs a pipeline created with HX_FORM_BATCH_STORE");
     BatchContext& c = p->ctx[pick];
     c.last_use = ++p->use_clock;
+    c.done_set = false;
     hx_status st = HX_OK;
     if (same && c.in_flight && !p->timing && !is_capturing(stream)) {
         // Nothing on the host changes: the stream waits for the context's
@@ -918,6 +925,7 @@ hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
             }
             if (st != HX_OK) return st;
             HX_TRY(hipEventRecord(c.ev_done, stream));
+            c.done_set = true;
             c.in_flight = true;
             if (i < n) {
                 st = ctx_wait(c);
@@ -925,7 +933,7 @@ hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
             }
         }
     }
-    HX_TRY(hipEventRecord(c.ev_done, stream));
+    if (!c.done_set) HX_TRY(hipEventRecord(c.ev_done, stream));
     c.in_flight = true;
     return HX_OK;
 }

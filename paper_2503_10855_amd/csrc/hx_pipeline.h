@@ -93,6 +93,7 @@ struct BatchContext {
     DevBuf cand_code, cand_row; // SPECULATE: listed pixels
     hipEvent_t ev_done = nullptr;
     hipEvent_t ev_t[5] = {};    // timing mode
+    bool done_set = false;      // this call's last launch completes ev_done
     bool in_flight = false;
     uint64_t last_use = 0;      // the pipeline's call counter at the last use
     // Leading words of each set of max slots that a call may have left

@@ -1,5 +1,7 @@
 // k_batch.hip -- host side of the batched launch: geometry and launchers
 // (the kernels: batch_impl.h, instantiated by batch_inst.hip).
+#include <hip/hip_ext.h>
+
 #include "batch_impl.h"
 
 namespace hx {
@@ -55,21 +57,30 @@ static const void* batch_kernel_ptr(int ks, int pass, int phase, bool short_tile
     return k;
 }
 
-hipError_t launch_batch_short(int ks, int c, const ShortArgs& s, const Taps& t, hipStream_t stream) {
+static hipError_t launch(const void* k, int64_t grid, int block, void** args, int lds,
+                         hipStream_t s, hipEvent_t done) {
+    if (!done) return hipLaunchKernel(k, dim3((unsigned)grid), dim3(block), args, lds, s);
+    return hipExtLaunchKernel(k, dim3((unsigned)grid), dim3(block), args, lds, s, nullptr, done,
+                              0);
+}
+
+hipError_t launch_batch_short(int ks, int c, const ShortArgs& s, const Taps& t,
+                              hipStream_t stream, hipEvent_t done) {
     ShortArgs sc = s;
     Taps tc = t;
     void* args[] = {(void*)&sc, (void*)&tc};
     for (int phase = 1; phase <= 2; ++phase) {
         const void* k = batch_kernel_ptr(ks, kPassShort, phase, c == 1);
         if (!k || s.n < 1 || (c != 1 && c != 2)) return hipErrorInvalidValue;
-        hipError_t e = hipLaunchKernel(k, dim3((unsigned)s.n), dim3(64), args, 0, stream);
+        hipError_t e = launch(k, s.n, 64, args, 0, stream, phase == 2 ? done : nullptr);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }
 
 hipError_t launch_batch_phase(int ks, int pass_mode, int phase, int ty, int64_t items,
-                              const void* d_table, const Taps& t, hipStream_t s) {
+                              const void* d_table, const Taps& t, hipStream_t s,
+                              hipEvent_t done) {
     const bool spec = pass_mode == HX_PASS_SPECULATE;
     const bool short_tile = spec && phase == 1 && ty <= kShortTile;
     const void* k = batch_kernel_ptr(ks, pass_mode, phase, short_tile);
@@ -88,7 +99,7 @@ hipError_t launch_batch_phase(int ks, int pass_mode, int phase, int ty, int64_t 
     const uint8_t* tab = (const uint8_t*)d_table;
     Taps tc = t;
     void* args[] = {(void*)&tab, (void*)&tc};
-    return hipLaunchKernel(k, dim3((unsigned)grid), dim3(block), args, lds, s);
+    return launch(k, grid, block, args, lds, s, done);
 }
 
 }  // namespace hx
