@@ -11,9 +11,9 @@
 // SPECULATE adds pass 0 (one item = one 8-row sampled band tile: blur +
 // Sobel -> a lower bound of the max), runs every stage in pass 1 (mask
 // against the bound's threshold, plus the list of pixels it set), and
-// re-decides only the listed pixels in pass 2 (the lists of up to
-// kP2Tiles pass-1 tiles per workgroup).  A tile whose list did not hold its
-// pixels is queued by pass 1 and redone by pass 2 in 8-row pieces.
+// re-decides only the listed pixels in pass 2 (one wave per pass-1 tile).
+// A tile whose list did not hold its pixels is queued by pass 1 and redone
+// by pass 2 in 8-row pieces.
 // Pass 2 starts after pass 1 has finished (a kernel boundary), so every max
 // is final when it is read; no workgroup ever waits for another one.  Each
 // wave takes the item of its index (the host sizes each grid to its pass's
@@ -96,12 +96,6 @@ __device__ __forceinline__ int global_wave() {
                                           (int)(threadIdx.x >> 6));
 }
 
-// Columns per lane of pass 0's tiles.  They are 8 rows tall, so the short
-// sweep runs them (see tile_impl.h).  On 64 x 1080p the pass reads 41 MB and
-// is bound by that: 17.0 us by the long sweep, 15.8 by this one (17.0 with 4
-// columns per lane); on 16 images of 64..256, 5.2 and 4.5 us.
-constexpr int kP0C = 2;
-
 // Word w of the bounds of image a.
 __device__ __forceinline__ unsigned long long* bound_word(const BatchHeader& h, const ImgArgs& a,
                                                           int w) {
@@ -113,33 +107,32 @@ __device__ __forceinline__ unsigned long long* bound_word(const BatchHeader& h, 
 // max, so each then holds a lower bound of it.  The first item of each
 // image also clears the image's max slot (pass 1 folds into it after this
 // kernel), so SPECULATE needs no reset kernel; the first item of all
-// empties pass 1's queue.
+// empties pass 1's queue.  The long sweep's form (64 x 1080p 15.3 us): the
+// short sweep takes as long alone (16), and with its LDS does not fit beside
+// another call's pass 1.
 template <int KS>
-__global__ __launch_bounds__(64)
+__global__ __launch_bounds__(64 * kWG) __attribute__((amdgpu_waves_per_eu(sweep_waves(KS))))
 void k_batch_p0(const uint8_t* __restrict__ table, Taps tp) {
-    using S = TileShape<KS, kP0C, SM_MAXONLY>;
-    __shared__ __align__(16) float rows[S::lds_floats(kSampleRows)];
+    using S = SweepShape<KS, kBC, SM_MAXONLY>;
     const TableView tv = view(table);
+    const int nw = gridDim.x * kWG;
     const uint64_t ep = (uint64_t)*as_global(tv.hdr.epoch) << 32;
-    const int k = xcd_remap(blockIdx.x, gridDim.x);   // one item per workgroup
-    if (k >= tv.hdr.n_items0) return;
-    const BatchItem it = tv.item(tv.items0, k);
-    const ImgArgs a = tv.imgs[it.image];
-    const int nstrips = (a.W + S::OW - 1) / S::OW;
-    const int x0 = (it.local % nstrips) * S::OW;
-    const int y0 = (it.local / nstrips) * sample_stride(a.H);
-    lds_float* lds = (lds_float*)rows;
-    tile_load<kP0C>(a, x0 - S::HL, y0 - S::HY, min(kSampleRows, a.H - y0) + 2 * S::HY, lds);
-    if (it.local == 0 && lane_id() < a.ways)
-        as_global(a.slot)[(int64_t)lane_id() * a.slot_step] = 0u;
-    if (k == 0 && lane_id() == 0) *as_global(tv.hdr.redo_n) = 0u;
-    tile_loads_done();
-    float gmax = 0.0f;
-    tile_sweep<KS, kP0C, SM_MAXONLY>(a, tp, x0, y0, kSampleRows, 0.0f, gmax, lds);
-    gmax = wave_max(gmax);
-    if (lane_id() == 0)
-        atomicMax(bound_word(tv.hdr, a, k & (a.ways - 1)),
-                  (unsigned long long)(ep | __float_as_uint(gmax)));
+    for (int k = global_wave(); k < tv.hdr.n_items0; k += nw) {
+        const BatchItem it = tv.item(tv.items0, k);
+        const ImgArgs a = tv.imgs[it.image];
+        if (it.local == 0 && lane_id() < a.ways)
+            as_global(a.slot)[(int64_t)lane_id() * a.slot_step] = 0u;
+        if (k == 0 && lane_id() == 0) *as_global(tv.hdr.redo_n) = 0u;
+        const int nstrips = (a.W + S::OW - 1) / S::OW;
+        float gmax = 0.0f;
+        sweep_tile<KS, kBC, SM_MAXONLY>(a, tp, (it.local % nstrips) * S::OW,
+                                         (it.local / nstrips) * sample_stride(a.H), kSampleRows,
+                                         0.0f, gmax);
+        gmax = wave_max(gmax);
+        if (lane_id() == 0)
+            atomicMax(bound_word(tv.hdr, a, k & (a.ways - 1)),
+                      (unsigned long long)(ep | __float_as_uint(gmax)));
+    }
 }
 
 // SPECULATE pass 1's threshold on G^2 of an image: pass 0 finished before
@@ -330,126 +323,70 @@ __global__ __launch_bounds__(64) void k_batch_short_mask(ShortArgs s, Taps tp) {
                                lds);
 }
 
-// Tiles whose lists one workgroup of SPECULATE's pass 2 takes, at most, and
-// the columns per lane of the pieces it redoes queued tiles in (8 rows
-// each; four waves' rows are 32 KB of LDS at k = 5, five workgroups per CU).
-constexpr int kP2Tiles = 16, kRedoC = 2, kRedoRows = 8;
+// Columns per lane and rows of the pieces SPECULATE's pass 2 redoes queued
+// tiles in (8 KB of LDS per wave at k = 5).
+constexpr int kRedoC = 2, kRedoRows = 8;
 
-// SPECULATE pass 2.  A tile's list is short (about 110 entries on average
-// on 1080p frames), so the pass is bound by latency: one wave per tile had
-// 8700 waves each wait for item, count and entries in turn (16 us, 38 us
-// when one of them redid a whole 64-row tile).  Here each workgroup reads
-// the state of up to kP2Tiles tiles with one lane each, and its 256 threads
-// then walk the concatenated lists, several entries in flight per thread;
-// tiles are dealt out one per workgroup in turn, as dense lists are
-// neighbours.  Queued tiles are redone by all waves of the grid, a piece
-// of 8 rows at a time.  64 x 1080p (51 queued tiles): 38.3 -> 17.7 us; 256
-// images of 64..2048 (172 queued): 43.4 -> 22.8 us.
+// SPECULATE pass 2: one wave per tile, as short as the loads it waits for
+// allow (item and count, image, max and entries), so many waves are kept in
+// flight: the redo of queued tiles is the short sweep's, which leaves the
+// kernel 73 registers and 11 KB of code (the long sweep's mask-only form took
+// 130 and 250 KB), so a wave of it fits beside three of another call's pass 1
+// on each SIMD.  Queued tiles are redone by all waves of the grid, a piece of
+// 8 rows at a time.  64 x 1080p 19 us, 256 uneven images 21.6; as workgroups
+// of four waves with 32 KB that shared a run of lists 19 and 23.6, and four
+// calls in flight took 0.157 ms each, not 0.150.
 template <int KS>
-__global__ __launch_bounds__(256)
+__global__ __launch_bounds__(64)
 void k_batch_p2s(const uint8_t* __restrict__ table, Taps tp) {
     using S = SweepShape<KS, kBC, SM_SPEC>;
     using RS = TileShape<KS, kRedoC, SM_MASK>;
-    struct Tile {
-        const float* code;
-        const int32_t* row;
-        uint8_t* mask;    // of column 0 of lane 0's first column, top row
-        int64_t mp;
-        float thr2;
-        int left;         // columns from there to the image's right edge
-        int words;        // mask rows are word aligned
-    };
-    __shared__ Tile st[kP2Tiles];
-    __shared__ uint32_t first[kP2Tiles + 1];   // entries before tile j
-    __shared__ __align__(16) float rows[4 * RS::lds_floats(kRedoRows)];
+    __shared__ __align__(16) float rows[RS::lds_floats(kRedoRows)];
     const TableView tv = view(table);
-    const int tid = threadIdx.x;
-    const int n = tv.hdr.n_items2, G = gridDim.x;
-    // 16 threads per tile read its state (and the words of its image's max).
-    static_assert(kP2Tiles * 16 == 256, "16 threads per tile");
+    const int lane = lane_id();
+    const int k = xcd_remap(blockIdx.x, gridDim.x);
     {
-        const int j = tid >> 4, l = tid & 15;
-        const int64_t k = blockIdx.x + (int64_t)j * G;
-        uint32_t cnt = 0;
-        if (k < n) {
-            const BatchItem it = tv.item(tv.items2, k);
-            const ImgArgs& a = tv.imgs[it.image];
-            cnt = as_global(tv.hdr.cand_n)[k];
-            uint32_t m2 = 0;
-            for (int w = l; w < a.ways; w += 16)
-                m2 = max(m2, as_global(a.slot)[(int64_t)w * a.slot_step]);
-#pragma unroll
-            for (int o = 8; o > 0; o >>= 1) m2 = max(m2, (uint32_t)__shfl_xor((int)m2, o, 16));
-            const int nstrips = (a.W + S::OW - 1) / S::OW;
-            const int x0 = (it.local % nstrips) * S::OW, y0 = (it.local / nstrips) * a.ty;
-            const SpecTile sp = list_of(tv.hdr, a, it.local);
-            if (cnt > sp.cap) cnt = 0;   // incomplete: queued
-            if (l == 0) {
-                if (it.local == 0 && a.dmax) *as_global(a.dmax) = max_from(m2);
-                st[j] = Tile{sp.code, sp.row, a.mask + (int64_t)y0 * a.mp + (x0 - S::HL), a.mp,
-                             thr2_from(m2, tv.hdr.theta), a.W - (x0 - S::HL),
-                             ((reinterpret_cast<uintptr_t>(a.mask) | (uint64_t)a.mp) & 3u) == 0};
-            }
-        }
-        if (l == 0) first[j + 1] = cnt;
-    }
-    __syncthreads();
-    if (tid < kP2Tiles) {
-        uint32_t sum = first[tid + 1];
-#pragma unroll
-        for (int o = 1; o < kP2Tiles; o <<= 1) {
-            const uint32_t up = __shfl_up(sum, o, kP2Tiles);
-            if (tid >= o) sum += up;
-        }
-        first[tid + 1] = sum;
-        if (tid == 0) {
-            first[0] = 0;
-            // The last reader of this batch's bounds has finished: advance
-            // the epoch for the next batch on this context.
-            if (blockIdx.x == 0) *as_global(tv.hdr.epoch) += 1u;
-        }
-    }
-    __syncthreads();
-    const uint32_t total = first[kP2Tiles];
-    constexpr int U = 4;   // entries in flight per thread
-    for (uint32_t t0 = tid; t0 < total; t0 += 256 * U) {
-        VecF<kBC> g2[U];
-        uint32_t rw[U];
-        int tj[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const uint32_t t = min(t0 + 256u * u, total - 1);
-            int j = 0;
-#pragma unroll
-            for (int b = kP2Tiles / 2; b > 0; b >>= 1)
-                if (first[j + b] <= t) j += b;
-            const uint32_t i = t - first[j];
-            const gptr<const VecF<kBC>> q = (gptr<const VecF<kBC>>)as_global(st[j].code) + i;
-#pragma unroll
-            for (int e = 0; e < kBC; ++e) g2[u].v[e] = q->v[e];
-            rw[u] = (uint32_t)as_global(st[j].row)[i];
-            tj[u] = j;
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (t0 + 256u * u >= total) break;
+        const BatchItem it = tv.item(tv.items2, k);
+        const int n_listed = (int)as_global(tv.hdr.cand_n)[k];
+        const ImgArgs a = tv.imgs[it.image];
+        const SpecTile sp = list_of(tv.hdr, a, it.local);
+        const uint32_t m2 = a.ways > 1 ? slot_max(a) : *as_global(a.slot);
+        const float thr2 = thr2_from(m2, tv.hdr.theta);
+        if (it.local == 0 && lane == 0 && a.dmax) *as_global(a.dmax) = max_from(m2);
+        // The last reader of this batch's bounds has finished: advance the
+        // epoch for the next batch on this context.
+        if (k == 0 && lane == 0) *as_global(tv.hdr.epoch) += 1u;
+        const int nstrips = (a.W + S::OW - 1) / S::OW;
+        const int left = (it.local % nstrips) * S::OW - S::HL;
+        const int y0 = (it.local / nstrips) * a.ty;
+        const int n = (uint32_t)n_listed > sp.cap ? 0 : n_listed;   // incomplete: queued
+        const bool mvec = ((reinterpret_cast<uintptr_t>(a.mask) % 4) == 0) & ((a.mp % 4) == 0);
+        for (int t = lane; t < n; t += 64) {
+            const gptr<const VecF<kBC>> q = (gptr<const VecF<kBC>>)as_global(sp.code) + t;
+            const uint32_t rw = (uint32_t)as_global(sp.row)[t];
+            const int cbase = left + kBC * (int)((rw >> 4) & 63u);
+            const gptr<uint8_t> rp =
+                as_global(a.mask) + (int64_t)(y0 + (int)(rw >> 10)) * a.mp + cbase;
             // Pass 1 set every listed pixel to 1 and left the others of the
             // lane-row at 0.  Only a listed pixel at or below the true
             // threshold changes (to 0): the lane-row is rewritten, as one
             // aligned word when it lies inside the image, only if one did.
-            const Tile& T = st[tj[u]];
+            // Those are few when the bound is close to the max, and
+            // scattered partial writes are what this pass spends its time
+            // on.  Both loads are unconditional, so they are in flight
+            // together.
+            float g2v[kBC];
+#pragma unroll
+            for (int e = 0; e < kBC; ++e) g2v[e] = q->v[e];
             uint32_t w = 0, was = 0;
 #pragma unroll
             for (int e = 0; e < kBC; ++e) {
-                const uint32_t listed = (rw[u] >> e) & 1u;
+                const uint32_t listed = (rw >> e) & 1u;
                 was |= listed << (8 * e);
-                w |= (listed & (uint32_t)(g2[u].v[e] > T.thr2)) << (8 * e);
+                w |= (listed & (uint32_t)(g2v[e] > thr2)) << (8 * e);
             }
             if (w != was) {
-                const int col = kBC * (int)((rw[u] >> 4) & 63u);
-                const gptr<uint8_t> rp =
-                    as_global(T.mask) + (int64_t)(rw[u] >> 10) * T.mp + col;
-                if (kBC == 4 && T.words && col + 4 <= T.left) {
+                if (kBC == 4 && mvec && cbase + 4 <= a.W) {
                     *(gptr<uint32_t>)rp = w;
                 } else {
 #pragma unroll
@@ -464,13 +401,12 @@ void k_batch_p2s(const uint8_t* __restrict__ table, Taps tp) {
     const uint32_t nq = *as_global(tv.hdr.redo_n);
     if (nq == 0) return;
     constexpr int kAcross = (S::OW + RS::OW - 1) / RS::OW;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int per = kAcross * ((tv.hdr.ty + kRedoRows - 1) / kRedoRows);
-    lds_float* lds = (lds_float*)rows + wave * RS::lds_floats(kRedoRows);
-    for (int64_t c = (int64_t)blockIdx.x * 4 + wave; c < (int64_t)nq * per; c += 4 * (int64_t)G) {
-        const int k = __builtin_amdgcn_readfirstlane(as_global(tv.hdr.redo)[c / per]);
+    lds_float* lds = (lds_float*)rows;
+    for (int64_t c = blockIdx.x; c < (int64_t)nq * per; c += gridDim.x) {
+        const int kq = __builtin_amdgcn_readfirstlane(as_global(tv.hdr.redo)[c / per]);
         const int r = (int)(c % per);
-        const BatchItem it = tv.item(tv.items2, k);
+        const BatchItem it = tv.item(tv.items2, kq);
         const ImgArgs a = tv.imgs[it.image];
         const int nstrips = (a.W + S::OW - 1) / S::OW;
         const int x0 = (it.local % nstrips) * S::OW + (r % kAcross) * RS::OW;

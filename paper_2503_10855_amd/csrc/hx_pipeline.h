@@ -92,6 +92,7 @@ struct BatchContext {
     DevBuf code;                // pass-1 store buffer (STORE batches)
     DevBuf cand_code, cand_row; // SPECULATE: listed pixels
     hipEvent_t ev_done = nullptr;
+    hipEvent_t ev_prev = nullptr;   // of the call before, or complete
     hipEvent_t ev_t[5] = {};    // timing mode
     bool done_set = false;      // this call's last launch completes ev_done
     bool in_flight = false;
@@ -191,6 +192,16 @@ struct hx_pipeline {
     uint64_t use_clock = 0;
     std::mutex batch_mu;  // guards context choice (the server calls from
                           // its own thread)
+    // Do batched calls come from several streams?  Yes for a few calls after
+    // one on another stream than the one before it.
+    hipStream_t batch_stream = nullptr;
+    int alternating = 0;
+    void note_stream(hipStream_t s) {
+        if (use_clock > 1 && s != batch_stream) alternating = 2 * kMaxContexts;
+        else if (alternating > 0) --alternating;
+        batch_stream = s;
+    }
+    bool streams_alternate() const { return alternating > 0; }
     bool timing = false;
     int last_timed_ctx = -1;
 };

@@ -16,11 +16,9 @@ size_t batch_table_bytes(int n, int64_t n1, int64_t n2, int64_t n0) {
 }
 
 int64_t batch_sample_items(int ks, int64_t H, int64_t W) {
-    const int64_t ow = ks == 3   ? TileShape<3, kP0C, SM_MAXONLY>::OW
-                       : ks == 5 ? TileShape<5, kP0C, SM_MAXONLY>::OW
-                                 : TileShape<7, kP0C, SM_MAXONLY>::OW;
+    const SweepGeom g{ks, kBC, kSampleRows};
     const int st = sample_stride(H);
-    return (W + ow - 1) / ow * ((H + st - 1) / st);
+    return g.strips(W) * ((H + st - 1) / st);
 }
 
 static __global__ void k_batch_reset(const uint8_t* __restrict__ table) {
@@ -57,10 +55,10 @@ static const void* batch_kernel_ptr(int ks, int pass, int phase, bool short_tile
     return k;
 }
 
-static hipError_t launch(const void* k, int64_t grid, int block, void** args, int lds,
-                         hipStream_t s, hipEvent_t done) {
-    if (!done) return hipLaunchKernel(k, dim3((unsigned)grid), dim3(block), args, lds, s);
-    return hipExtLaunchKernel(k, dim3((unsigned)grid), dim3(block), args, lds, s, nullptr, done,
+static hipError_t launch(const void* k, int64_t grid, void** args, int lds, hipStream_t s,
+                         hipEvent_t done) {
+    if (!done) return hipLaunchKernel(k, dim3((unsigned)grid), dim3(64), args, lds, s);
+    return hipExtLaunchKernel(k, dim3((unsigned)grid), dim3(64), args, lds, s, nullptr, done,
                               0);
 }
 
@@ -72,7 +70,7 @@ hipError_t launch_batch_short(int ks, int c, const ShortArgs& s, const Taps& t,
     for (int phase = 1; phase <= 2; ++phase) {
         const void* k = batch_kernel_ptr(ks, kPassShort, phase, c == 1);
         if (!k || s.n < 1 || (c != 1 && c != 2)) return hipErrorInvalidValue;
-        hipError_t e = launch(k, s.n, 64, args, 0, stream, phase == 2 ? done : nullptr);
+        hipError_t e = launch(k, s.n, args, 0, stream, phase == 2 ? done : nullptr);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -85,21 +83,13 @@ hipError_t launch_batch_phase(int ks, int pass_mode, int phase, int ty, int64_t 
     const bool short_tile = spec && phase == 1 && ty <= kShortTile;
     const void* k = batch_kernel_ptr(ks, pass_mode, phase, short_tile);
     if (!k || items < 0) return hipErrorInvalidValue;
-    int64_t grid = items;
-    int block = 64, lds = 0;
+    const int64_t grid = items < 1 ? 1 : items;
+    int lds = 0;
     if (short_tile) lds = (ty + 2 * (ks / 2 + 2)) * 64 * kBC * (int)sizeof(float);
-    if (spec && phase == 2) {
-        // Enough workgroups to cover the chip before any takes a second
-        // tile's list.
-        block = 256;
-        const int64_t want = items < 512 ? items : 512, need = (items + kP2Tiles - 1) / kP2Tiles;
-        grid = want > need ? want : need;
-    }
-    if (grid < 1) grid = 1;
     const uint8_t* tab = (const uint8_t*)d_table;
     Taps tc = t;
     void* args[] = {(void*)&tab, (void*)&tc};
-    return launch(k, grid, block, args, lds, s, done);
+    return launch(k, grid, args, lds, s, done);
 }
 
 }  // namespace hx

@@ -24,7 +24,7 @@
 //
 // Stages C and D keep a row's per-column decisions in one 32-bit word per
 // lane, one byte per column (the layout of the lane's mask bytes): the
-// signs of L (0/1), the 3-wide windows' "holds an L > 0" / "holds only
+// signs of L (0x00/0xff), the 3-wide windows' "holds an L > 0" / "holds only
 // L > 0" (OR / AND of the word and its copies shifted by one column, the
 // neighbouring lanes' edge bytes shifted in by one DPP move and one
 // alignbit each), and the threshold G^2 > thr2 as 0x00/0xff bytes (the

@@ -228,3 +228,41 @@ def test_small_batches_in_turn_on_one_context(hx, ks):
             p.sync()
             assert torch.equal(dm, rm)
             assert all(torch.equal(a, b) for a, b in zip(got2, ref))
+
+
+@pytest.mark.parametrize("contexts,n_streams", [(1, 1), (1, 3), (2, 3)])
+def test_repeated_batch_on_new_contents(hx, contexts, n_streams):
+    """One batch repeated on the same context with new contents each time,
+    first far ahead of the GPU on one stream, then on several in turn: every
+    call's masks and maxima are those of its own contents."""
+    shapes = [(700, 900), (33, 2000), (1100, 1900), (1100, 1900), (900, 1300)] * 2
+    steps = 9
+    sets = [[torch.from_numpy(synth.image(h, w, 311, 20 * s + i) * np.float32(1 + s)).cuda()
+             for i, (h, w) in enumerate(shapes)] for s in range(3)]
+    with hx.Pipeline(ksize=5, sigma=1.0, theta=THETA, max_pixels=1 << 24, max_images=len(shapes),
+                     batch_contexts=contexts) as p:
+        p.set_schedule(256, 64, 4, hx.PASS_STORE)
+        want = []
+        for imgs in sets:
+            dm = torch.zeros(len(shapes), device="cuda")
+            want.append((p.edge_detect_batched(imgs, dmax=dm), dm))
+        p.sync()
+        p.set_schedule()
+        for used in (1, n_streams):
+            streams = [torch.cuda.Stream() for _ in range(used)]
+            lanes = [([torch.empty_like(x) for x in sets[0]],
+                      [torch.empty(x.shape, dtype=torch.uint8, device="cuda") for x in sets[0]],
+                      torch.zeros(len(shapes), device="cuda")) for _ in streams]
+            torch.cuda.synchronize()
+            kept = []
+            for i in range(steps):
+                src, masks, dm = lanes[i % used]
+                with torch.cuda.stream(streams[i % used]):
+                    torch._foreach_copy_(src, sets[i % 3])
+                    p.edge_detect_batched(src, masks, dmax=dm, stream=streams[i % used])
+                    kept.append(([m.clone() for m in masks], dm.clone()))
+            torch.cuda.synchronize()
+            for i, (masks, dm) in enumerate(kept):
+                print(f"{contexts} contexts, {used} streams, call {i}", flush=True)
+                assert torch.equal(dm, want[i % 3][1])
+                assert all(torch.equal(a, b) for a, b in zip(masks, want[i % 3][0]))
