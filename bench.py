@@ -4,7 +4,7 @@
 One step = the whole hot path (blur, Laplacian, zero crossing, Sobel, max
 reduction, threshold) over one batch of seeded synthetic images already
 resident in HBM.  The default workload is 64 images of 1920x1080 (5x5
-Gaussian, sigma 1), run as one batched graph launch; the same images are
+Gaussian, sigma 1), run as one batched call; the same images are
 also timed through the per-image forms (fused and one kernel per stage)
 for the batched-vs-per-image comparison.  Prints one JSON line.
 
@@ -41,11 +41,11 @@ PATH_BYTES_PER_PX = 5.0    # input read once + mask written once
 KERNEL_BYTES_PER_PX = {1: {1: 4.0, 2: 1.0}, 2: {1: 4.0, 2: 5.0}, 3: {1: 5.0, 2: 0.0}}
 BATCH_DEFAULT_PASS = 3    # the library's pass structure for batched calls
 BATCH_TILE_W = 256        # batched sweep tiles: one wave, 4 columns per lane
-BATCH_DEFAULT_TY = 64     # their height when neither tuned nor fixed
+BATCH_DEFAULT_TY = 48     # their height for the larger batches, neither tuned nor fixed
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_batch_64x1080p.json")
 SWEEP_SOURCES = ["paper_2503_10855_amd/csrc/" + f for f in
-                 ("sweep_impl.h", "hx_device.h", "hx_kernels.h", "k_batch.hip",
-                  "thresh_impl.h")]
+                 ("sweep_impl.h", "tile_impl.h", "batch_impl.h", "batch_inst.hip", "hx_device.h",
+                  "hx_kernels.h", "k_batch.hip", "thresh_impl.h")]
 
 
 def workloads():
@@ -164,8 +164,7 @@ def timed_streams(fns, streams, steps, warmup):
     bracketed by events on the current stream, which every stream waits on
     at the start and waits for at the end.  The warm-up runs at least three
     calls per stream whatever `warmup` says (the first builds a batch
-    context's table, the second captures its graph, the third replays it),
-    so every timed call replays a captured graph."""
+    context's table), so every timed call reuses its context's table."""
     import torch
     S = len(streams)
     for i in range(max(warmup, 3 * S)):
@@ -315,7 +314,7 @@ def main():
     sync = torch.cuda.synchronize
 
     # One batch context per stream (at least the library's default 4), so
-    # that each stream's output set keeps its own table and graph.
+    # that each stream's output set keeps its own table.
     with hx.Pipeline(ksize=wl.ksize, sigma=wl.sigma, theta=wl.theta,
                      max_pixels=pixels, max_images=max(len(srcs), 1),
                      pass_mode=args.pass_mode, batch_contexts=min(8, max(4, S))) as p:
@@ -435,7 +434,7 @@ def main():
         "data": "synthetic",
         "config": {"workload": wl.name, "images": len(wl.sizes), "pixels": pixels,
                    "ksize": wl.ksize, "sigma": wl.sigma, "theta": wl.theta,
-                   "form": f"batched graph launch, consecutive batches on {S} "
+                   "form": f"batched call, consecutive batches on {S} "
                            f"stream{'s' if S > 1 else ''} in turn",
                    "streams": S, "output_sets_identical": same_sets,
                    "pass_mode": {0: "batch default", 1: "store", 2: "recompute",
@@ -529,7 +528,7 @@ def serve_leg(hx, n, rate, budget_mb, streams, max_batch, pool_n=None, verbose=T
         arena = torch.empty(max(budget - own, 1 << 12), dtype=torch.uint8, device="cuda")
         with hx.Server(p, hbm_budget=budget, streams=streams,
                        max_batch=max_batch, arena=arena) as srv:
-            # Warm-up: every batch context captures its graph once.  A
+            # Warm-up: every batch context is used once.  A
             # full pinned pool is drained before the next submission.
             warm = []
             for i in range(min(64, n)):
