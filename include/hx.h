@@ -257,9 +257,9 @@ hx_status hx_edge_detect(hx_pipeline* p, const hx_image* img, float* d_max,
  * sum H*W <= max_pixels.  Each image's result is bit-identical to
  * hx_edge_detect on it alone.  Batched calls use one of batch_contexts
  * scratch sets each, so calls on different streams overlap; a call whose
- * context is still in use waits for it, on the host where the descriptor
- * table is rebuilt or calls come from several streams, else on the device
- * (with the host at most two large calls ahead).  A batch with more
+ * context is still in use waits for it: a repeated batch on the device
+ * (the host stays at most two large calls ahead), a new one on the host,
+ * where its descriptor table is rebuilt.  A batch with more
  * tiles than a context's descriptor table holds (only possible with many
  * images a few pixels wide or tall) runs as several launches in turn. */
 hx_status hx_edge_detect_batched(hx_pipeline* p, const hx_image* imgs,

@@ -850,17 +850,14 @@ hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
     c.last_use = ++p->use_clock;
     c.done_set = false;
     hx_status st = HX_OK;
-    p->note_stream(stream);
-    if (same && c.in_flight && !p->timing && !p->streams_alternate() && !is_capturing(stream)) {
+    if (same && c.in_flight && !p->timing && !is_capturing(stream)) {
         // Nothing on the host changes: the stream waits for the context's
         // previous call (no wait at all if that is this stream's own).  The
-        // host stays at most two large calls ahead: waiting for the previous
-        // one leaves gaps (64 x 1080p 194 against 187 us a call), and calls
-        // queued up further have run slower on some hardware queues (235).
-        // With calls from several streams the host does wait for it: all
-        // queued up ahead, the streams run in step, with the latency-bound
-        // passes 0 and 2 of all at once (64 x 1080p on four streams in
-        // 32-row tiles 0.150 against 0.139 ms a call).
+        // host stays at most two large calls ahead of a context: waiting for
+        // the previous one leaves gaps (64 x 1080p 194 against 187 us a
+        // call), and calls queued up further have run slower on some
+        // hardware queues (235), and on four streams in step with each other
+        // (32-row tiles 0.146..0.150 against 0.138..0.141 ms a call).
         HX_TRY(hipStreamWaitEvent(stream, c.ev_done, 0));
         if (pass != kPassShort) {
             std::swap(c.ev_done, c.ev_prev);

@@ -192,16 +192,6 @@ struct hx_pipeline {
     uint64_t use_clock = 0;
     std::mutex batch_mu;  // guards context choice (the server calls from
                           // its own thread)
-    // Do batched calls come from several streams?  Yes for a few calls after
-    // one on another stream than the one before it.
-    hipStream_t batch_stream = nullptr;
-    int alternating = 0;
-    void note_stream(hipStream_t s) {
-        if (use_clock > 1 && s != batch_stream) alternating = 2 * kMaxContexts;
-        else if (alternating > 0) --alternating;
-        batch_stream = s;
-    }
-    bool streams_alternate() const { return alternating > 0; }
     bool timing = false;
     int last_timed_ctx = -1;
 };
