@@ -52,13 +52,6 @@ __device__ __forceinline__ float lap_from(float ns, float ew, float c) {
     return fmaf(-4.0f, c, ns + ew);
 }
 
-// 4c - ((n + s) + (e + w)): its sign bit is set exactly when lap_from is
-// > 0 (both round the same exact value, a non-zero one never to zero, and
-// x - x is +0), for finite sums.  The sweeps need no more of L than that.
-__device__ __forceinline__ float neg_lap_from(float ns, float ew, float c) {
-    return fmaf(4.0f, c, -(ns + ew));
-}
-
 // Sobel as two smoothings and two differences:
 //   sy = ew + 2 B(x)          along a row (ew = B(x-1) + B(x+1)),
 //   vs = ns + 2 B(y)          down a column (ns = B(y-1) + B(y+1)),

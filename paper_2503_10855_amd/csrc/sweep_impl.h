@@ -24,7 +24,7 @@
 //
 // Stages C and D keep a row's per-column decisions in one 32-bit word per
 // lane, one byte per column (the layout of the lane's mask bytes): the
-// signs of L (0x00/0xff), the 3-wide windows' "holds an L > 0" / "holds only
+// signs of L (0/1), the 3-wide windows' "holds an L > 0" / "holds only
 // L > 0" (OR / AND of the word and its copies shifted by one column, the
 // neighbouring lanes' edge bytes shifted in by one DPP move and one
 // alignbit each), and the threshold G^2 > thr2 as 0x00/0xff bytes (the
@@ -113,8 +113,30 @@ __device__ __forceinline__ float lane_fetch(float v) {
     else return lane_fetch<Q + 1>(dpp_from_left(v));
 }
 
+// 1 if l > 0, else 0 (for finite l): the bits of l as a signed integer,
+// clamped to [0, 1] in one instruction.
+__device__ __forceinline__ uint32_t pos_bit(float l) {
+    uint32_t r;
+    asm("v_med3_i32 %0, %1, 0, 1" : "=v"(r) : "v"(l));
+    return r;
+}
+
 // Row words of stage D hold one byte per column of the lane (byte e =
-// column e, bytes C..3 zero).
+// column e, bytes C..3 zero).  The low bytes of b[0..C-1] packed so.
+template <int C>
+__device__ __forceinline__ uint32_t col_bytes(const uint32_t (&b)[C]) {
+    if constexpr (C == 4) {
+        // Two byte gathers (v_perm_b32: selector 0x0c gives a zero byte).
+        return __builtin_amdgcn_perm(b[1], b[0], 0x0c0c0400u) |
+               __builtin_amdgcn_perm(b[3], b[2], 0x04000c0cu);
+    } else {
+        uint32_t w = b[0];
+#pragma unroll
+        for (int e = 1; e < C; ++e) w |= b[e] << (8 * e);
+        return w;
+    }
+}
+
 // Byte e = 0xff if t[e] has its sign bit set, else 0 (v_perm_b32 selectors
 // 9 and 11 replicate the sign bit of byte 3 of its low / high source).
 template <int C>
@@ -463,8 +485,8 @@ __device__ __forceinline__ void sweep_body(const ImgArgs& a, const Taps& tp,
     float bb[P][C];   // B rows
     float ew[P][C];   // B(x-1) + B(x+1)
     float sy[P][C];   // Sobel sy
-    uint32_t ho[P];   // per L row, byte e: the 3-wide window at column e holds
-    uint32_t ha[P];   // an L > 0 (ho) / only L > 0 (ha), as 0xff
+    uint32_t ho[P];   // per L row, byte e: the 3-wide window at column e
+    uint32_t ha[P];   // holds an L > 0 (ho) / holds only L > 0 (ha), 0/1
     float g2d[C];     // G^2 of the row waiting for its Z
     uint32_t tbd = 0; // its threshold bytes (0xff where G^2 > thr2)
     float gacc = 0.0f;
@@ -488,10 +510,10 @@ __device__ __forceinline__ void sweep_body(const ImgArgs& a, const Taps& tp,
         cdl[e] = 0.0f;
         g2l[e] = 0.0f;
     }
-    // The lane's columns inside the image, as 0/1 bytes (border variants).
+    // The lane's columns inside the image, as 0xff bytes (border variants).
     uint32_t emw = 0;
 #pragma unroll
-    for (int e = 0; e < C; ++e) emw |= ecol[e] ? (1u << (8 * e)) : 0u;
+    for (int e = 0; e < C; ++e) emw |= ecol[e] ? (0xffu << (8 * e)) : 0u;
     auto flush_out = [&]() {
         if constexpr (S::NEED_Z) {
             if (pv) {
@@ -730,8 +752,7 @@ __device__ __forceinline__ void sweep_body(const ImgArgs& a, const Taps& tp,
                 float l[C];
 #pragma unroll
                 for (int e = 0; e < C; ++e)
-                    l[e] = S::NEED_Z ? neg_lap_from(ns[e], ew[J1][e], bb[J1][e])
-                                     : lap_from(ns[e], ew[J1][e], bb[J1][e]);
+                    l[e] = lap_from(ns[e], ew[J1][e], bb[J1][e]);
                 if constexpr (MODE == SM_BGL) {
                     if (row_out) {
                         store_f(fo, vl, l);
@@ -752,9 +773,13 @@ __device__ __forceinline__ void sweep_body(const ImgArgs& a, const Taps& tp,
 #pragma unroll
                         for (int e = 1; e < C; ++e) l[e] = fixB[e] ? l[e - 1] : l[e];
                     }
-                    // Z needs only whether L > 0: the sign bit of l, which
-                    // holds -L here, as a 0xff byte per column.
-                    const uint32_t sw = col_sign_bytes<C>(l);
+                    // Z needs only the sign of L: 1 if L > 0 (L's bits,
+                    // read as a signed integer, are >= 1; -0 reads as
+                    // INT_MIN), one byte per column.
+                    uint32_t sb[C];
+#pragma unroll
+                    for (int e = 0; e < C; ++e) sb[e] = pos_bit(l[e]);
+                    const uint32_t sw = col_bytes<C>(sb);
                     const uint32_t sl = cols_from_left<C>(sw), sr = cols_from_right<C>(sw);
                     ho[J] = sw | sl | sr;
                     ha[J] = sw & sl & sr;
@@ -784,8 +809,8 @@ __device__ __forceinline__ void sweep_body(const ImgArgs& a, const Taps& tp,
                             } else {
                                 static_assert(C <= 4, "one mask byte per column in a word");
                                 // Mask byte e = Z and G^2 > thr2: 0 or 1.
-                                const uint32_t mw =
-                                    any & ~all & tbd & ((BX || BQ) ? emw : 0x01010101u);
+                                uint32_t mw = any & ~all & tbd;
+                                if constexpr (BX || BQ) mw &= emw;
                                 mwl = mw;
                                 if constexpr (MODE == SM_SPEC) {
                                     bal = __ballot(mw != 0u);

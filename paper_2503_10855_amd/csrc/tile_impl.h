@@ -179,11 +179,11 @@ __device__ __forceinline__ void tile_body(const ImgArgs& a, const Taps& tp, int 
     const int ncol = lane_out ? (BD ? min(W - cbase, C) : C) : 0;  // output columns
     const bool left_fix = BD && cbase + C == 0;
     bool right_fix[C];
-    uint32_t emw = 0;   // the lane's output columns, as 0/1 bytes
+    uint32_t emw = 0;   // the lane's output columns, as 0xff bytes
 #pragma unroll
     for (int e = 0; e < C; ++e) {
         right_fix[e] = BD && cbase + e == W;
-        emw |= e < ncol ? (1u << (8 * e)) : 0u;
+        emw |= e < ncol ? (0xffu << (8 * e)) : 0u;
     }
 
     const RowSpan msk(S::TO_MASK ? (const void*)a.mask : (const void*)a.src, y0, ylim - y0,
@@ -310,7 +310,7 @@ __device__ __forceinline__ void tile_body(const ImgArgs& a, const Taps& tp, int 
                     if constexpr (S::NEED_Z) {
                         float l[C];
 #pragma unroll
-                        for (int e = 0; e < C; ++e) l[e] = neg_lap_from(ns[e], ew1[e], b1[e]);
+                        for (int e = 0; e < C; ++e) l[e] = lap_from(ns[e], ew1[e], b1[e]);
                         if constexpr (MODE == TM_STAGES) {
                             if (row_out) {
                                 if (so->B) {
@@ -319,11 +319,7 @@ __device__ __forceinline__ void tile_body(const ImgArgs& a, const Taps& tp, int 
                                 }
                                 if (so->L) {
                                     const RowSpan p(so->L, vl, 1, W, 4, W);
-                                    float lv[C];
-#pragma unroll
-                                    for (int e = 0; e < C; ++e)
-                                        lv[e] = lap_from(ns[e], ew1[e], b1[e]);
-                                    store_floats<C>(p, vl, cbase, lv, ncol);
+                                    store_floats<C>(p, vl, cbase, l, ncol);
                                 }
                                 if (so->G) {
                                     const RowSpan p(so->G, vl, 1, W, 4, W);
@@ -335,7 +331,10 @@ __device__ __forceinline__ void tile_body(const ImgArgs& a, const Taps& tp, int 
                             }
                         }
                         if constexpr (BD) edge_cols<C>(l, left_fix, right_fix);
-                        const uint32_t sw = col_sign_bytes<C>(l);   // L > 0
+                        uint32_t sb[C];
+#pragma unroll
+                        for (int e = 0; e < C; ++e) sb[e] = pos_bit(l[e]);
+                        const uint32_t sw = col_bytes<C>(sb);
                         const uint32_t sl = cols_from_left<C>(sw), sr = cols_from_right<C>(sw);
                         uint32_t ho = sw | sl | sr, ha = sw & sl & sr;
                         if constexpr (BD) {
@@ -366,7 +365,7 @@ __device__ __forceinline__ void tile_body(const ImgArgs& a, const Taps& tp, int 
                                     const uint32_t zlo =
                                         (uint32_t)(reinterpret_cast<uintptr_t>(so->Z) +
                                                    (uint64_t)vz * (uint64_t)W) & 3u;
-                                    store_mask<C>(p, vz, (uint32_t)cbase, zw & 0x01010101u, zlo, ncol);
+                                    store_mask<C>(p, vz, (uint32_t)cbase, zw, zlo, ncol);
                                 }
                             }
                             if constexpr (S::TO_MASK) {
