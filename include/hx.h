@@ -241,7 +241,10 @@ hx_status hx_pipeline_get_schedule(const hx_pipeline* p, int64_t height,
  * share one set: such a call on a different stream from the previous one
  * first makes its stream wait for that call's work, so calls on several
  * streams are correct but need not overlap.  (SPECULATE per-image calls use
- * the batch contexts instead.) */
+ * the batch contexts instead.)  A call recorded into a graph (on a stream
+ * under capture) shares that set's planes but not its max slots; replays are
+ * not calls, so the caller orders them against the set's other calls that
+ * may overlap them (on one stream they are in order). */
 hx_status hx_edge_detect(hx_pipeline* p, const hx_image* img, float* d_max,
                          hipStream_t stream);
 

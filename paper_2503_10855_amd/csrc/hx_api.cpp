@@ -305,28 +305,38 @@ static ImgArgs base_args(const hx_image* img, uint32_t* slot, float* d_max) {
 // Does the pipeline hold scratch for `form`?
 static bool has_form(const hx_pipeline* p, int form) { return (p->prm.forms & form) != 0; }
 
-// Is `stream` being captured into a graph (or may it not be asked)?
-static bool is_capturing(hipStream_t stream) {
+// The graph capture a call on `stream` is recorded into: its id, 0 if it runs
+// at once.  (Only the null stream may refuse to say, while another stream is
+// captured; it cannot be captured itself.)
+static unsigned long long capture_id(hipStream_t stream) {
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    return hipStreamIsCapturing(stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone;
+    unsigned long long id = 0;
+    if (hipStreamGetCaptureInfo(stream, &cs, &id) != hipSuccess) {
+        (void)hipGetLastError();
+        return 0;
+    }
+    if (cs == hipStreamCaptureStatusNone) return 0;
+    return id ? id : ~0ull;
 }
 
 // This call's max slot of the pair, *next left at zero for the next call.
 // The fused STORE form's threshold kernel zeroes the other slot (store), so
 // when the previous call left this one at zero it needs no clearing launch;
-// every other form clears both slots first.
-static hipError_t begin_slots(hx_pipeline::ImgScratch& sc, bool store, hipStream_t stream,
-                              uint32_t** slot, uint32_t** next, bool* leaves_zero) {
+// every other form clears both slots first.  A recorded call has one slot,
+// which it clears; it hands none on.
+static hipError_t begin_slots(hx_pipeline* p, hx_pipeline::ImgScratch& sc, bool store,
+                              hipStream_t stream, uint32_t** slot, uint32_t** next) {
+    if (&sc == &p->img_rec) {
+        *slot = sc.slots;
+        *next = nullptr;
+        return launch_fill_u32(sc.slots, 0u, kSlotWords, stream);
+    }
     *slot = sc.slots + sc.parity * kSlotWords;
     *next = sc.slots + (sc.parity ^ 1) * kSlotWords;
     sc.parity ^= 1;
     const bool slot_zero = sc.next_zero;
     sc.next_zero = false;  // until this call's launches are all enqueued
-    // A call recorded into a graph runs later, any number of times: it
-    // clears its slots itself and leaves nothing to the next call.
-    const bool recorded = is_capturing(stream);
-    *leaves_zero = !recorded;
-    if (store && slot_zero && !recorded) return hipSuccess;
+    if (store && slot_zero) return hipSuccess;
     return launch_fill_u32(sc.slots, 0u, 2 * kSlotWords, stream);
 }
 
@@ -340,8 +350,7 @@ static hx_status run_short(hx_pipeline* p, const hx_image* img, float* d_max,
                            const StageOut* so, hx_pipeline::ImgScratch& scr,
                            hipStream_t stream) {
     uint32_t *slot, *next;
-    bool leaves_zero;
-    HX_TRY(begin_slots(scr, true, stream, &slot, &next, &leaves_zero));
+    HX_TRY(begin_slots(p, scr, true, stream, &slot, &next));
     ImgArgs a = base_args(img, slot, d_max);
     a.ways = kSlotWays;
     a.fout = scr.code;
@@ -365,7 +374,7 @@ static hx_status run_short(hx_pipeline* p, const hx_image* img, float* d_max,
     HX_TRY(launch_tile(so ? (int)TM_STAGES : (int)SM_STORE, ks, sc.tile_w / 64, sc.tile_h, a, t,
                        so ? *so : StageOut{}, stream));
     HX_TRY(launch_threshold_code(a, p->prm.thresh_frac, stream, next));
-    scr.next_zero = leaves_zero;
+    scr.next_zero = true;
     return HX_OK;
 }
 
@@ -397,8 +406,7 @@ static hx_status run_image(hx_pipeline* p, const hx_image* img, float* d_max,
     if (s.fusion_depth == 1 && takes_short_form(p, img, s))
         return run_short(p, img, d_max, nullptr, scr, stream);
     uint32_t *slot, *next;
-    bool leaves_zero;
-    HX_TRY(begin_slots(scr, store_fused, stream, &slot, &next, &leaves_zero));
+    HX_TRY(begin_slots(p, scr, store_fused, stream, &slot, &next));
     p->img_last_slot = slot;
     ImgArgs a = base_args(img, slot, d_max);
     const float theta = p->prm.thresh_frac;
@@ -415,7 +423,7 @@ static hx_status run_image(hx_pipeline* p, const hx_image* img, float* d_max,
             HX_TRY(launch_sweep(SM_MASK, ks, c, s.tile_h, a, p->taps, theta, stream));
             if (d_max) HX_TRY(launch_write_max(a, stream));
         }
-        scr.next_zero = leaves_zero;
+        scr.next_zero = true;
         return HX_OK;
     }
     StageBufs b{};
@@ -438,7 +446,7 @@ static hx_status run_image(hx_pipeline* p, const hx_image* img, float* d_max,
             HX_TRY(launch_zero_cross(a, b, b.L, tw1, th1, stream));
         }
         HX_TRY(launch_threshold_zg(a, b, theta, tw1, th1, stream));
-        scr.next_zero = leaves_zero;
+        scr.next_zero = true;
         return HX_OK;
     }
     // Depth 1: one kernel per stage.
@@ -447,22 +455,25 @@ static hx_status run_image(hx_pipeline* p, const hx_image* img, float* d_max,
     HX_TRY(launch_zero_cross(a, b, b.L, s.tile_w, s.tile_h, stream));
     HX_TRY(launch_sobel_max(a, b, s.tile_w, s.tile_h, s.reduce_mode, stream));
     HX_TRY(launch_threshold_zg(a, b, theta, s.tile_w, s.tile_h, stream));
-    scr.next_zero = leaves_zero;
+    scr.next_zero = true;
     return HX_OK;
 }
 
 // Per-image calls share the pipeline's per-image scratch: one on a stream
 // other than the previous one's waits (on the device) for the previous
-// one's work first.
-static hx_status img_order_begin(hx_pipeline* p, hipStream_t stream) {
-    if (p->img_used && p->img_stream != stream)
-        HX_TRY(hipStreamWaitEvent(stream, p->img_ev, 0));
+// one's work first; a recorded one for those before it in its capture.
+static hx_status img_order_begin(hx_pipeline* p, hipStream_t stream, unsigned long long capture) {
+    const hx_pipeline::ImgOrder& o = capture ? p->rec_order : p->img_order;
+    if (o.used && o.stream != stream && o.capture == capture)
+        HX_TRY(hipStreamWaitEvent(stream, o.ev, 0));
     return HX_OK;
 }
-static hx_status img_order_end(hx_pipeline* p, hipStream_t stream) {
-    HX_TRY(hipEventRecord(p->img_ev, stream));
-    p->img_used = true;
-    p->img_stream = stream;
+static hx_status img_order_end(hx_pipeline* p, hipStream_t stream, unsigned long long capture) {
+    hx_pipeline::ImgOrder& o = capture ? p->rec_order : p->img_order;
+    HX_TRY(hipEventRecord(o.ev, stream));
+    o.used = true;
+    o.stream = stream;
+    o.capture = capture;
     return HX_OK;
 }
 
@@ -484,12 +495,13 @@ hx_status run_image_ordered(hx_pipeline* p, const hx_image* img, float* d_max,
         return run_image(p, img, d_max, s, p->img_shared, stream);
     const bool store = s.fusion_depth == 4 ? s.pass_mode == HX_PASS_STORE
                                            : s.fusion_depth == 1 && takes_short_form(p, img, s);
-    if (may_own && store && owns_scratch(p, stream))
+    const unsigned long long capture = capture_id(stream);
+    if (may_own && store && !capture && owns_scratch(p, stream))
         return run_image(p, img, d_max, s, p->img_own, stream);
-    hx_status st = img_order_begin(p, stream);
+    hx_status st = img_order_begin(p, stream, capture);
     if (st != HX_OK) return st;
-    st = run_image(p, img, d_max, s, p->img_shared, stream);
-    hx_status st2 = img_order_end(p, stream);
+    st = run_image(p, img, d_max, s, capture ? p->img_rec : p->img_shared, stream);
+    hx_status st2 = img_order_end(p, stream, capture);
     return st != HX_OK ? st : st2;
 }
 
@@ -740,7 +752,7 @@ static hx_status launch_on(hx_pipeline* p, BatchContext& c, const hx_image* imgs
     TraceRange tr("hx.batch.enqueue");
     // The last kernel completes the context's event itself, except in a
     // recorded call, where run_batched records it.
-    const hipEvent_t done = is_capturing(stream) ? nullptr : c.ev_done;
+    const hipEvent_t done = capture_id(stream) ? nullptr : c.ev_done;
     c.done_set = done != nullptr;
     if (pass == kPassShort) return enqueue_short(p, c, stream, done);
     c.dirty[0] = std::max(c.dirty[0], c.n_ways);
@@ -797,7 +809,7 @@ hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
     int64_t px = 0;
     for (int i = 0; i < n && by_size && px <= kShortBatchPixels; ++i)
         px += imgs[i].height * imgs[i].width;
-    if (by_size && px <= kShortBatchPixels && !p->timing && !is_capturing(stream))
+    if (by_size && px <= kShortBatchPixels && !p->timing && !capture_id(stream))
         pass = kPassShort;
     if (!pass) pass = kBatchPass;
     if (pass < HX_PASS_STORE || pass > kPassShort)
@@ -850,7 +862,7 @@ hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
     c.last_use = ++p->use_clock;
     c.done_set = false;
     hx_status st = HX_OK;
-    if (same && c.in_flight && !p->timing && !is_capturing(stream)) {
+    if (same && c.in_flight && !p->timing && !capture_id(stream)) {
         // Nothing on the host changes: the stream waits for the context's
         // previous call (no wait at all if that is this stream's own).  The
         // host stays at most two large calls ahead of a context: waiting for
@@ -1001,8 +1013,9 @@ static hx_status alloc_scratch(hx_pipeline* p) {
     const int f = p->prm.forms;
     p->plane_elems = plane_capacity(p->prm.max_pixels);
     const size_t pe = (size_t)p->plane_elems;
-    HX_TRY(hipEventCreateWithFlags(&p->img_ev, hipEventDisableTiming));
-    HX_TRY(p->slot1.alloc(4 * kSlotWords * sizeof(uint32_t), m));
+    HX_TRY(hipEventCreateWithFlags(&p->img_order.ev, hipEventDisableTiming));
+    HX_TRY(hipEventCreateWithFlags(&p->rec_order.ev, hipEventDisableTiming));
+    HX_TRY(p->slot1.alloc(5 * kSlotWords * sizeof(uint32_t), m));
     if (f & (HX_FORM_IMAGE | HX_FORM_STAGES | HX_FORM_SRAD))
         HX_TRY(p->planeA.alloc(pe * sizeof(float), m));
     if (f & (HX_FORM_STAGES | HX_FORM_SRAD)) HX_TRY(p->planeL.alloc(pe * sizeof(float), m));
@@ -1019,6 +1032,8 @@ static hx_status alloc_scratch(hx_pipeline* p) {
     p->img_own.slots = p->img_shared.slots + 2 * kSlotWords;
     p->img_own.code = (float*)p->planeOwn.ptr;
     p->img_own.blur = (float*)p->planeOwnB.ptr;
+    p->img_rec = p->img_shared;
+    p->img_rec.slots = p->img_own.slots + 2 * kSlotWords;
     if (f & HX_FORM_STAGES) {
         HX_TRY(p->planeG2.alloc(pe * sizeof(float), m));
         HX_TRY(p->planeZ.alloc(pe, m));
@@ -1137,7 +1152,8 @@ void hx_pipeline_destroy(hx_pipeline* p) {
     p->planeZ.release();
     p->bufPart.release();
     p->srad_part.release();
-    if (p->img_ev) (void)hipEventDestroy(p->img_ev);
+    for (hipEvent_t e : {p->img_order.ev, p->rec_order.ev})
+        if (e) (void)hipEventDestroy(e);
     delete p;
 }
 
@@ -1218,7 +1234,7 @@ hx_status hx_edge_detect(hx_pipeline* p, const hx_image* img, float* d_max,
     // a call recorded into a graph takes STORE, which needs none.
     if (s.fusion_depth == 4 && s.pass_mode == HX_PASS_SPECULATE && !p->forced &&
         !p->prm.pass_mode && !p->tuned.count(shape_class(img->height, img->width)) &&
-        is_capturing(stream))
+        capture_id(stream))
         s = store_schedule(img->height, img->width);
     TraceRange trace("hx.edge_detect");
     logf(2, "per-image call %lldx%lld: %s", (long long)img->height, (long long)img->width,
@@ -1320,16 +1336,18 @@ hx_status hx_edge_detect_stages(hx_pipeline* p, const hx_image* img, float* d_B,
                        img->width < (int64_t(1) << 28) &&
                        plane_need(img->height, img->width) <= p->plane_elems;
     const StageOut so{d_B, d_L, d_G, d_Z};
-    if (sweep && owns_scratch(p, stream))
+    const unsigned long long capture = capture_id(stream);
+    if (sweep && !capture && owns_scratch(p, stream))
         return run_short(p, img, d_max, &so, p->img_own, stream);
-    st = img_order_begin(p, stream);
+    hx_pipeline::ImgScratch& scr = capture ? p->img_rec : p->img_shared;
+    st = img_order_begin(p, stream, capture);
     if (st != HX_OK) return st;
     if (sweep) {
-        st = run_short(p, img, d_max, &so, p->img_shared, stream);
-        hx_status st2 = img_order_end(p, stream);
+        st = run_short(p, img, d_max, &so, scr, stream);
+        hx_status st2 = img_order_end(p, stream, capture);
         return st != HX_OK ? st : st2;
     }
-    st = run_image(p, img, d_max, s, p->img_shared, stream);
+    st = run_image(p, img, d_max, s, scr, stream);
     if (st == HX_OK) {
         ImgArgs a = base_args(img, p->img_last_slot, d_max);
         StageBufs b{};
@@ -1341,7 +1359,7 @@ hx_status hx_edge_detect_stages(hx_pipeline* p, const hx_image* img, float* d_B,
         hipError_t e = launch_export_stages(a, b, d_B, d_L, d_Z, d_G, stream);
         if (e != hipSuccess) st = hip_fail(e, "launch_export_stages");
     }
-    hx_status st2 = img_order_end(p, stream);
+    hx_status st2 = img_order_end(p, stream, capture);
     return st != HX_OK ? st : st2;
 }
 
@@ -1371,7 +1389,8 @@ hx_status hx_srad(hx_pipeline* p, float* d_J, int64_t height, int64_t width, int
         return fail(HX_E_UNSUPPORTED, "SRAD partial sums exceed the pipeline's capacity");
     DeviceGuard g(p->device);
     const int64_t pb = (width + 3) & ~int64_t(3);
-    hx_status st = img_order_begin(p, stream);
+    const unsigned long long capture = capture_id(stream);
+    hx_status st = img_order_begin(p, stream, capture);
     if (st != HX_OK) return st;
     float* jb = (float*)p->planeA.ptr;
     hipError_t e = launch_srad(d_J, jb, pitch, pb, fused ? nullptr : (float*)p->planeL.ptr, pb,
@@ -1382,7 +1401,7 @@ hx_status hx_srad(hx_pipeline* p, float* d_J, int64_t height, int64_t width, int
                              (size_t)pb * sizeof(float), (size_t)width * sizeof(float),
                              (size_t)height, hipMemcpyDeviceToDevice, stream);
     if (e != hipSuccess) st = hip_fail(e, "SRAD launch");
-    hx_status st2 = img_order_end(p, stream);
+    hx_status st2 = img_order_end(p, stream, capture);
     return st != HX_OK ? st : st2;
 }
 

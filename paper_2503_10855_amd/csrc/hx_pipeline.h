@@ -157,11 +157,16 @@ struct hx_pipeline {
     hx::DevBuf planeL;   // L / SRAD's c plane
     hx::DevBuf planeG2, planeZ, bufPart;
     hx::DevBuf srad_part;
-    // Ordering of per-image calls on the shared scratch: each records img_ev
-    // on its stream; a call on another stream waits for it first.
-    hipEvent_t img_ev = nullptr;
-    hipStream_t img_stream = nullptr;
-    bool img_used = false;
+    // Ordering of per-image calls on the shared scratch: each records the
+    // event on its stream; a call on another stream waits for it first.
+    // Calls recorded into a graph are ordered among those of one capture.
+    struct ImgOrder {
+        hipEvent_t ev = nullptr;
+        hipStream_t stream = nullptr;
+        bool used = false;
+        unsigned long long capture = 0;   // the last call's (0: not recorded)
+    };
+    ImgOrder img_order, rec_order;
     // Scratch of the STORE forms: two max slots (each call uses one and
     // leaves the other at zero for the next call; next_zero says the
     // previous call did) and the code plane, and for blur sizes above 7 the
@@ -174,7 +179,11 @@ struct hx_pipeline {
         float* blur = nullptr;
     };
     ImgScratch img_shared;
-    uint32_t* img_last_slot = nullptr;   // of the last call on img_shared
+    // Of calls recorded into a graph, which run any number of times at any
+    // point between the others: the shared planes, and one max slot that no
+    // other call uses and each recorded call clears itself.
+    ImgScratch img_rec;
+    uint32_t* img_last_slot = nullptr;   // of the last call on img_shared or img_rec
     // A set of its own for STORE-form calls on one stream, the first that
     // makes one: no other stream's call ever uses it, so its calls are
     // ordered by their stream alone and record no event (one costs about 3
