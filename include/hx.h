@@ -262,7 +262,12 @@ hx_status hx_edge_detect(hx_pipeline* p, const hx_image* img, float* d_max,
  * scratch sets each, so calls on different streams overlap; a call whose
  * context is still in use waits for it: a repeated batch on the device
  * (the host stays at most two large calls ahead), a new one on the host,
- * where its descriptor table is rebuilt.  A batch with more
+ * where its descriptor table is rebuilt.  A call recorded into a graph
+ * takes its context out of the rotation for the pipeline's life, so that its
+ * replays never meet another call there (replays of one graph must not
+ * overlap each other); with one context left, and for a batch beyond a
+ * table, it is recorded image by image instead, without a context, and its
+ * replays must not overlap those of other such calls.  A batch with more
  * tiles than a context's descriptor table holds (only possible with many
  * images a few pixels wide or tall) runs as several launches in turn. */
 hx_status hx_edge_detect_batched(hx_pipeline* p, const hx_image* imgs,

@@ -345,7 +345,7 @@ void k_batch_p2s(const uint8_t* __restrict__ table, Taps tp) {
     const TableView tv = view(table);
     const int lane = lane_id();
     const int k = xcd_remap(blockIdx.x, gridDim.x);
-    {
+    if (k < tv.hdr.n_items2) {
         const BatchItem it = tv.item(tv.items2, k);
         const int n_listed = (int)as_global(tv.hdr.cand_n)[k];
         const ImgArgs a = tv.imgs[it.image];

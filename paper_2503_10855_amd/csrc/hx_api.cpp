@@ -699,19 +699,31 @@ static hx_status build_table(hx_pipeline* p, BatchContext& c, const hx_image* im
     return HX_OK;
 }
 
-// One image whose tiles alone exceed a context's table: the per-image
-// RECOMPUTE form (two sweeps and no tables), with the image's max in the
-// context's first slot.  Same bits as the batched passes.
-static hx_status run_oversized(hx_pipeline* p, BatchContext& c, const hx_image& im,
-                               float* d_max, hipStream_t stream) {
-    ImgArgs a = base_args(&im, c.slots, d_max);
-    c.dirty[0] = std::max(c.dirty[0], 1);
+// One image without a table: the per-image RECOMPUTE form (two sweeps), with
+// its max in the word `slot`.  Same bits as the batched passes.
+static hx_status run_tableless(hx_pipeline* p, uint32_t* slot, const hx_image& im, float* d_max,
+                               hipStream_t stream) {
+    ImgArgs a = base_args(&im, slot, d_max);
     const int ks = p->prm.ksize, cw = batch_sweep_c(), ty = batch_sweep_ty();
     HX_TRY(launch_fill_u32(a.slot, 0u, 1, stream));
     HX_TRY(launch_sweep(SM_MAXONLY, ks, cw, ty, a, p->taps, p->prm.thresh_frac, stream));
     HX_TRY(launch_sweep(SM_MASK, ks, cw, ty, a, p->taps, p->prm.thresh_frac, stream));
     if (d_max) HX_TRY(launch_write_max(a, stream));
     return HX_OK;
+}
+
+// One image whose tiles alone exceed a context's table, with its max in the
+// context's first slot.
+static hx_status run_oversized(hx_pipeline* p, BatchContext& c, const hx_image& im,
+                               float* d_max, hipStream_t stream) {
+    c.dirty[0] = std::max(c.dirty[0], 1);
+    return run_tableless(p, c.slots, im, d_max, stream);
+}
+
+int free_contexts(const hx_pipeline* p) {
+    int n = 0;
+    for (int i = 0; i < p->n_ctx; ++i) n += !p->ctx[i].recorded;
+    return n;
 }
 
 // The two launches of a small batch.  They use whichever set of the
@@ -740,32 +752,61 @@ static hx_status enqueue_short(hx_pipeline* p, BatchContext& c, hipStream_t stre
 }
 
 // Launch a batch that fits one context on context c, whose table holds it
-// already if `same`.
+// already if `same`.  done: completed by the last kernel itself (nullable).
 static hx_status launch_on(hx_pipeline* p, BatchContext& c, const hx_image* imgs, int32_t n,
                            float* d_max, int pass, const SweepGeom& geo, bool same,
-                           hipStream_t stream) {
+                           hipStream_t stream, hipEvent_t done) {
     if (!same) {
         TraceRange tr("hx.batch.table");
         hx_status st = build_table(p, c, imgs, n, d_max, pass, geo, stream);
         if (st != HX_OK) return st;
     }
     TraceRange tr("hx.batch.enqueue");
-    // The last kernel completes the context's event itself, except in a
-    // recorded call, where run_batched records it.
-    const hipEvent_t done = capture_id(stream) ? nullptr : c.ev_done;
-    c.done_set = done != nullptr;
+    const bool timed = p->timing && !c.recorded;
     if (pass == kPassShort) return enqueue_short(p, c, stream, done);
     c.dirty[0] = std::max(c.dirty[0], c.n_ways);
     // The three kernels are launched one by one, also for a repeated batch:
     // replaying them as a captured graph cost 6 to 8 us more per call (16
     // thumbnails 28.5 against 21.2 us, 2 x 1080p 36.1 against 28.9).
-    HX_TRY(enqueue_phases(p, c, pass, stream, p->timing, done));
-    if (p->timing) p->last_timed_ctx = (int)(&c - p->ctx);
+    HX_TRY(enqueue_phases(p, c, pass, stream, timed, done));
+    if (timed) p->last_timed_ctx = (int)(&c - p->ctx);
     logf(2, "batch context %d: %d images, items %lld / %lld / %lld (pass 1 / 2 / 0), %s%s",
          (int)(&c - p->ctx), n, (long long)c.n_items[1], (long long)c.n_items[2],
          (long long)c.n_items[0], same ? "table reused" : "table built",
-         p->timing ? ", timed" : "");
+         timed ? ", timed" : "");
     return HX_OK;
+}
+
+// A batched call recorded into a graph.  The graph keeps the grids and the
+// addresses of a context's table (with the copy that fills it), list and
+// slots, so the context leaves the rotation; the one that eager calls need,
+// and a batch beyond a table, are left alone: then image by image, with
+// nothing in the graph that a later call rewrites.
+static hx_status record_batch(hx_pipeline* p, const hx_image* imgs, int32_t n, float* d_max,
+                              int pass, const SweepGeom& geo, hipStream_t stream,
+                              unsigned long long capture) {
+    ImgWork tot;
+    for (int i = 0; i < n; ++i) {
+        const ImgWork w = img_work(imgs[i], pass, geo);
+        tot.tiles += w.tiles;
+        tot.p2 += w.p2;
+        tot.p0 += w.p0;
+        tot.code += w.code;
+    }
+    BatchContext* c = nullptr;
+    for (int i = 0; i < p->n_ctx; ++i)
+        if (!p->ctx[i].recorded && (!c || p->ctx[i].last_use < c->last_use)) c = &p->ctx[i];
+    if (c && free_contexts(p) > 1 && fits(p->caps, tot, pass)) {
+        hx_status st = ctx_wait(*c);
+        if (st != HX_OK) return st;
+        c->recorded = true;
+        return launch_on(p, *c, imgs, n, d_max, pass, geo, false, stream, nullptr);
+    }
+    hx_status st = img_order_begin(p, stream, capture);
+    for (int i = 0; i < n && st == HX_OK; ++i)
+        st = run_tableless(p, p->img_rec.slots, imgs[i], d_max ? d_max + i : nullptr, stream);
+    hx_status st2 = img_order_end(p, stream, capture);
+    return st != HX_OK ? st : st2;
 }
 
 BatchKey batch_key(const hx_image* imgs, int32_t n) {
@@ -789,6 +830,7 @@ constexpr int64_t kNarrowPixels = int64_t(1) << 19;
 hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
                       float* d_max, int pass, int ty, hipStream_t stream, int ctx) {
     const int ks = p->prm.ksize;
+    const unsigned long long capture = capture_id(stream);
     TraceRange trace("hx.batch");
     const char* ty_from = ty ? "fixed" : "default";
     {
@@ -809,7 +851,7 @@ hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
     int64_t px = 0;
     for (int i = 0; i < n && by_size && px <= kShortBatchPixels; ++i)
         px += imgs[i].height * imgs[i].width;
-    if (by_size && px <= kShortBatchPixels && !p->timing && !capture_id(stream))
+    if (by_size && px <= kShortBatchPixels && !p->timing && !capture)
         pass = kPassShort;
     if (!pass) pass = kBatchPass;
     if (pass < HX_PASS_STORE || pass > kPassShort)
@@ -831,6 +873,7 @@ hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
     int pick = -1, oldest_match = -1, oldest = -1;
     for (int i = 0; i < p->n_ctx; ++i) {
         BatchContext& c = p->ctx[i];
+        if (c.recorded) continue;
         if (holds(c)) {
             if (!c.in_flight || hipEventQuery(c.ev_done) == hipSuccess) {
                 pick = i;
@@ -841,8 +884,11 @@ hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
         if (oldest < 0 || c.last_use < p->ctx[oldest].last_use) oldest = i;
     }
     if (pick < 0) pick = oldest_match >= 0 ? oldest_match : oldest;
-    if (ctx >= 0) pick = p->n_ctx > 0 ? ctx % p->n_ctx : -1;
-    const bool same = pick >= 0 && holds(p->ctx[pick]);
+    if (ctx >= 0 && pick >= 0) {
+        int left = ctx % free_contexts(p);
+        for (pick = 0; p->ctx[pick].recorded || left > 0; ++pick) left -= !p->ctx[pick].recorded;
+    }
+    const bool same = pick >= 0 && !capture && holds(p->ctx[pick]);
     if (same) ty = p->ctx[pick].last_ty;
     SweepGeom geo{ks, px <= kNarrowPixels ? 1 : 2, kShortBatchRows};
     if (pass != kPassShort) {
@@ -858,11 +904,11 @@ hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
     if (pass == HX_PASS_STORE && !has_form(p, HX_FORM_BATCH_STORE))
         return fail(HX_E_UNSUPPORTED,
                     "batched STORE needs a pipeline created with HX_FORM_BATCH_STORE");
+    if (capture) return record_batch(p, imgs, n, d_max, pass, geo, stream, capture);
     BatchContext& c = p->ctx[pick];
     c.last_use = ++p->use_clock;
-    c.done_set = false;
     hx_status st = HX_OK;
-    if (same && c.in_flight && !p->timing && !capture_id(stream)) {
+    if (same && c.in_flight && !p->timing) {
         // Nothing on the host changes: the stream waits for the context's
         // previous call (no wait at all if that is this stream's own).  The
         // host stays at most two large calls ahead of a context: waiting for
@@ -911,7 +957,7 @@ hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
              fits(p->caps, tot, pass) ? "" : ", split into groups");
     }
     if (fits(p->caps, tot, pass)) {
-        st = launch_on(p, c, imgs, n, d_max, pass, geo, same, stream);
+        st = launch_on(p, c, imgs, n, d_max, pass, geo, same, stream, c.ev_done);
         if (st != HX_OK) return st;
         c.default_ty = want_ty == 0;
     } else {
@@ -942,13 +988,12 @@ hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
                 ++i;
             } else {
                 st = launch_on(p, c, imgs + i, j - i, d_max ? d_max + i : nullptr, pass, geo,
-                               false, stream);
+                               false, stream, nullptr);
                 c.last_pass = -1;
                 i = j;
             }
             if (st != HX_OK) return st;
             HX_TRY(hipEventRecord(c.ev_done, stream));
-            c.done_set = true;
             c.in_flight = true;
             if (i < n) {
                 st = ctx_wait(c);
@@ -956,7 +1001,6 @@ hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
             }
         }
     }
-    if (!c.done_set) HX_TRY(hipEventRecord(c.ev_done, stream));
     c.in_flight = true;
     return HX_OK;
 }

@@ -94,8 +94,10 @@ struct BatchContext {
     hipEvent_t ev_done = nullptr;
     hipEvent_t ev_prev = nullptr;   // of the call before, or complete
     hipEvent_t ev_t[5] = {};    // timing mode
-    bool done_set = false;      // this call's last launch completes ev_done
     bool in_flight = false;
+    // A call recorded into a graph reads this context's table and scratch at
+    // every replay: no other call may ever use them.
+    bool recorded = false;
     uint64_t last_use = 0;      // the pipeline's call counter at the last use
     // Leading words of each set of max slots that a call may have left
     // non-zero, and those the table's images use.
@@ -228,10 +230,14 @@ constexpr int kBatchPass = HX_PASS_SPECULATE;
 // the batch's class, else SPECULATE / the default tile height.  ctx >= 0
 // runs on that batch context (waiting for its previous batch) instead of
 // the one the context policy picks; the batch autotuner uses it to keep
-// one batch in flight per context.
+// one batch in flight per context.  A call recorded into a graph keeps its
+// context for good; when only one is left for the calls that run at once, it
+// runs image by image without one.
 hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
                       float* d_max, int pass_mode, int ty, hipStream_t stream,
                       int ctx = -1);
+// Contexts that no recorded call holds.
+int free_contexts(const hx_pipeline* p);
 // Wait for a context's last launch.
 hx_status ctx_wait(BatchContext& c);
 

@@ -237,7 +237,7 @@ hx_status hx_autotune_batch(hx_pipeline* p, const hx_image* imgs, int32_t n,
     // the throughput trials keep that many calls in flight, as a caller
     // feeding batches on as many streams does.  All calls write the same masks with the same bits;
     // after the last one the masks hold the result of any of them.
-    const int S = std::max(1, std::min(p->n_ctx, hx_pipeline::kMaxContexts));
+    const int S = std::max(1, std::min(free_contexts(p), hx_pipeline::kMaxContexts));
     hipStream_t st_[hx_pipeline::kMaxContexts] = {};
     hipEvent_t done_[hx_pipeline::kMaxContexts] = {};
     hipEvent_t e0 = nullptr, e1 = nullptr;

@@ -102,3 +102,97 @@ def test_recorded_calls_on_two_streams_of_one_capture(hx):
             torch.cuda.synchronize()
             assert torch.equal(dm, want_m)
             assert all(torch.equal(m, r) for m, r in zip(masks, want))
+
+
+@pytest.mark.parametrize("contexts,graphs", [(1, 1), (2, 2), (4, 2)])
+@pytest.mark.parametrize("form", ["auto", "recompute", "store", "large"])
+def test_eager_batches_between_replays_of_a_batch(hx, contexts, graphs, form):
+    """Batched calls recorded into graphs (more of them than contexts can be
+    spared, too), replayed on new contents between eager calls on more
+    batches than there are contexts, of other sizes and forms: a replay's
+    table and scratch are its own."""
+    shapes = [(1080, 1920)] * 4 if form == "large" else [(200, 300), (64, 64), (333, 251)]
+    kind = {"recompute": hx.PASS_RECOMPUTE, "store": hx.PASS_STORE}.get(form)
+    sets = [[torch.from_numpy(synth.image(h, w, 413 + s, i)).cuda() * sc
+             for i, (h, w) in enumerate(shapes)] for s, sc in enumerate((BRIGHT, DARK, 1.0))]
+    others = [[torch.from_numpy(synth.image(50 + 90 * b + i, 700 - 80 * b, 416, i)).cuda() * DARK
+               for i in range(1 + 7 * (b % 3))] for b in range(6)]
+    n_max = max(len(s) for s in sets + others)
+    with hx.Pipeline(theta=THETA, max_pixels=1 << 24, max_images=n_max,
+                     batch_contexts=contexts) as p:
+        def batched(srcs, **kw):
+            dm = torch.zeros(len(srcs), device="cuda")
+            return p.edge_detect_batched(srcs, dmax=dm, **kw), dm
+
+        p.set_schedule(64, 16, 1)
+        want = []
+        for srcs in sets + others:
+            dm = torch.zeros(len(srcs), device="cuda")
+            want.append(([p.edge_detect(s, dmax=dm[i:i + 1]) for i, s in enumerate(srcs)], dm))
+        p.sync()
+
+        def check(got, i):
+            torch.cuda.synchronize()
+            assert torch.equal(got[1], want[i][1]), i
+            assert all(torch.equal(a, b) for a, b in zip(got[0], want[i][0])), i
+
+        p.set_schedule(*((256, 32, 4, kind) if kind else ()))
+        check(batched(sets[0]), 0)
+        recs = []
+        for _ in range(graphs):
+            x = [torch.empty_like(s) for s in sets[0]]
+            masks = [torch.zeros(s.shape, dtype=torch.uint8, device="cuda") for s in x]
+            dm = torch.zeros(len(x), device="cuda")
+            torch._foreach_copy_(x, sets[1])
+            g = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(g):
+                p.edge_detect_batched(x, masks, dmax=dm)
+            recs.append((g, x, masks, dm))
+        p.set_schedule()
+        side = torch.cuda.Stream()
+        for rep in range(3):
+            for j, (g, x, masks, dm) in enumerate(recs):
+                for i in (0, 1, 2):
+                    torch._foreach_copy_(x, sets[i])
+                    dm.fill_(-1.0)
+                    print(f"{form} {contexts} contexts graph {j} replay {rep} set {i}", flush=True)
+                    g.replay()
+                    check((masks, dm), i)
+                    for b in range(6):
+                        with torch.cuda.stream(side if b % 2 else torch.cuda.default_stream()):
+                            got = batched(others[b], stream=torch.cuda.current_stream())
+                        check(got, 3 + b)
+                    check(batched(sets[(i + 1) % 3]), (i + 1) % 3)
+        print("tuner beside a recorded call", flush=True)
+        p.autotune_batch(sets[2])
+        for g, x, masks, dm in recs:
+            torch._foreach_copy_(x, sets[0])
+            g.replay()
+            check((masks, dm), 0)
+
+
+def test_recorded_per_image_speculate(hx):
+    """A fixed SPECULATE per-image call, recorded more often than there are
+    contexts, with eager calls of the same form between the replays."""
+    h, w = 500, 777
+    srcs = images(h, w, 417)
+    with hx.Pipeline(theta=THETA, max_pixels=h * w, max_images=1, batch_contexts=2,
+                     pass_mode=hx.PASS_SPECULATE) as p:
+        want_m = torch.zeros(4, device="cuda")
+        want = [p.edge_detect(s, dmax=want_m[i:i + 1]) for i, s in enumerate(srcs)]
+        p.sync()
+        masks = [torch.zeros_like(m) for m in want]
+        dm = torch.zeros(4, device="cuda")
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            for i, s in enumerate(srcs):
+                p.edge_detect(s, masks[i], dmax=dm[i:i + 1])
+        em = torch.zeros(1, device="cuda")
+        for rep in range(4):
+            print(f"replay {rep}", flush=True)
+            dm.fill_(-1.0)
+            g.replay()
+            e = p.edge_detect(srcs[rep], dmax=em)
+            torch.cuda.synchronize()
+            assert torch.equal(dm, want_m) and em[0] == want_m[rep] and torch.equal(e, want[rep])
+            assert all(torch.equal(m, r) for m, r in zip(masks, want))
