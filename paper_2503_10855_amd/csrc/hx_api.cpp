@@ -830,6 +830,9 @@ constexpr int64_t kNarrowPixels = int64_t(1) << 19;
 hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
                       float* d_max, int pass, int ty, hipStream_t stream, int ctx) {
     const int ks = p->prm.ksize;
+    // kPassShort is this function's own choice, never a caller's.
+    if (pass < HX_PASS_AUTO || pass > HX_PASS_SPECULATE)
+        return fail(HX_E_INVALID, "pass_mode %d unknown", pass);
     const unsigned long long capture = capture_id(stream);
     TraceRange trace("hx.batch");
     const char* ty_from = ty ? "fixed" : "default";
@@ -854,8 +857,6 @@ hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
     if (by_size && px <= kShortBatchPixels && !p->timing && !capture)
         pass = kPassShort;
     if (!pass) pass = kBatchPass;
-    if (pass < HX_PASS_STORE || pass > kPassShort)
-        return fail(HX_E_INVALID, "pass_mode %d unknown", pass);
     std::unique_lock<std::mutex> lk(p->batch_mu);
     // Which context: one that already holds this batch (its table is reused
     // as it is) and is idle; else the oldest of those holding it; else the
