@@ -378,12 +378,19 @@ static hx_status run_short(hx_pipeline* p, const hx_image* img, float* d_max,
     return HX_OK;
 }
 
+// Can run_short address the image's rows and its own planes'?  (Crops of very
+// wide parents and images of some 30 million columns it cannot; the stage
+// kernels take those.)
+static bool short_form_fits(const hx_pipeline* p, const hx_image* img) {
+    return tile_rows_fit(p->prm.ksize, img->height,
+                         std::max(img->src_pitch, round4(img->width)));
+}
+
 // Does the depth-1 schedule s, chosen and not asked for, stand for run_short
-// (a blur size without fused sweeps)?  Its planes' rows are addressed with
-// 32 bits.
+// (a blur size without fused sweeps)?
 static bool takes_short_form(const hx_pipeline* p, const hx_image* img, const hx_schedule& s) {
     return !p->forced && !p->prm.fusion_depth && !fused_ks(p->prm.ksize) &&
-           s.reduce_mode == HX_REDUCE_TREE && img->width < (int64_t(1) << 28);
+           s.reduce_mode == HX_REDUCE_TREE && short_form_fits(p, img);
 }
 
 static hx_status run_image(hx_pipeline* p, const hx_image* img, float* d_max,
@@ -1377,8 +1384,7 @@ hx_status hx_edge_detect_stages(hx_pipeline* p, const hx_image* img, float* d_B,
     if (s.fusion_depth == 3 && d_B)
         return fail(HX_E_UNSUPPORTED, "fusion depth 3 keeps B on chip: pass d_B = NULL");
     const bool as_asked = p->forced && p->forced_sched.fusion_depth <= 3;
-    const bool sweep = !as_asked && has_form(p, HX_FORM_STAGES) &&
-                       img->width < (int64_t(1) << 28) &&
+    const bool sweep = !as_asked && has_form(p, HX_FORM_STAGES) && short_form_fits(p, img) &&
                        plane_need(img->height, img->width) <= p->plane_elems;
     const StageOut so{d_B, d_L, d_G, d_Z};
     const unsigned long long capture = capture_id(stream);

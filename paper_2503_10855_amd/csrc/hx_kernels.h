@@ -113,6 +113,16 @@ struct SweepGeom {
 // then the faster one.
 constexpr int kShortTile = 16;
 
+// The short sweep addresses the rows of a tile, its halo among them, with
+// 32-bit byte offsets from the first: do those of an H-row plane with rows of
+// `pitch` floats fit?  (The fused forms always take sweeps, which have that
+// bound in common, on taller tiles the long one's more tightly.)
+inline bool tile_rows_fit(int ks, int64_t H, int64_t pitch) {
+    const int64_t most = kShortTile + 2 * (ks / 2 + 2);
+    const int64_t rows = H < most ? H : most;
+    return pitch <= ((int64_t(1) << 30) - 1) / rows;
+}
+
 // Is (ks, c, ty) one of the compiled sweep shapes?
 bool sweep_supported(int ks, int c, int ty);
 
