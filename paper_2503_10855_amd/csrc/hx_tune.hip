@@ -149,8 +149,11 @@ hx_status hx_autotune(hx_pipeline* p, int64_t height, int64_t width, const char*
     hx_schedule best{};
     float best_ms = 1e30f;
     hx_status st = HX_OK;
+    // Each candidate as if forced: a depth 1 that is only chosen stands for
+    // another form at the blur sizes without sweeps.
     const bool was_forced = p->forced;
-    p->forced = false;
+    const hx_schedule was_sched = p->forced_sched;
+    p->forced = true;
     struct Trial {
         hx_schedule s;
         float ms;
@@ -158,6 +161,7 @@ hx_status hx_autotune(hx_pipeline* p, int64_t height, int64_t width, const char*
     std::vector<Trial> trials;
     for (const hx_schedule& c : candidates(p->prm.ksize)) {
         if (validate_schedule(p, c) != HX_OK) continue;
+        p->forced_sched = c;
         // One warm-up call (allocates scratch), then the fastest of three.
         st = run_image_ordered(p, &im, nullptr, c, s, false);
         if (st != HX_OK) break;
@@ -184,6 +188,7 @@ hx_status hx_autotune(hx_pipeline* p, int64_t height, int64_t width, const char*
         }
     }
     p->forced = was_forced;
+    p->forced_sched = was_sched;
     e = hipStreamSynchronize(s);
     cleanup();
     if (st != HX_OK) return st;
