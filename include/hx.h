@@ -185,8 +185,9 @@ void hx_pipeline_destroy(hx_pipeline* p);
 hx_status hx_pipeline_sync(hx_pipeline* p);
 
 /* Timing mode, for benchmarks.  While enabled, batched calls launch their
- * kernels (reset, [pass 0,] pass 1, pass 2) bracketed with HIP events on
- * the call's stream.
+ * kernels (reset, [pass 0,] pass 1, pass 2; small batches: the maxima as
+ * pass 1, the masks as pass 2) bracketed with HIP events on the call's
+ * stream.
  * hx_pipeline_last_timing waits for the last batched call and returns the
  * durations in milliseconds of its kernels in ms[0..3]: reset, pass 1,
  * pass 2, and pass 0 (SPECULATE only, 0 otherwise; it runs between the

@@ -737,9 +737,10 @@ int free_contexts(const hx_pipeline* p) {
 // The two launches of a small batch.  They use whichever set of the
 // context's max slots is known to be zero and leave the other one zero.
 static hx_status enqueue_short(hx_pipeline* p, BatchContext& c, hipStream_t stream,
-                               hipEvent_t done) {
+                               bool timed, hipEvent_t done) {
     int set = c.dirty[0] == 0 ? 0 : 1;
     const int64_t words = p->caps.ways * p->caps.slot_step;   // of one set
+    if (timed) HX_TRY(hipEventRecord(c.ev_t[0], stream));
     if (c.dirty[set] != 0) {
         HX_TRY(launch_fill_u32(c.slots + set * words, 0u, words, stream));
         c.dirty[set] = 0;
@@ -754,29 +755,40 @@ static hx_status enqueue_short(hx_pipeline* p, BatchContext& c, hipStream_t stre
     s.nzero = c.dirty[1 - set];
     s.theta = p->prm.thresh_frac;
     c.dirty[set] = c.n_ways;
-    HX_TRY(launch_batch_short(p->prm.ksize, c.last_c, s, p->taps, stream, done));
+    if (timed) {
+        HX_TRY(hipEventRecord(c.ev_t[1], stream));
+        HX_TRY(hipEventRecord(c.ev_t[4], stream));
+    }
+    HX_TRY(launch_batch_short(p->prm.ksize, c.last_c, 1, s, p->taps, stream));
+    if (timed) HX_TRY(hipEventRecord(c.ev_t[2], stream));
+    HX_TRY(launch_batch_short(p->prm.ksize, c.last_c, 2, s, p->taps, stream, done));
+    if (timed) HX_TRY(hipEventRecord(c.ev_t[3], stream));
     c.dirty[1 - set] = 0;
     return HX_OK;
 }
 
 // Launch a batch that fits one context on context c, whose table holds it
-// already if `same`.  done: completed by the last kernel itself (nullable).
+// already if `same`.  timed: between timing events.  done: completed by the
+// last kernel itself (nullable).
 static hx_status launch_on(hx_pipeline* p, BatchContext& c, const hx_image* imgs, int32_t n,
                            float* d_max, int pass, const SweepGeom& geo, bool same,
-                           hipStream_t stream, hipEvent_t done) {
+                           hipStream_t stream, bool timed, hipEvent_t done) {
     if (!same) {
         TraceRange tr("hx.batch.table");
         hx_status st = build_table(p, c, imgs, n, d_max, pass, geo, stream);
         if (st != HX_OK) return st;
     }
     TraceRange tr("hx.batch.enqueue");
-    const bool timed = p->timing && !c.recorded;
-    if (pass == kPassShort) return enqueue_short(p, c, stream, done);
-    c.dirty[0] = std::max(c.dirty[0], c.n_ways);
-    // The three kernels are launched one by one, also for a repeated batch:
+    // The kernels are launched one by one, also for a repeated batch:
     // replaying them as a captured graph cost 6 to 8 us more per call (16
     // thumbnails 28.5 against 21.2 us, 2 x 1080p 36.1 against 28.9).
-    HX_TRY(enqueue_phases(p, c, pass, stream, timed, done));
+    if (pass == kPassShort) {
+        hx_status st = enqueue_short(p, c, stream, timed, done);
+        if (st != HX_OK) return st;
+    } else {
+        c.dirty[0] = std::max(c.dirty[0], c.n_ways);
+        HX_TRY(enqueue_phases(p, c, pass, stream, timed, done));
+    }
     if (timed) p->last_timed_ctx = (int)(&c - p->ctx);
     logf(2, "batch context %d: %d images, items %lld / %lld / %lld (pass 1 / 2 / 0), %s%s",
          (int)(&c - p->ctx), n, (long long)c.n_items[1], (long long)c.n_items[2],
@@ -808,7 +820,7 @@ static hx_status record_batch(hx_pipeline* p, const hx_image* imgs, int32_t n, f
         hx_status st = ctx_wait(*c);
         if (st != HX_OK) return st;
         c->recorded = true;
-        return launch_on(p, *c, imgs, n, d_max, pass, geo, false, stream, nullptr);
+        return launch_on(p, *c, imgs, n, d_max, pass, geo, false, stream, false, nullptr);
     }
     hx_status st = img_order_begin(p, stream, capture);
     for (int i = 0; i < n && st == HX_OK; ++i)
@@ -838,6 +850,7 @@ constexpr int64_t kNarrowPixels = int64_t(1) << 19;
 hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
                       float* d_max, int pass, int ty, hipStream_t stream, int ctx) {
     const int ks = p->prm.ksize;
+    const bool timed = p->timing;
     // kPassShort is this function's own choice, never a caller's.
     if (pass < HX_PASS_AUTO || pass > HX_PASS_SPECULATE)
         return fail(HX_E_INVALID, "pass_mode %d unknown", pass);
@@ -862,8 +875,7 @@ hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
     int64_t px = 0;
     for (int i = 0; i < n && by_size && px <= kShortBatchPixels; ++i)
         px += imgs[i].height * imgs[i].width;
-    if (by_size && px <= kShortBatchPixels && !p->timing && !capture)
-        pass = kPassShort;
+    if (by_size && px <= kShortBatchPixels && !capture) pass = kPassShort;
     if (!pass) pass = kBatchPass;
     std::unique_lock<std::mutex> lk(p->batch_mu);
     // Which context: one that already holds this batch (its table is reused
@@ -917,7 +929,7 @@ hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
     BatchContext& c = p->ctx[pick];
     c.last_use = ++p->use_clock;
     hx_status st = HX_OK;
-    if (same && c.in_flight && !p->timing) {
+    if (same && c.in_flight && !timed) {
         // Nothing on the host changes: the stream waits for the context's
         // previous call (no wait at all if that is this stream's own).  The
         // host stays at most two large calls ahead of a context: waiting for
@@ -966,7 +978,7 @@ hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
              fits(p->caps, tot, pass) ? "" : ", split into groups");
     }
     if (fits(p->caps, tot, pass)) {
-        st = launch_on(p, c, imgs, n, d_max, pass, geo, same, stream, c.ev_done);
+        st = launch_on(p, c, imgs, n, d_max, pass, geo, same, stream, timed, c.ev_done);
         if (st != HX_OK) return st;
         c.default_ty = want_ty == 0;
     } else {
@@ -997,7 +1009,7 @@ hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
                 ++i;
             } else {
                 st = launch_on(p, c, imgs + i, j - i, d_max ? d_max + i : nullptr, pass, geo,
-                               false, stream, nullptr);
+                               false, stream, timed, nullptr);
                 c.last_pass = -1;
                 i = j;
             }

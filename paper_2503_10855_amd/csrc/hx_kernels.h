@@ -241,8 +241,9 @@ int batch_p2_rows(int64_t W);
 // Zero the table's images' max slots; grid sized for max_images.
 // SPECULATE batches do not need it (pass 0 clears them).
 hipError_t launch_batch_reset(const void* d_table, int max_images, hipStream_t s);
-// The two launches of the form of small batches (an internal pass structure,
-// beyond HX_PASS_*), on tiles of c = 1 or 2 columns per lane by 8 rows.
+// One launch (phase 1: the maxima, 2: the masks) of the form of small batches
+// (an internal pass structure, beyond HX_PASS_*), on tiles of c = 1 or 2
+// columns per lane by 8 rows.
 constexpr int kPassShort = 4;
 constexpr int kShortBatchRows = 8;
 struct ShortArgs {
@@ -254,7 +255,7 @@ struct ShortArgs {
     int64_t set;              // words from ImgArgs::slot to the ones it uses
     float theta;
 };
-hipError_t launch_batch_short(int ks, int c, const ShortArgs& s, const Taps& t,
+hipError_t launch_batch_short(int ks, int c, int phase, const ShortArgs& s, const Taps& t,
                               hipStream_t stream, hipEvent_t done = nullptr);
 // One pass (phase 0, 1 or 2) over the table's `items` items of that phase,
 // ty the batch's tile height.  Phase 0 exists for SPECULATE only.  done

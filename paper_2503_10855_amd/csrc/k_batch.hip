@@ -62,18 +62,15 @@ static hipError_t launch(const void* k, int64_t grid, void** args, int lds, hipS
                               0);
 }
 
-hipError_t launch_batch_short(int ks, int c, const ShortArgs& s, const Taps& t,
+hipError_t launch_batch_short(int ks, int c, int phase, const ShortArgs& s, const Taps& t,
                               hipStream_t stream, hipEvent_t done) {
+    const void* k = batch_kernel_ptr(ks, kPassShort, phase, c == 1);
+    if (!k || s.n < 1 || (c != 1 && c != 2) || phase < 1 || phase > 2)
+        return hipErrorInvalidValue;
     ShortArgs sc = s;
     Taps tc = t;
     void* args[] = {(void*)&sc, (void*)&tc};
-    for (int phase = 1; phase <= 2; ++phase) {
-        const void* k = batch_kernel_ptr(ks, kPassShort, phase, c == 1);
-        if (!k || s.n < 1 || (c != 1 && c != 2)) return hipErrorInvalidValue;
-        hipError_t e = launch(k, s.n, args, 0, stream, phase == 2 ? done : nullptr);
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    return launch(k, s.n, args, 0, stream, done);
 }
 
 hipError_t launch_batch_phase(int ks, int pass_mode, int phase, int ty, int64_t items,
