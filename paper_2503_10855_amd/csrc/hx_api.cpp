@@ -848,9 +848,10 @@ constexpr int64_t kShortBatchPixels = int64_t(6) << 20;
 constexpr int64_t kNarrowPixels = int64_t(1) << 19;
 
 hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
-                      float* d_max, int pass, int ty, hipStream_t stream, int ctx) {
+                      float* d_max, int pass, int ty, hipStream_t stream, int ctx,
+                      bool count) {
     const int ks = p->prm.ksize;
-    const bool timed = p->timing;
+    const bool timed = p->timing && count;
     // kPassShort is this function's own choice, never a caller's.
     if (pass < HX_PASS_AUTO || pass > HX_PASS_SPECULATE)
         return fail(HX_E_INVALID, "pass_mode %d unknown", pass);
@@ -1295,16 +1296,20 @@ hx_status hx_edge_detect(hx_pipeline* p, const hx_image* img, float* d_max,
     hx_schedule s = choose_schedule(p, img->height, img->width);
     st = validate_schedule(p, s);
     if (st != HX_OK) return st;
-    // SPECULATE chosen by size alone rebuilds a table that the host keeps;
-    // a call recorded into a graph takes STORE, which needs none.
-    if (s.fusion_depth == 4 && s.pass_mode == HX_PASS_SPECULATE && !p->forced &&
-        !p->prm.pass_mode && !p->tuned.count(shape_class(img->height, img->width)) &&
-        capture_id(stream))
-        s = store_schedule(img->height, img->width);
+    DeviceGuard g(p->device);
+    // SPECULATE chosen by size alone: a call recorded into a graph takes
+    // STORE, which keeps no batch context, and the timing mode of batched
+    // calls does not count the others.
+    const bool by_size = s.fusion_depth == 4 && s.pass_mode == HX_PASS_SPECULATE && !p->forced &&
+                         !p->prm.pass_mode &&
+                         !p->tuned.count(shape_class(img->height, img->width));
+    const bool speculate = by_size && !capture_id(stream);
+    if (by_size && !speculate) s = store_schedule(img->height, img->width);
     TraceRange trace("hx.edge_detect");
     logf(2, "per-image call %lldx%lld: %s", (long long)img->height, (long long)img->width,
          schedule_text(s).c_str());
-    DeviceGuard g(p->device);
+    if (speculate)
+        return run_batched(p, img, 1, d_max, HX_PASS_SPECULATE, s.tile_h, stream, -1, false);
     return run_image_ordered(p, img, d_max, s, stream);
 }
 

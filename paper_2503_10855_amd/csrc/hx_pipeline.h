@@ -232,10 +232,10 @@ constexpr int kBatchPass = HX_PASS_SPECULATE;
 // the one the context policy picks; the batch autotuner uses it to keep
 // one batch in flight per context.  A call recorded into a graph keeps its
 // context for good; when only one is left for the calls that run at once, it
-// runs image by image without one.
+// runs image by image without one.  count: timing mode applies to it.
 hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
                       float* d_max, int pass_mode, int ty, hipStream_t stream,
-                      int ctx = -1);
+                      int ctx = -1, bool count = true);
 // Contexts that no recorded call holds.
 int free_contexts(const hx_pipeline* p);
 // Wait for a context's last launch.
