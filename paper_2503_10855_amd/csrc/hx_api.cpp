@@ -930,6 +930,7 @@ hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
     BatchContext& c = p->ctx[pick];
     c.last_use = ++p->use_clock;
     hx_status st = HX_OK;
+    hipEvent_t done = c.ev_done;   // this call's
     if (same && c.in_flight && !timed) {
         // Nothing on the host changes: the stream waits for the context's
         // previous call (no wait at all if that is this stream's own).  The
@@ -940,13 +941,20 @@ hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
         // (32-row tiles 0.146..0.150 against 0.138..0.141 ms a call).
         HX_TRY(hipStreamWaitEvent(stream, c.ev_done, 0));
         if (pass != kPassShort) {
-            std::swap(c.ev_done, c.ev_prev);
-            HX_TRY(hipEventSynchronize(c.ev_done));
+            HX_TRY(hipEventSynchronize(c.ev_prev));
+            done = c.ev_prev;
         }
     } else {
         st = ctx_wait(c);
         if (st != HX_OK) return st;
     }
+    // A call that failed may have queued some of its launches, behind the
+    // previous call's: the context is busy until they end.
+    auto busy = [&](hx_status failed) {
+        if (hipEventRecord(c.ev_done, stream) != hipSuccess) (void)hipStreamSynchronize(stream);
+        c.in_flight = true;
+        return failed;
+    };
 
     // The common case: the whole batch fits the context.
     ImgWork tot;
@@ -979,8 +987,9 @@ hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
              fits(p->caps, tot, pass) ? "" : ", split into groups");
     }
     if (fits(p->caps, tot, pass)) {
-        st = launch_on(p, c, imgs, n, d_max, pass, geo, same, stream, timed, c.ev_done);
-        if (st != HX_OK) return st;
+        st = launch_on(p, c, imgs, n, d_max, pass, geo, same, stream, timed, done);
+        if (st != HX_OK) return busy(st);
+        if (done != c.ev_done) std::swap(c.ev_done, c.ev_prev);
         c.default_ty = want_ty == 0;
     } else {
         // Consecutive groups that fit, one after another on this context
@@ -1014,7 +1023,7 @@ hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
                 c.last_pass = -1;
                 i = j;
             }
-            if (st != HX_OK) return st;
+            if (st != HX_OK) return busy(st);
             HX_TRY(hipEventRecord(c.ev_done, stream));
             c.in_flight = true;
             if (i < n) {

@@ -92,7 +92,7 @@ struct BatchContext {
     DevBuf code;                // pass-1 store buffer (STORE batches)
     DevBuf cand_code, cand_row; // SPECULATE: listed pixels
     hipEvent_t ev_done = nullptr;
-    hipEvent_t ev_prev = nullptr;   // of the call before, or complete
+    hipEvent_t ev_prev = nullptr;   // of an earlier call
     hipEvent_t ev_t[5] = {};    // timing mode
     bool in_flight = false;
     // A call recorded into a graph reads this context's table and scratch at
