@@ -151,11 +151,12 @@ def _stream(stream):
 
 
 def image_desc(src: torch.Tensor, mask: torch.Tensor) -> Image:
-    ss, ms, shape = src.stride(), mask.stride(), src.shape
-    if src.dtype != torch.float32 or len(ss) != 2 or ss[1] != 1:
+    # The type first: what is no float32 tensor may have no strides.
+    if src.dtype != torch.float32 or len(ss := src.stride()) != 2 or ss[1] != 1:
         raise TypeError("src must be a 2-D float32 tensor with unit column stride")
-    if mask.dtype != torch.uint8 or len(ms) != 2 or ms[1] != 1:
+    if mask.dtype != torch.uint8 or len(ms := mask.stride()) != 2 or ms[1] != 1:
         raise TypeError("mask must be a 2-D uint8 tensor with unit column stride")
+    shape = src.shape
     if mask.shape != shape:
         raise ValueError("mask and src shapes differ")
     if not (src.is_cuda and mask.is_cuda):
