@@ -322,7 +322,8 @@ hx_status hx_autotune(hx_pipeline* p, int64_t height, int64_t width,
 /* The batch autotuner: times the batched call on the caller's batch (imgs,
  * n: as hx_edge_detect_batched; their masks are written, with the same
  * bits as any schedule gives) under every candidate -- sweep tile heights
- * 16..160 rows x pass structures SPECULATE, RECOMPUTE and, when the
+ * 16..160 rows x pass structures SPECULATE (at 32..80 rows with either of
+ * two kernels for its last pass), RECOMPUTE and, when the
  * pipeline holds HX_FORM_BATCH_STORE, STORE -- and keeps the one with the
  * highest throughput for the batch's class (floor(log2) of its total
  * pixels and of n): the time per call with batch_contexts calls in flight

@@ -336,12 +336,20 @@ constexpr int kRedoC = 2, kRedoRows = 8;
 // 8 rows at a time.  64 x 1080p 19 us, 256 uneven images 21.6; as workgroups
 // of four waves with 32 KB that shared a run of lists 19 and 23.6, and four
 // calls in flight took 0.157 ms each, not 0.150.
-template <int KS>
+// CLAIM: the same with 128 registers claimed, so that its waves take places of
+// another call's pass 1 (136 registers, three on a SIMD) instead of squeezing
+// in beside it.  Which is faster with calls in flight depends on how their
+// rounds of tiles fall together, so the batch tuner tries both.  us a call,
+// beside / claimed: 64 x 1080p k5 on 3 and 4 streams 161 / 147 and 137..150 /
+// 132, 2 streams 163 / 165, alone 183.4 / 184.7; 200 images of 64..2048 on 2
+// and 4 streams 105 / 114 and 97 / 101; 256 x 512x512 on 2 streams 97 / 105.
+template <int KS, bool CLAIM>
 __global__ __launch_bounds__(64)
 void k_batch_p2s(const uint8_t* __restrict__ table, Taps tp) {
     using S = SweepShape<KS, kBC, SM_SPEC>;
     using RS = TileShape<KS, kRedoC, SM_MASK>;
     __shared__ __align__(16) float rows[RS::lds_floats(kRedoRows)];
+    if constexpr (CLAIM) asm volatile("" ::: "v127");
     const TableView tv = view(table);
     const int lane = lane_id();
     const int k = xcd_remap(blockIdx.x, gridDim.x);

@@ -568,8 +568,8 @@ hx_status ctx_wait(BatchContext& c) {
 // with `timed`, bracket each launch with the context's timing events
 // (ev_t: 0 reset 1 pass-0 4 pass-1 2 pass-2 3).  Grids are sized to the
 // batch (measured faster than persistent workgroups striding over items).
-static hipError_t enqueue_phases(hx_pipeline* p, BatchContext& c, int pass, hipStream_t s,
-                                 bool timed, hipEvent_t done) {
+static hipError_t enqueue_phases(hx_pipeline* p, BatchContext& c, int pass, bool claim,
+                                 hipStream_t s, bool timed, hipEvent_t done) {
     const int ks = p->prm.ksize;
     hipError_t e = timed ? hipEventRecord(c.ev_t[0], s) : hipSuccess;
     if (e == hipSuccess && pass != HX_PASS_SPECULATE)
@@ -583,7 +583,7 @@ static hipError_t enqueue_phases(hx_pipeline* p, BatchContext& c, int pass, hipS
     if (e == hipSuccess && timed) e = hipEventRecord(c.ev_t[2], s);
     if (e == hipSuccess)
         e = launch_batch_phase(ks, pass, 2, c.last_ty, c.n_items[2], c.table.ptr, p->taps, s,
-                               done);
+                               done, claim);
     if (e == hipSuccess && timed) e = hipEventRecord(c.ev_t[3], s);
     return e;
 }
@@ -771,7 +771,7 @@ static hx_status enqueue_short(hx_pipeline* p, BatchContext& c, hipStream_t stre
 // already if `same`.  timed: between timing events.  done: completed by the
 // last kernel itself (nullable).
 static hx_status launch_on(hx_pipeline* p, BatchContext& c, const hx_image* imgs, int32_t n,
-                           float* d_max, int pass, const SweepGeom& geo, bool same,
+                           float* d_max, int pass, bool claim, const SweepGeom& geo, bool same,
                            hipStream_t stream, bool timed, hipEvent_t done) {
     if (!same) {
         TraceRange tr("hx.batch.table");
@@ -787,7 +787,7 @@ static hx_status launch_on(hx_pipeline* p, BatchContext& c, const hx_image* imgs
         if (st != HX_OK) return st;
     } else {
         c.dirty[0] = std::max(c.dirty[0], c.n_ways);
-        HX_TRY(enqueue_phases(p, c, pass, stream, timed, done));
+        HX_TRY(enqueue_phases(p, c, pass, claim, stream, timed, done));
     }
     if (timed) p->last_timed_ctx = (int)(&c - p->ctx);
     logf(2, "batch context %d: %d images, items %lld / %lld / %lld (pass 1 / 2 / 0), %s%s",
@@ -803,7 +803,7 @@ static hx_status launch_on(hx_pipeline* p, BatchContext& c, const hx_image* imgs
 // and a batch beyond a table, are left alone: then image by image, with
 // nothing in the graph that a later call rewrites.
 static hx_status record_batch(hx_pipeline* p, const hx_image* imgs, int32_t n, float* d_max,
-                              int pass, const SweepGeom& geo, hipStream_t stream,
+                              int pass, bool claim, const SweepGeom& geo, hipStream_t stream,
                               unsigned long long capture) {
     ImgWork tot;
     for (int i = 0; i < n; ++i) {
@@ -820,7 +820,7 @@ static hx_status record_batch(hx_pipeline* p, const hx_image* imgs, int32_t n, f
         hx_status st = ctx_wait(*c);
         if (st != HX_OK) return st;
         c->recorded = true;
-        return launch_on(p, *c, imgs, n, d_max, pass, geo, false, stream, false, nullptr);
+        return launch_on(p, *c, imgs, n, d_max, pass, claim, geo, false, stream, false, nullptr);
     }
     hx_status st = img_order_begin(p, stream, capture);
     for (int i = 0; i < n && st == HX_OK; ++i)
@@ -849,7 +849,7 @@ constexpr int64_t kNarrowPixels = int64_t(1) << 19;
 
 hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
                       float* d_max, int pass, int ty, hipStream_t stream, int ctx,
-                      bool count) {
+                      bool count, int claim) {
     const int ks = p->prm.ksize;
     const bool timed = p->timing && count;
     // kPassShort is this function's own choice, never a caller's.
@@ -864,6 +864,7 @@ hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
             if (!ty) {
                 ty = it->second.ty;
                 ty_from = "tuned";
+                if (claim < 0) claim = it->second.claim;
             }
             // A tuned STORE needs the STORE plane; without it the default
             // pass structure runs.
@@ -926,7 +927,7 @@ hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
     if (pass == HX_PASS_STORE && !has_form(p, HX_FORM_BATCH_STORE))
         return fail(HX_E_UNSUPPORTED,
                     "batched STORE needs a pipeline created with HX_FORM_BATCH_STORE");
-    if (capture) return record_batch(p, imgs, n, d_max, pass, geo, stream, capture);
+    if (capture) return record_batch(p, imgs, n, d_max, pass, claim > 0, geo, stream, capture);
     BatchContext& c = p->ctx[pick];
     c.last_use = ++p->use_clock;
     hx_status st = HX_OK;
@@ -987,7 +988,7 @@ hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
              fits(p->caps, tot, pass) ? "" : ", split into groups");
     }
     if (fits(p->caps, tot, pass)) {
-        st = launch_on(p, c, imgs, n, d_max, pass, geo, same, stream, timed, done);
+        st = launch_on(p, c, imgs, n, d_max, pass, claim > 0, geo, same, stream, timed, done);
         if (st != HX_OK) return busy(st);
         if (done != c.ev_done) std::swap(c.ev_done, c.ev_prev);
         c.default_ty = want_ty == 0;
@@ -1018,8 +1019,8 @@ hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
                 c.last_pass = -1;  // the table no longer matches any batch
                 ++i;
             } else {
-                st = launch_on(p, c, imgs + i, j - i, d_max ? d_max + i : nullptr, pass, geo,
-                               false, stream, timed, nullptr);
+                st = launch_on(p, c, imgs + i, j - i, d_max ? d_max + i : nullptr, pass,
+                               claim > 0, geo, false, stream, timed, nullptr);
                 c.last_pass = -1;
                 i = j;
             }

@@ -261,9 +261,10 @@ hipError_t launch_batch_short(int ks, int c, int phase, const ShortArgs& s, cons
 // ty the batch's tile height.  Phase 0 exists for SPECULATE only.  done
 // (nullable; here and in launch_batch_short): an event the last kernel
 // completes by itself, which saves the stream a marker of its own (about 1
-// us, and 0.6 us of host time).
+// us, and 0.6 us of host time).  claim: SPECULATE's pass 2 as the kernel that
+// claims registers (k_batch_p2s).
 hipError_t launch_batch_phase(int ks, int pass_mode, int phase, int ty, int64_t items,
                               const void* d_table, const Taps& t, hipStream_t s,
-                              hipEvent_t done = nullptr);
+                              hipEvent_t done = nullptr, bool claim = false);
 
 }  // namespace hx

@@ -120,10 +120,12 @@ struct BatchKey {
     bool operator<(const BatchKey& o) const { return px != o.px ? px < o.px : n < o.n; }
 };
 BatchKey batch_key(const hx_image* imgs, int32_t n);
-// The batched launch's schedule: rows per sweep tile and pass structure.
+// The batched launch's schedule: rows per sweep tile, pass structure, and
+// which of SPECULATE's two pass 2 kernels.
 struct BatchChoice {
     int ty = 0;
     int pass = 0;
+    int claim = 0;
 };
 // Tile heights the batched form accepts (multiples of 8 in [kBatchTyMin,
 // kBatchTyMax]) and the ones the batch autotuner tries.
@@ -233,9 +235,10 @@ constexpr int kBatchPass = HX_PASS_SPECULATE;
 // one batch in flight per context.  A call recorded into a graph keeps its
 // context for good; when only one is left for the calls that run at once, it
 // runs image by image without one.  count: timing mode applies to it.
+// claim: BatchChoice's, -1 the tuned one (else 0).
 hx_status run_batched(hx_pipeline* p, const hx_image* imgs, int32_t n,
                       float* d_max, int pass_mode, int ty, hipStream_t stream,
-                      int ctx = -1, bool count = true);
+                      int ctx = -1, bool count = true, int claim = -1);
 // Contexts that no recorded call holds.
 int free_contexts(const hx_pipeline* p);
 // Wait for a context's last launch.

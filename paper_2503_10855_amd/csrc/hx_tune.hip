@@ -83,21 +83,24 @@ std::vector<hx_schedule> candidates(int ks) {
 }
 
 // Batch candidates: tile heights x pass structures (STORE only where the
-// pipeline holds its code planes).
+// pipeline holds its code planes), SPECULATE at the usual heights with either
+// pass 2.
 std::vector<BatchChoice> batch_candidates(const hx_pipeline* p) {
     std::vector<BatchChoice> c;
     std::vector<int> passes = {HX_PASS_SPECULATE, HX_PASS_RECOMPUTE};
     if (p->prm.forms & HX_FORM_BATCH_STORE) passes.push_back(HX_PASS_STORE);
     for (int pass : passes)
         for (int ty : {16, 24, 32, 48, 64, 72, 80, 96, 112, 128, 160})
-            c.push_back(BatchChoice{ty, pass});
+            for (int claim = 0; claim < (pass == HX_PASS_SPECULATE && ty >= 32 && ty <= 80 ? 2 : 1);
+                 ++claim)
+                c.push_back(BatchChoice{ty, pass, claim});
     return c;
 }
 
 bool parse_batch_entry(const char* line, int* ks, BatchKey* k, BatchChoice* c) {
     return std::sscanf(line, " {\"batch\": {\"ksize\": %d, \"px_log2\": %d, \"n_log2\": %d, "
-                             "\"tile_h\": %d, \"pass\": %d",
-                       ks, &k->px, &k->n, &c->ty, &c->pass) == 5;
+                             "\"tile_h\": %d, \"pass\": %d, \"claim\": %d",
+                       ks, &k->px, &k->n, &c->ty, &c->pass, &c->claim) >= 5;
 }
 
 // Minimal reader for the cache lines this file writes.
@@ -288,7 +291,8 @@ hx_status hx_autotune_batch(hx_pipeline* p, const hx_image* imgs, int32_t n,
         const auto t_end = std::chrono::steady_clock::now() + std::chrono::milliseconds(30);
         int k = 0;
         while (st == HX_OK && (k < 3 * S || std::chrono::steady_clock::now() < t_end)) {
-            st = run_batched(p, imgs, n, nullptr, cands[0].pass, cands[0].ty, st_[k % S], k % S);
+            st = run_batched(p, imgs, n, nullptr, cands[0].pass, cands[0].ty, st_[k % S], k % S, true,
+                             cands[0].claim);
             if (++k % S == 0 && st == HX_OK)
                 for (int i = 0; i < S && st == HX_OK; ++i)
                     if ((e = hipStreamSynchronize(st_[i])) != hipSuccess)
@@ -298,14 +302,14 @@ hx_status hx_autotune_batch(hx_pipeline* p, const hx_image* imgs, int32_t n,
     for (const BatchChoice& c : cands) {
         // Untimed: three calls per stream (each context builds its table).
         for (int r = 0; r < 3 * S && st == HX_OK; ++r)
-            st = run_batched(p, imgs, n, nullptr, c.pass, c.ty, st_[r % S], r % S);
+            st = run_batched(p, imgs, n, nullptr, c.pass, c.ty, st_[r % S], r % S, true, c.claim);
         for (int i = 0; i < S && st == HX_OK; ++i)
             if ((e = hipStreamSynchronize(st_[i])) != hipSuccess)
                 st = hip_fail(e, "batch autotune warm-up");
         std::vector<float> ms;
         for (int r = 0; r < 5 && st == HX_OK; ++r) {
             e = hipEventRecord(e0, s);
-            if (e == hipSuccess) st = run_batched(p, imgs, n, nullptr, c.pass, c.ty, s, 0);
+            if (e == hipSuccess) st = run_batched(p, imgs, n, nullptr, c.pass, c.ty, s, 0, true, c.claim);
             if (e == hipSuccess && st == HX_OK) e = hipEventRecord(e1, s);
             float t = 0.0f;
             if (e != hipSuccess) st = hip_fail(e, "batch autotune timing");
@@ -322,7 +326,7 @@ hx_status hx_autotune_batch(hx_pipeline* p, const hx_image* imgs, int32_t n,
             e = hipEventRecord(e0, s);
             for (int i = 1; i < S && e == hipSuccess; ++i) e = hipStreamWaitEvent(st_[i], e0, 0);
             for (int k = 0; k < K && e == hipSuccess && st == HX_OK; ++k)
-                st = run_batched(p, imgs, n, nullptr, c.pass, c.ty, st_[k % S], k % S);
+                st = run_batched(p, imgs, n, nullptr, c.pass, c.ty, st_[k % S], k % S, true, c.claim);
             for (int i = 1; i < S && e == hipSuccess && st == HX_OK; ++i) {
                 e = hipEventRecord(done_[i], st_[i]);
                 if (e == hipSuccess) e = hipStreamWaitEvent(s, done_[i], 0);
@@ -337,9 +341,11 @@ hx_status hx_autotune_batch(hx_pipeline* p, const hx_image* imgs, int32_t n,
         std::sort(ms.begin(), ms.end());
         std::sort(tp.begin(), tp.end());
         const Trial t{c, ms[ms.size() / 2], tp[tp.size() / 2]};
-        logf(1, "batch tuner: %d-row tiles, pass %d: %.4f ms per call with %d in flight, "
-             "%.4f ms alone", c.ty, c.pass, t.tput_ms, S, t.ms);
-        trials.push_back(t);
+        logf(1, "batch tuner: %d-row tiles, pass %d%s: %.4f ms per call with %d in flight, "
+             "%.4f ms alone", c.ty, c.pass, c.claim ? " claiming" : "", t.tput_ms, S, t.ms);
+        // One trial per tile height and pass structure: the faster pass 2.
+        if (!c.claim) trials.push_back(t);
+        else if (t.tput_ms < trials.back().tput_ms) trials.back() = t;
         if (t.tput_ms < best_ms) {
             best_ms = t.tput_ms;
             best = c;
@@ -364,14 +370,15 @@ hx_status hx_autotune_batch(hx_pipeline* p, const hx_image* imgs, int32_t n,
         for (const Trial& t : trials)
             std::fprintf(f,
                          "{\"batch_trial\": {\"ksize\": %d, \"px_log2\": %d, \"n_log2\": %d, "
-                         "\"tile_h\": %d, \"pass\": %d, \"ms\": %.5f, \"tput_ms\": %.5f, "
-                         "\"in_flight\": %d, \"pixels\": %lld, \"images\": %d}}\n",
-                         p->prm.ksize, key.px, key.n, t.c.ty, t.c.pass, t.ms, t.tput_ms, S,
-                         (long long)total, n);
+                         "\"tile_h\": %d, \"pass\": %d, \"claim\": %d, \"ms\": %.5f, "
+                         "\"tput_ms\": %.5f, \"in_flight\": %d, \"pixels\": %lld, "
+                         "\"images\": %d}}\n",
+                         p->prm.ksize, key.px, key.n, t.c.ty, t.c.pass, t.c.claim, t.ms,
+                         t.tput_ms, S, (long long)total, n);
         std::fprintf(f,
                      "{\"batch\": {\"ksize\": %d, \"px_log2\": %d, \"n_log2\": %d, "
-                     "\"tile_h\": %d, \"pass\": %d, \"tput_ms\": %.5f}}\n",
-                     p->prm.ksize, key.px, key.n, best.ty, best.pass, best_ms);
+                     "\"tile_h\": %d, \"pass\": %d, \"claim\": %d, \"tput_ms\": %.5f}}\n",
+                     p->prm.ksize, key.px, key.n, best.ty, best.pass, best.claim, best_ms);
         std::fclose(f);
     }
     return HX_OK;
@@ -389,7 +396,8 @@ hx_status hx_autotune_load(hx_pipeline* p, const char* cache_path) {
         BatchChoice bc{};
         if (parse_batch_entry(line, &ks, &bk, &bc)) {
             if (ks == p->prm.ksize && bc.ty >= kBatchTyMin && bc.ty <= kBatchTyMax &&
-                bc.ty % 8 == 0 && bc.pass >= HX_PASS_STORE && bc.pass <= HX_PASS_SPECULATE) {
+                bc.ty % 8 == 0 && bc.pass >= HX_PASS_STORE && bc.pass <= HX_PASS_SPECULATE &&
+                (bc.claim == 0 || bc.claim == 1)) {
                 p->batch_tuned[bk] = bc;
                 ++loaded;
             }

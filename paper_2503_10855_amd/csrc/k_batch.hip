@@ -36,7 +36,7 @@ hipError_t launch_batch_reset(const void* d_table, int max_images, hipStream_t s
     return hipGetLastError();
 }
 
-#define HX_DECL(K, P) const void* batch_kernel_k##K##_p##P(int pass, int phase, bool short_tile);
+#define HX_DECL(K, P) const void* batch_kernel_k##K##_p##P(int pass, int phase, bool alt);
 #define HX_DECL_K(K) HX_DECL(K, 0) HX_DECL(K, 1) HX_DECL(K, 2) HX_DECL(K, 3)
 HX_DECL_K(3)
 HX_DECL_K(5)
@@ -44,10 +44,10 @@ HX_DECL_K(7)
 #undef HX_DECL_K
 #undef HX_DECL
 
-static const void* batch_kernel_ptr(int ks, int pass, int phase, bool short_tile) {
+static const void* batch_kernel_ptr(int ks, int pass, int phase, bool alt) {
     const void* k = nullptr;
 #define HX_P(K, P) \
-    if (ks == K && !k) k = batch_kernel_k##K##_p##P(pass, phase, short_tile);
+    if (ks == K && !k) k = batch_kernel_k##K##_p##P(pass, phase, alt);
 #define HX_PK(K) HX_P(K, 0) HX_P(K, 1) HX_P(K, 2) HX_P(K, 3)
     HX_PK(3) HX_PK(5) HX_PK(7)
 #undef HX_PK
@@ -75,10 +75,10 @@ hipError_t launch_batch_short(int ks, int c, int phase, const ShortArgs& s, cons
 
 hipError_t launch_batch_phase(int ks, int pass_mode, int phase, int ty, int64_t items,
                               const void* d_table, const Taps& t, hipStream_t s,
-                              hipEvent_t done) {
+                              hipEvent_t done, bool claim) {
     const bool spec = pass_mode == HX_PASS_SPECULATE;
     const bool short_tile = spec && phase == 1 && ty <= kShortTile;
-    const void* k = batch_kernel_ptr(ks, pass_mode, phase, short_tile);
+    const void* k = batch_kernel_ptr(ks, pass_mode, phase, short_tile || (spec && phase == 2 && claim));
     if (!k || items < 0) return hipErrorInvalidValue;
     const int64_t grid = items < 1 ? 1 : items;
     int lds = 0;
