@@ -269,10 +269,12 @@ hx_status hx_autotune_batch(hx_pipeline* p, const hx_image* imgs, int32_t n,
     }
     hipStream_t s = st_[0];
     const BatchKey key = batch_key(imgs, n);
+    // One per tile height and pass structure, the faster pass 2's.
     struct Trial {
         BatchChoice c;
         float ms;       // one call alone: median of five
         float tput_ms;  // per call with S calls in flight: median of three runs
+        float by_claim[2];   // tput_ms of each pass 2
     };
     std::vector<Trial> trials;
     BatchChoice best{};
@@ -340,16 +342,15 @@ hx_status hx_autotune_batch(hx_pipeline* p, const hx_image* imgs, int32_t n,
         if (st != HX_OK) break;
         std::sort(ms.begin(), ms.end());
         std::sort(tp.begin(), tp.end());
-        const Trial t{c, ms[ms.size() / 2], tp[tp.size() / 2]};
+        Trial t{c, ms[ms.size() / 2], tp[tp.size() / 2], {1e30f, 1e30f}};
         logf(1, "batch tuner: %d-row tiles, pass %d%s: %.4f ms per call with %d in flight, "
              "%.4f ms alone", c.ty, c.pass, c.claim ? " claiming" : "", t.tput_ms, S, t.ms);
-        // One trial per tile height and pass structure: the faster pass 2.
+        if (c.claim) std::copy_n(trials.back().by_claim, 2, t.by_claim);
+        t.by_claim[c.claim] = t.tput_ms;
         if (!c.claim) trials.push_back(t);
         else if (t.tput_ms < trials.back().tput_ms) trials.back() = t;
-        if (t.tput_ms < best_ms) {
-            best_ms = t.tput_ms;
-            best = c;
-        }
+        else trials.back().by_claim[1] = t.tput_ms;
+        if (trials.back().tput_ms < best_ms) best_ms = trials.back().tput_ms;
     }
     for (int i = 0; i < S; ++i) {
         const hipError_t ei = hipStreamSynchronize(st_[i]);
@@ -359,6 +360,16 @@ hx_status hx_autotune_batch(hx_pipeline* p, const hx_image* imgs, int32_t n,
     if (st != HX_OK) return st;
     if (e != hipSuccess) return hip_fail(e, "batch autotune");
     if (best_ms >= 1e30f) return fail(HX_E_UNSUPPORTED, "no batch schedule could run");
+    for (const Trial& t : trials)
+        if (t.tput_ms == best_ms) {
+            // The light pass 2 has to be 2 % faster to be chosen: its time with
+            // calls in flight differs more between sets of streams (64 x 1080p
+            // on 4: 137..151 us a call, claiming 132..141), and the caller's
+            // are others than these.
+            best = t.c;
+            best.claim = t.by_claim[1] < 1.02f * t.by_claim[0];
+            break;
+        }
     p->batch_tuned[key] = best;
     logf(1, "batch tuner: class (2^%d px, 2^%d images) -> %d-row tiles, pass %d", key.px,
          key.n, best.ty, best.pass);
