@@ -67,7 +67,7 @@ typedef struct hx_server hx_server;
  *  RECOMPUTE:  pass 1 computes blur and Sobel only, for the max; pass 2
  *              recomputes every stage and writes the mask directly.
  *  SPECULATE:  pass 0 computes G^2 on sampled row bands (8 rows at the
- *              top of every min(clamp(H/32, 128, 256), max(H/4, 8))
+ *              top of every min(clamp(H/32, 192, 256), max(H/4, 8))
  *              rows) for a lower
  *              bound m <= max G^2 of each image; pass 1 computes every
  *              stage once, writes the mask against the threshold of m (a
@@ -112,9 +112,12 @@ typedef struct {
  * by max_pixels and max_images; a call of a form the pipeline was created
  * without returns HX_E_UNSUPPORTED and enqueues nothing.
  *  IMAGE:        per-image calls at fusion depth 4 (STORE / RECOMPUTE):
- *                one max slot and a pass-1 code plane (4 B per pixel).
+ *                max slots and two pass-1 code planes (8 B per pixel), a
+ *                shared one and one of the first stream's own.
  *  STAGES:       fusion depths 1-3, the stage hook, the reduction variants:
- *                B, L, G^2 and Z planes (13 B per pixel) and the tree's
+ *                B, L, G^2 and Z planes (13 B per pixel, B's also the
+ *                shared code plane of IMAGE), the own code plane of IMAGE
+ *                (4 B; with ksize above 7 two planes, 8 B) and the tree's
  *                partial maxima.
  *  BATCH:        batched calls (and per-image SPECULATE): per batch context
  *                the max slots, bounds, descriptor table and its pinned
@@ -246,7 +249,7 @@ hx_status hx_pipeline_get_schedule(const hx_pipeline* p, int64_t height,
  * share one set: such a call on a different stream from the previous one
  * first makes its stream wait for that call's work, so calls on several
  * streams are correct but need not overlap.  (SPECULATE per-image calls use
- * the batch contexts instead.)  A call recorded into a graph (on a stream
+ * the batch contexts instead, and wait for one as batched calls do.)  A call recorded into a graph (on a stream
  * under capture) shares that set's planes but not its max slots; replays are
  * not calls, so the caller orders them against the set's other calls that
  * may overlap them (on one stream they are in order). */

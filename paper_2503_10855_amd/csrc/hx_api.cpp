@@ -189,16 +189,17 @@ static hx_schedule store_schedule(int64_t H, int64_t W) {
 // tiles of 48 rows: 48 rows (fewer halo rows computed) where that gives the
 // chip more than a round of its 3072 wave slots, shorter ones where it does
 // not; 16 rows run the short sweep.  Whole calls, us, at 16 / 24 / 32 / 48 /
-// 64 rows (the upper rows before the launches and slots got cheaper):
-//   192 (16 x 256x256 k5)          30.7  31.8  34.9  41.3  48.0
-//   368 (2 x 1080x1920 k5)         30.8  28.5  31.9  38.3  44.3
-//   829 (64 of 64..1024 k5)        50.4  47.7  53.3  66.1  78.5
-//   1462 (4096x4096 k5)                  36.2  41.8  40.4  50.8
-//   1472 (8 x 1080x1920 k5)        62.4  39.8  41.2  42.3  49.9
-//   2038 (64 of 64..2048 k5)       82.1  62.1  57.8  64.1  74.0
-//   3150 (6000x6000 k5)                  68.4  63.7  71.3  65.6
-//   5985 (8192x8192 k5)                 104.3 101.0  96.7 100.5
-//   11776 (64 x 1080x1920 k5)                 183.2 178.5 186.8
+// 64 rows, the chosen one marked *:
+//   192 (16 x 256x256 k5)          27.7*  29.9   28.3   39.5   42.0
+//   368 (2 x 1080x1920 k5)         27.1   27.5*  29.2   35.2   41.8
+//   800 (64 of 64..1024 k5)        48.0   42.8*  47.5   52.9   62.5
+//   1462 (4096x4096 k5)            58.6   35.8*  41.1   39.6   50.1
+//   1472 (8 x 1080x1920 k5)        57.9   38.3*  39.8   41.3   48.9
+//   2659 (64 of 64..2048 k5)       93.0   65.3   66.3*  69.1   75.5
+//   3125 (6000x6000 k5)           107.7   61.3   53.9*  60.8   55.9
+//   5814 (8192x8192 k5)           183.9  106.3  101.6   95.4* 101.0
+//   8534 (256 of 64..2048 k5)     251.1  160.0  155.0  158.0* 165.1
+//   11776 (64 x 1080x1920 k5)     318.8  190.2  186.8  186.0* 190.4
 static int spec_ty(int64_t tiles) {
     return tiles <= 256 ? 16 : tiles <= 1700 ? 24 : tiles <= 4096 ? 32 : 48;
 }

@@ -131,7 +131,8 @@ hipError_t launch_fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t s);
 hipError_t launch_sweep(int mode, int ks, int c, int ty, const ImgArgs& a,
                         const Taps& t, float theta, hipStream_t s);
 // The short sweep (tile_impl.h): SM_STORE or TM_STAGES for ks 1, 3, 5, 7,
-// TM_BLUR for the larger sizes; c columns per lane, ty rows per tile (even).
+// TM_BLUR for the larger sizes; c columns per lane, ty rows per tile (a
+// multiple of 4, at most 32).
 hipError_t launch_tile(int mode, int ks, int c, int ty, const ImgArgs& a, const Taps& t,
                        const StageOut& so, hipStream_t s);
 // Pass 2 of STORE: code -> mask, and M into dmax.

@@ -86,7 +86,7 @@ struct BatchContext {
     DevBuf table;               // device descriptor table
     HostBuf h_table;            // pinned staging copy of the table
     DevBuf state;               // the small arrays, SPECULATE's bounds and epoch first
-    uint32_t* slots = nullptr;  // in state: max_images max slots
+    uint32_t* slots = nullptr;  // in state: two sets of BatchCaps::ways max slots
     uint32_t* cand_n = nullptr; // SPECULATE: entries each tile listed
     int32_t* redo = nullptr;    // SPECULATE: tiles whose lists overflowed
     DevBuf code;                // pass-1 store buffer (STORE batches)
@@ -224,8 +224,8 @@ hx_status run_image_ordered(hx_pipeline* p, const hx_image* img, float* d_max,
                             const hx_schedule& s, hipStream_t stream, bool may_own = true);
 // Pass structure of batched calls unless one is fixed: SPECULATE reads
 // the input about 1.1 times (once, plus the sampled bands) and measured
-// fastest on the 64 x 1920x1080 batch (0.30 ms per step against 0.36 ms
-// for RECOMPUTE and 0.46 ms for STORE).
+// fastest on the 64 x 1920x1080 batch (0.186 ms a call against 0.288 ms
+// for RECOMPUTE and 0.387 ms for STORE).
 constexpr int kBatchPass = HX_PASS_SPECULATE;
 
 // The batched form.  pass_mode / ty 0: the batch autotuner's choice for

@@ -296,8 +296,9 @@ class Pipeline:
 
     def edge_detect_stages(self, src, stream=None, stages=("B", "L", "Z", "G")):
         """The stage hook: a dict of device tensors B, L, Z, G (those named in
-        `stages`), M and mask.  Depth 1 by default; under a forced depth-2
-        (depth-3) schedule L (B) is kept on chip and cannot be asked for."""
+        `stages`), M and mask.  One fused sweep by default; under a forced
+        depth-2 (depth-3) schedule L (B) is kept on chip and cannot be asked
+        for."""
         H, W = src.shape
         dev = src.device
         out = dict(M=torch.empty(1, dtype=torch.float32, device=dev),
