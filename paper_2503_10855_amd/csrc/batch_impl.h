@@ -276,9 +276,9 @@ void k_batch_p2(const uint8_t* __restrict__ table, Taps tp) {
 // small batch is bound by its launches and by what one wave takes for its
 // tile, so a third launch, and pass 1's wider tiles with their lists, cost
 // more than the second blur.  Whole calls, us, this form and SPECULATE: 16
-// images of 64..256 k3 14.5 and 24.4, 4 x 512x512 k5 17.1 and 28.0,
-// 1080x1920 k5 18.6 and 25.4, 2 of them 25.0 and 28.8, 3 of them 30.8 and
-// 32.0, 4 of them 39.8 and 33.8.  Each tile's arguments come from the launch
+// images of 64..256 k3 10.9 and 22.6, 4 x 512x512 k5 15.9 and 22.7,
+// 1080x1920 k5 17.3 and 23.2, 2 of them 22.2 and 25.7, 3 of them 27.8 and
+// 31.0, 4 of them 52.5 and 33.1.  Each tile's arguments come from the launch
 // where they can, which saves a chain of loads through the table's header.
 template <int KS, int C>
 __global__ __launch_bounds__(64) void k_batch_short_max(ShortArgs s, Taps tp) {

@@ -21,9 +21,9 @@ const void* HX_CAT(batch_kernel_k, HX_KS, _p, HX_PART)(int pass, int phase, bool
 #if HX_PART == 0
     if (pass == kPassShort)
         return phase == 1 ? (alt ? (const void*)k_batch_short_max<HX_KS, 1>
-                                        : (const void*)k_batch_short_max<HX_KS, 2>)
+                                 : (const void*)k_batch_short_max<HX_KS, 2>)
                           : (alt ? (const void*)k_batch_short_mask<HX_KS, 1>
-                                        : (const void*)k_batch_short_mask<HX_KS, 2>);
+                                 : (const void*)k_batch_short_mask<HX_KS, 2>);
     if (pass == HX_PASS_SPECULATE) {
         if (phase == 0) return (const void*)k_batch_p0<HX_KS>;
         if (phase == 1 && alt) return (const void*)k_batch_p1t<HX_KS>;

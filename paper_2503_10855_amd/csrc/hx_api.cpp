@@ -345,8 +345,8 @@ static hipError_t begin_slots(hx_pipeline* p, hx_pipeline::ImgScratch& sc, bool 
 // stage planes so (nullable) written on the way.  Blur sizes above 7 run
 // their blur as a sweep of its own and the rest on its plane (with the
 // one-tap blur, exactly the identity): 1080x1920 k9 77 us a call in five
-// unfused kernels (blur 26), 24 in these three (blur 7.8).  The stage hook
-// on 1080x1920 k5: 78 us in five kernels and a copy of the planes, 25 here.
+// unfused kernels (blur 26), 21 in these three (blur 8.6).  The stage hook
+// on 1080x1920 k5: 78 us in five kernels and a copy of the planes, 19 here.
 static hx_status run_short(hx_pipeline* p, const hx_image* img, float* d_max,
                            const StageOut* so, hx_pipeline::ImgScratch& scr,
                            hipStream_t stream) {
@@ -843,8 +843,8 @@ BatchKey batch_key(const hx_image* imgs, int32_t n) {
 
 // Batches of up to this many pixels run in two launches on short tiles
 // (k_batch_short_max has the figures), of one column per lane up to
-// kNarrowPixels: 16 images of 64..256 14.5 us a call with one, 15.2 with two;
-// 1 Mpx 17.1 and 17.5, 2.9 Mpx 33.8 and 19.3.
+// kNarrowPixels: 16 images of 64..256 10.9 us a call with one, 12.1 with two;
+// 1 Mpx 15.1 and 15.8, 2.1 Mpx 16.7 and 17.2, 4.1 Mpx 30.7 and 21.9.
 constexpr int64_t kShortBatchPixels = int64_t(6) << 20;
 constexpr int64_t kNarrowPixels = int64_t(1) << 19;
 
